@@ -1,0 +1,208 @@
+"""Performance cases of the HOT linear-layer backward: what a training program calls, over the
+range of layers it calls it on.
+
+A case is one pass of one layer:
+
+- ``step``: the forward-time activation compression, then both gradients
+  (``hot_compress_activation`` + ``hot_linear_backward``), as every trained layer runs once per step;
+- ``split``: the same with the two gradients asked for separately (``hot_linear_backward_gx`` and
+  ``hot_linear_backward_gw``), as a program does that schedules them apart;
+- ``frozen``: the activation gradient alone with weights quantised once
+  (``hot_linear_backward_gx_cached``), as LoRA-style fine-tuning runs its frozen base layers;
+- ``select``: the calibration of one layer's quantiser (``hot_select_quantizer``).
+
+Sizes (L tokens, O outputs, I inputs), value distributions and settings are those of the paper's
+latency table, of the benchmark workloads and of the tests; ``draw`` spreads over the same ranges.
+"""
+import zlib
+
+import torch
+
+import paper_2503_21261_amd as hot
+
+DEVICE = "cuda"
+ROUND = hot.HOT_ROUND_PSEUDO_STOCHASTIC
+QUANTIZER = {"token": hot.HOT_Q_PER_TOKEN, "tensor": hot.HOT_Q_PER_TENSOR}
+
+
+def _case(name, kind, L, O, I, block=16, sample=0, lp_l1=False, gx_bits=4, gw_bits=8, quantizer="token",
+          x="normal", g_y="normal"):
+    case = dict(kind=kind, L=L, O=O, I=I, block=block, sample=sample, lp_l1=lp_l1, gx_bits=gx_bits,
+                gw_bits=gw_bits, quantizer=quantizer, x=x, g_y=g_y)
+    if name:
+        case["name"] = name
+    return case
+
+
+def listed():
+    return [
+        # One image of 197 tokens through a ViT-B projection: the paper's own latency measurement,
+        # bound by launches and latencies.
+        _case("vitb_proj_1_image", "step", 197, 768, 768, sample=197, g_y="chan_outlier"),
+        # A small batch: 512 tokens through a square layer.
+        _case("linear_512_tokens", "step", 512, 768, 768, g_y="chan_outlier"),
+        # A mobile vision transformer's MLP at its 7 x 7 stage, 64 images, with the paper's LP_L1
+        # list of kept rows; samples of 49 tokens end in a padded block.
+        _case("mlp_49_tokens_64_images", "step", 64 * 49, 448, 1792, sample=49, lp_l1=True, g_y="tok_outlier"),
+        # Nothing a multiple of anything: ten sequences of 333 tokens, an odd input width.
+        _case("ragged_333_tokens_odd_width", "step", 10 * 333, 1008, 771, sample=333, quantizer="tensor"),
+        # ViT-B fc1 at batch 64, 32-row blocks.
+        _case("vitb_fc1_64_images", "step", 64 * 197, 3072, 768, block=32, x="bf16", g_y="t4"),
+        # ViT-B fc2 at batch 64 with the bfloat16 weight gradient, both gradients asked for separately.
+        _case("vitb_fc2_64_images_bf16_gw", "split", 64 * 197, 768, 3072, gw_bits=16, g_y="chan_outlier"),
+        # Pre-training warm-up (INT8 everywhere): ViT-B fc1 at batch 32, each image tiled by itself.
+        _case("vitb_fc1_32_images_int8_warmup", "step", 32 * 197, 3072, 768, sample=197, gx_bits=8, g_y="chan_outlier"),
+        # ViT-B qkv at batch 256; calibration chose one scale for the tensor.
+        _case("vitb_qkv_256_images_per_tensor", "step", 256 * 197, 2304, 768, quantizer="tensor", g_y="normal"),
+        # LoRA fine-tuning: the frozen LLM down-projection's activation gradient, one sequence.
+        _case("llm_down_frozen_2048_tokens", "frozen", 2048, 4096, 11008, block=64, g_y="t3"),
+        # Calibration of the LLM down-projection's quantiser on a whole batch.
+        _case("llm_down_calibration", "select", 16384, 4096, 11008, block=64, g_y="t3"),
+        # LLM up-projection, 8 x 2048 tokens: the large matrix products.
+        _case("llm_up_16384_tokens", "step", 16384, 11008, 4096, block=64, x="chan_outlier", g_y="t3"),
+        # ViT-L fc2 at batch 1024: the large streams (3.3 GB in, 3.3 GB out).
+        _case("vitl_fc2_1024_images", "step", 1024 * 197, 1024, 4096, x="bf16"),
+    ]
+
+
+def _blocks(case):
+    """Token blocks of the tensor: whole runs, or padded sample by sample."""
+    n, L, S = case["block"], case["L"], case["sample"]
+    return L // S * -(-S // n) if S else L // n
+
+
+def _reduced(case):
+    return _blocks(case) * (case["block"] // 2)
+
+
+def work(case):
+    """Compulsory traffic (every operand in once, every result out once; the compressed activation
+    out in the forward and in again in the backward) and integer operations of one pass."""
+    L, O, I, kind = case["L"], case["O"], case["I"], case["kind"]
+    if kind == "select":
+        return {"bytes": 4 * L * O, "flops": 0}
+    if kind == "frozen":
+        return {"bytes": 4 * L * O + O * I * case["gx_bits"] // 8 + 4 * L * I, "flops": 2 * L * O * I}
+    act = _reduced(case) * I * case["gw_bits"] // 8
+    return {"bytes": 4 * (L * I + L * O + O * I) + 2 * act + 4 * (L * I + O * I),
+            "flops": 2 * L * O * I + 2 * O * I * _reduced(case)}
+
+
+def _cost(case):
+    """Microseconds at round rates, to keep drawn cases below the largest listed one."""
+    w = work(case)
+    return w["bytes"] / 4e6 + w["flops"] / 2e9
+
+
+def draw(rng):
+    limit = max(_cost(c) for c in listed())
+
+    def spread(lo, hi):
+        return int(round(lo * (hi / lo) ** rng.random()))
+
+    while True:
+        block = rng.choice([16, 16, 32, 64])
+        kind = rng.choice(["step"] * 6 + ["split", "frozen", "select"])
+        O = max(block, spread(64, 11008) // block * block)
+        I = spread(64, 11008)
+        if rng.random() < 0.5:
+            I = max(64, I // 64 * 64)
+        tokens = spread(128, 201728)
+        if rng.random() < 0.4:
+            sample = rng.choice([49, 197, 333, 2048, spread(40, 2048)])
+            L = max(1, tokens // sample) * sample
+        else:
+            sample, L = 0, max(block, tokens // block * block)
+        case = _case(None, kind, L, O, I, block=block, sample=sample, lp_l1=rng.random() < 0.25,
+                     gx_bits=8 if rng.random() < 0.15 else 4, gw_bits=16 if rng.random() < 0.15 else 8,
+                     quantizer=rng.choice(["token", "tensor"]), x=rng.choice(["normal", "bf16", "chan_outlier"]),
+                     g_y=rng.choice(["normal", "chan_outlier", "tok_outlier", "t3", "t4"]))
+        if _cost(case) <= limit and _reduced(case) <= 133144:
+            return case
+
+
+def _normal(shape, std, seed, name):
+    g = torch.Generator(device=DEVICE)
+    g.manual_seed((seed * 1_000_003 + zlib.crc32(name.encode())) & 0x7FFF_FFFF_FFFF)
+    return torch.randn(shape, generator=g, device=DEVICE, dtype=torch.float32).mul_(std)
+
+
+def _picks(count, total, seed, name):
+    g = torch.Generator()
+    g.manual_seed((seed * 1_000_003 + zlib.crc32(name.encode())) & 0x7FFF_FFFF_FFFF)
+    return torch.randperm(total, generator=g)[:count].to(DEVICE)
+
+
+def _activation(case, seed):
+    x = _normal((case["L"], case["I"]), 1.0, seed, "x")
+    if case["x"] == "bf16":
+        x = x.to(torch.bfloat16).to(torch.float32)
+    elif case["x"] == "chan_outlier":   # 1 % of the channels twenty times as large
+        x[:, _picks(max(1, case["I"] // 100), case["I"], seed, "x.cols")] *= 20.0
+    return x
+
+
+def _gradient(case, seed):
+    shape, kind = (case["L"], case["O"]), case["g_y"]
+    g = _normal(shape, 1e-3, seed, "g_y")
+    if kind == "chan_outlier":
+        g[:, _picks(4, shape[1], seed, "g_y.cols")] *= 50.0
+    elif kind == "tok_outlier":
+        g[_picks(max(1, shape[0] // 64), shape[0], seed, "g_y.rows")] *= 50.0
+    elif kind in ("t3", "t4"):          # Student-t: a normal over the root of a mean of squares
+        df = int(kind[1])
+        s = torch.zeros(shape, device=DEVICE)
+        for i in range(df):
+            s += _normal(shape, 1.0, seed, f"g_y.chi{i}").square_()
+        g /= s.div_(df).sqrt_()
+    return g
+
+
+def prepare(case, seed):
+    L, O, I = case["L"], case["O"], case["I"]
+    keep = case["block"] // 2
+    cfg = hot.Config(block=case["block"], keep=keep, gx_bits=case["gx_bits"], gw_bits=case["gw_bits"],
+                     rounding=ROUND, sample_tokens=case["sample"],
+                     keep_idx=hot.hot_lowpass_l1_rows(case["block"], keep) if case["lp_l1"] else None)
+    state = {"kind": case["kind"], "cfg": cfg, "quantizer": QUANTIZER[case["quantizer"]], "I": I,
+             "g_y": _gradient(case, seed), "ws": hot.alloc_workspace(cfg, L, O, I, device=DEVICE)}
+    if case["kind"] == "select":
+        return state
+    w = _normal((O, I), 0.02, seed, "w")
+    state["g_x"] = torch.empty((L, I), device=DEVICE)
+    if case["kind"] == "frozen":
+        state["wq"] = hot.hot_quantize_weight(cfg, w, hot.alloc_weight_buffer(cfg, O, I, device=DEVICE), state["ws"])
+        return state
+    state["w"] = w
+    state["x"] = _activation(case, seed)
+    state["act"] = hot.alloc_act_buffer(cfg, L, I, device=DEVICE)
+    state["g_w"] = torch.empty((O, I), device=DEVICE)
+    return state
+
+
+def run(state):
+    kind, cfg, g_y, ws = state["kind"], state["cfg"], state["g_y"], state["ws"]
+    if kind == "select":
+        return hot.hot_select_quantizer(cfg, g_y, ws)
+    if kind == "frozen":
+        return hot.hot_linear_backward_gx_cached(cfg, g_y, state["wq"], state["I"], state["quantizer"],
+                                                 state["g_x"], ws)
+    hot.hot_compress_activation(cfg, state["x"], state["act"], ws)
+    if kind == "split":
+        g_x = hot.hot_linear_backward_gx(cfg, g_y, state["w"], state["quantizer"], state["g_x"], ws)
+        g_w = hot.hot_linear_backward_gw(cfg, g_y, state["act"], state["I"], state["g_w"], ws)
+        return g_x, g_w
+    return hot.hot_linear_backward(cfg, g_y, state["w"], state["act"], state["quantizer"], state["g_x"],
+                                   state["g_w"], ws)
+
+
+def tolerance(case):
+    """The integer stages are exact.  What may differ is the fp32 scaling behind them (the scales'
+    product and its product with the sum: 3.5e-8 in the 2-norm against double precision), the order
+    of the bfloat16 variant's fp32 sums (4.8e-7 against double precision; the split case returns
+    both gradients) and that of the fp64 calibration sums; each stated about four times as large."""
+    if case["kind"] == "select":
+        return {"rel": 1e-10}
+    if case["kind"] != "frozen" and case["gw_bits"] == 16:
+        return {"rel": 2e-6}
+    return {"rel": 1.5e-7}
