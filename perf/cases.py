@@ -196,6 +196,101 @@ def run(state):
                                    state["g_w"], ws)
 
 
+def _walsh(v, n):
+    """Butterflies of the unnormalised n-point transform along dim 1 of [blocks, n, cols], in the
+    stated order (h = 1, 2, ...) and in 32 bits: the codes are decided on these values."""
+    for h in _powers(n):
+        a, b = v.view(v.shape[0], n // (2 * h), 2, h, -1).unbind(2)
+        v = torch.stack((a + b, a - b), 2).view(v.shape)
+    return v
+
+
+def _powers(n):
+    return [1 << i for i in range(n.bit_length() - 1)]
+
+
+def _kept_rows(n, lp_l1):
+    """The n/2 kept rows of the transform, from the sign changes of the explicit matrix."""
+    sign = [[bin(k & j).count("1") & 1 for j in range(n)] for k in range(n)]
+
+    def changes(row):
+        return sum(a != b for a, b in zip(row, row[1:]))
+
+    if not lp_l1:
+        return sorted(range(n), key=lambda k: changes(sign[k]))[:n // 2]
+    wide = 4 if n == 16 else 8              # the block's tokens as a grid in raster order
+
+    def key(k):
+        down, along = changes(sign[k][::wide]), changes(sign[k][:wide])
+        return down + along, max(down, along), down
+
+    return sorted(range(n), key=key)[:n // 2]
+
+
+def _codes(t, amax, bits):
+    """Codes (as doubles) of the pseudo-stochastic quantiser, whose threshold is the low bits of the
+    scaled 32-bit value, and the scale."""
+    top = float(2 ** (bits - 1) - 1)
+    tops = torch.full_like(amax, top)       # both divisions rounded once: not times a reciprocal
+    inv = torch.where(amax > 0, tops / amax, torch.zeros_like(amax))
+    v = t * inv
+    low = v.floor()
+    threshold = (v.view(torch.int32) & 0x7FF).to(torch.float32) * (1.0 / 2048.0)
+    q = (low + (v - low > threshold).to(torch.float32)).clamp_(-top, top)
+    return q.double(), (amax / tops).double()
+
+
+def _token_blocks(case, t):
+    n, S = case["block"], case["sample"]
+    if S:
+        t = torch.nn.functional.pad(t.view(-1, S, t.shape[1]), (0, 0, 0, -S % n))
+    return t.reshape(-1, n, t.shape[-1])
+
+
+def _reduced_operand(case, t):
+    """Kept rows of the token-direction transform, quantised: (values, scale) in 64 bits."""
+    n = case["block"]
+    kept = _walsh(_token_blocks(case, t), n)[:, _kept_rows(n, case["lp_l1"])].reshape(-1, t.shape[1])
+    if case["gw_bits"] == 16:
+        return kept.to(torch.bfloat16).double(), 1.0
+    return _codes(kept, kept.abs().max(), 8)
+
+
+def _times(a, b):
+    """Product of doubles in slices of the result's rows, to bound what is held at once."""
+    return torch.cat([part @ b for part in a.split(16384)])
+
+
+def exact(case, seed):
+    """The same codes, then products, scales and error sums in 64 bits."""
+    L, O, I, n, kind = case["L"], case["O"], case["I"], case["block"], case["kind"]
+    if work(case)["flops"] > 1e12 and kind != "frozen":   # minutes at the double-precision rate
+        return None
+    g_y = _gradient(case, seed)
+    t = _walsh(g_y.view(-1, n, 1), n).view(L, O)
+    if kind == "select":
+        mse = []
+        for amax in (t.abs().amax(1, keepdim=True), t.abs().max()):
+            total = 0.0
+            for part, top in zip(t.split(1024), amax.split(1024) if amax.dim() else [amax] * (L // 1024 + 1)):
+                q, scale = _codes(part, top, case["gx_bits"])
+                total += float((part.double() - q * scale).square().sum())
+            mse.append(total / (float(n) * L * O))
+        token, tensor = mse
+        return (1 if tensor > 0 and tensor - token >= 0.5 * tensor else 0), token, tensor
+    w = _normal((O, I), 0.02, seed, "w")
+    rotated = _walsh(w.view(-1, n, I), n).view(O, I)
+    qw, sw = _codes(rotated, rotated.abs().max(), case["gx_bits"])
+    qg, sg = _codes(t, t.abs().amax(1, keepdim=True) if case["quantizer"] == "token" else t.abs().max(),
+                    case["gx_bits"])
+    g_x = _times(qg, qw) * sg * sw / n
+    if kind == "frozen":
+        return g_x
+    a, sa = _reduced_operand(case, g_y)
+    b, sb = _reduced_operand(case, _activation(case, seed))
+    return g_x, a.t().contiguous() @ b * sa * sb / n
+
+
 def tolerance(case):
     """The integer stages are exact.  What may differ is the fp32 scaling behind them (the scales'
     product and its product with the sum: 3.5e-8 in the 2-norm against double precision), the order
