@@ -98,7 +98,9 @@ GwLayout gw_layout(const Config& c, int64_t L, int64_t O, int64_t I) {
   g.scalars = 0;
   g.qg = kWsPrefix;
   g.partial = g.qg + (size_t)round_up(O * g.pitch, 256);
-  g.total = g.partial + gemm_scratch_bytes(O, I, g.pitch, c.gw_bits);
+  const size_t hand = gemm_scratch_bytes(O, I, g.pitch, c.gw_bits), img = image_scratch_bytes(O, I, g.pitch, c.gw_bits);
+  g.least = g.partial + hand;
+  g.total = g.partial + (img > hand ? img : hand);
   return g;
 }
 
@@ -121,7 +123,9 @@ FusedLayout fused_layout(const Config& c, int64_t L, int64_t O, int64_t I) {
   f.partial = f.qgh + (size_t)round_up(O * f.gw.pitch, 256);   // shared by the two GEMMs
   const size_t sx = gemm_scratch_bytes(L, I, f.gx.pitch, c.gx_bits);
   const size_t sw = gemm_scratch_bytes(O, I, f.gw.pitch, c.gw_bits);
-  f.total = f.partial + (sx > sw ? sx : sw);
+  f.least = f.partial + (sx > sw ? sx : sw);
+  f.total = f.partial + image_scratch_bytes(O, I, f.gw.pitch, c.gw_bits);
+  f.total = f.total > f.least ? f.total : f.least;
   return f;
 }
 
@@ -336,8 +340,8 @@ namespace {
 hipError_t gemm(const Config& c, const uint8_t* A, const uint8_t* B, int64_t M, int64_t N, int64_t pitch,
                 int bits, uint8_t* base, size_t partial_off, int32_t* out_i32, float* out_f32,
                 const float* row_scale, int row_stride, const float* col_scale, int n, hipStream_t s,
-                int stage = -1) {
-  return launch_igemm(A, B, M, N, pitch, pitch, bits, plan_gemm(M, N, pitch, bits, true),
+                int stage = -1, bool images = false) {
+  return launch_igemm(A, B, M, N, pitch, pitch, bits, plan_gemm(M, N, pitch, bits, true, images),
                       (int32_t*)(base + partial_off), (unsigned long long*)(base + kGemmFlagsOffset),
                       out_i32, out_f32, row_scale, row_stride, col_scale, n, s, stage, c.epoch);
 }
@@ -517,7 +521,7 @@ hot_status hot_linear_backward_gw(const hot_config* cfg, const float* g_y, const
     return HOT_ERR_ARG;
   if (!tok_shape_ok(c, L, O) || !tok_shape_ok(c, L, I)) return HOT_ERR_SHAPE;
   const GwLayout g = gw_layout(c, L, O, I);
-  if (ws_bytes < g.total) return HOT_ERR_WORKSPACE;
+  if (ws_bytes < g.least) return HOT_ERR_WORKSPACE;
   const ActLayout a = act_layout(c, L, I);
   hipStream_t s = (hipStream_t)stream;
   uint8_t* base = (uint8_t*)ws;
@@ -530,7 +534,7 @@ hot_status hot_linear_backward_gw(const hot_config* cfg, const float* g_y, const
   st = gw_operand(c, g_y, L, O, qg, g.pitch, s_g, part_g, s);
   if (st != HOT_OK) return st;
   HOT_TRY(gemm(c, qg, abase + a.codes, O, I, g.pitch, c.gw_bits, base, g.partial, nullptr, g_w, s_g, 0,
-               (const float*)abase, c.n, s, kStGwGemm));
+               (const float*)abase, c.n, s, kStGwGemm, ws_bytes >= g.total));
   return HOT_OK;
 }
 
@@ -550,7 +554,8 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
   const ActLayout a = act_layout(c, L, I);
   hipStream_t s = (hipStream_t)stream;
   uint8_t* base = (uint8_t*)ws;
-  if (ws_bytes < f.total) return HOT_ERR_WORKSPACE;
+  if (ws_bytes < f.least) return HOT_ERR_WORKSPACE;
+  const bool images = ws_bytes >= f.total;
   HOT_TRY(begin_call(c, ws, s));
   if (!shared_gy_passes(c, L, O)) {
     // The two separate paths, with both operand transforms ahead of both GEMMs (the workspace
@@ -567,7 +572,7 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
                  f.partial, s);
     if (st != HOT_OK) return st;
     HOT_TRY(gemm(c, base + f.qgh, (const uint8_t*)act_buf + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial,
-                 nullptr, g_w, (const float*)(base + f.s_gh), 0, (const float*)act_buf, c.n, s, kStGwGemm));
+                 nullptr, g_w, (const float*)(base + f.s_gh), 0, (const float*)act_buf, c.n, s, kStGwGemm, images));
     return HOT_OK;
   }
   float* s_w = (float*)(base + f.gx.scalars);
@@ -588,7 +593,7 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
   HOT_TRY(gemm(c, qg, qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr, g_x, s_g,
                per_token ? 1 : 0, s_w, c.n, s, kStGxGemm));
   HOT_TRY(gemm(c, qgh, abase + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial, nullptr, g_w, s_gh,
-               0, (const float*)abase, c.n, s, kStGwGemm));
+               0, (const float*)abase, c.n, s, kStGwGemm, images));
   return HOT_OK;
 }
 

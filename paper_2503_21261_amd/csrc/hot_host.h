@@ -64,11 +64,13 @@ struct GemmPlan {
   int bm, bn, bkb;
   int split;              // workgroups (K slices) per output tile
   int64_t tiles;
-  size_t partial_bytes;   // split > 1: tiles * (split - 1) * bm * bn int32
+  bool images;            // the slices' sums are added by a second kernel
+  size_t partial_bytes;   // split > 1: tiles * (split - 1, or split with `images`) * bm * bn int32
 };
 // `scratch`: a region of gemm_scratch_bytes() and the workspace's flag slots are available,
-// so K may be split.
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch);
+// so K may be split; `images`: a region of image_scratch_bytes() is.
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images);
+size_t image_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits);
 // Upper bound of partial_bytes over every plan of this shape (whatever mode is forced).
 size_t gemm_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits);
 // Measurement / test overrides: 0 = cost model, 1 = one workgroup per tile, s >= 2 = s K
@@ -83,14 +85,16 @@ struct GxLayout {
 };
 struct GwLayout {
   int64_t Lr, pitch;                  // reduced token count, bytes per operand row
-  size_t scalars, qg, partial, total;
+  size_t scalars, qg, partial;
+  size_t least, total;                // without and with room for a split added by a second kernel
 };
 // hot_linear_backward: the g_x layout first (so its operand view applies unchanged),
 // then the per-token abs-max partials and the g_w operands.
 struct FusedLayout {
   GxLayout gx;
   GwLayout gw;                        // pitch only; offsets below
-  size_t s_gh, rowpart, qgh, partial, total;
+  size_t s_gh, rowpart, qgh, partial;
+  size_t least, total;                // as in GwLayout
 };
 struct SelLayout {
   size_t scalars, rowmax, partial, total;

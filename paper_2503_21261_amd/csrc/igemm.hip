@@ -88,12 +88,36 @@ int64_t large_tile_split(int64_t M, int64_t N, int64_t k_bytes, int bits, int cu
   while (s > 1 && (k_bytes / s < 16384 || tiles * (s - 1) > kMaxSplitSlots)) --s;
   return s >= 2 ? s : 0;
 }
+// Slices of a GEMM on 128x128 tiles whose partial sums a second kernel adds (kImages); 0 = does
+// not apply.  A slice costs about 0.5 us per 128-byte K stage, an image 0.03 us to write and
+// read back, so the sum of both is least at sqrt(16 stages / tiles) slices, at most about two
+// workgroups per compute unit (multiples of 8 let an XCD keep whole slices).  Measured, best of
+// 1-24 slices against this rule's: 4 tiles x 49 stages 13.6 / 13.6 us (8 slices; the hand-over
+// 22.8), 16 x 32 14.6 / 14.6 (21.6), 32 x 49 16.7 / 17.1 (25.8), 36 x 788 104.5 / 106.7 (16
+// slices; the hand-over on 256x256 tiles 197), bfloat16 36 x 99 25.2 / 25.2 (unsplit 55.0),
+// 144 x 99 53.9 / 53.9 (59.8).
+// INT8 GEMMs of more than 42 tiles stay with the hand-over, which hides the images under the last
+// slices' work: 56 tiles x 12 stages 16.0 against 15.9 us, 144 x 50 31.1 against 36.4, 108 x 197
+// 71 against 76.  bfloat16 has no hand-over: any output with no more tiles than units, and three
+// slices or more (two: 36 tiles x 16 stages 17.1 us against 14.3 unsplit).
+int64_t image_slices(int64_t M, int64_t N, int64_t k_bytes, int bits, int cus) {
+  if (bits == 4 || M <= 0 || N <= 0) return 0;
+  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), nk = k_bytes / 128;
+  if (tiles > (bits == 16 ? cus : cus / 6)) return 0;
+  int64_t s = 1;
+  while ((s + 1) * (s + 1) * tiles <= 16 * nk) ++s;
+  if (s > 2 * cus / tiles) s = 2 * cus / tiles;
+  if (s > nk / 4) s = nk / 4;
+  if (s > 64) s = 64;
+  if (s > 8) s = s < 12 ? 8 : (s + 4) / 8 * 8;
+  return s >= (bits == 16 ? 3 : 4) ? s : 0;
+}
 }  // namespace
 
 void set_gemm_mode(int mode) { g_gemm_mode.store(mode); }
 void set_gemm_wait_us(int us) { g_gemm_wait_us.store(us); }
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images) {
   // Cost of a tile shape, fitted to measurements on MI355X (ten layer shapes from 512 to 201728
   // tokens, every INT4 tile timed on each; within 4 % of the measured time, and the measured
   // best tile or one within 2 % of it on all ten): a compute unit works through its share of
@@ -111,6 +135,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
   const int cus = compute_units();
   GemmPlan p;
   p.split = 1;
+  p.images = false;
   p.partial_bytes = 0;
   double best = 1e30;
   for (int c = 0; c < ncand; ++c) {
@@ -137,6 +162,17 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
     p.tiles = ceil_div(M, p.bm) * ceil_div(N, p.bn);
     return p;
   }
+  if (images && mode == 0) {
+    const int64_t s = image_slices(M, N, k_bytes, bits, cus);
+    if (s) {
+      p.bm = p.bn = 128;
+      p.tiles = ceil_div(M, 128) * ceil_div(N, 128);
+      p.split = (int)s;
+      p.images = true;
+      p.partial_bytes = image_scratch_bytes(M, N, k_bytes, bits);
+      return p;
+    }
+  }
   if (scratch && mode == 0) {
     const int64_t s = large_tile_split(M, N, k_bytes, bits, cus);
     if (s) {
@@ -162,6 +198,12 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
   return p;
 }
 
+size_t image_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits) {
+  if (M <= 0 || N <= 0) return 0;
+  return (size_t)(ceil_div(M, 128) * ceil_div(N, 128) * image_slices(M, N, k_bytes, bits, compute_units())) *
+         128 * 128 * 4;
+}
+
 size_t gemm_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits) {
   if (bits == 16 || M <= 0 || N <= 0) return 0;
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128);
@@ -184,11 +226,11 @@ namespace {
 template <int BM, bool INT4, bool BF16>
 constexpr int gemm_waves_m() { return (BM == 256 && !INT4) ? 4 : 2; }
 
-template <int BM, int BN, int BKB, bool INT4, bool BF16, bool SPLITK>
+template <int BM, int BN, int BKB, bool INT4, bool BF16, int SPLIT>
 hipError_t launch_kernel(const GemmArgs& g, unsigned grid, hipStream_t s, int gemm_stage) {
   const size_t lds = 2 * (size_t)(BM + BN) * BKB;
   constexpr int WM = gemm_waves_m<BM, INT4, BF16>();
-  auto kern = igemm_kernel<BM, BN, WM, 2, BKB, INT4, BF16, SPLITK>;
+  auto kern = igemm_kernel<BM, BN, WM, 2, BKB, INT4, BF16, SPLIT>;
   static std::atomic<bool> attr_set{false};  // per instantiation; setting it twice is harmless
   if (!attr_set.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -201,46 +243,70 @@ hipError_t launch_kernel(const GemmArgs& g, unsigned grid, hipStream_t s, int ge
   return hipGetLastError();
 }
 
+// GemmArgs::xcd_cols of a split launch: one rectangle of the tile grid per XCD where the grid
+// divides evenly, the split that fetches the fewest operand bytes (A row bands once per XCD
+// column, B bands once per XCD row).
+template <int BM>
+int slice_placement(const GemmArgs& g, int64_t tiles) {
+  if (BM == 128 && 8 % g.split == 0 && g.tiles_m % (8 / g.split) == 0) {
+    // a slice per group of XCDs: the fewest operand bytes of all (ViT-B proj g_w, 36 tiles in
+    // 8 slices: 50.5 -> 45 us; the 256x256 split measured slower this way, 385 against 360 us
+    // on the ViT-L g_w GEMM, and keeps the rectangles)
+    return -1;
+  }
+  if (tiles % 8 != 0) return 0;
+  int cols = 0;
+  double best = 0.0;
+  for (int rx = 1; rx <= 8; rx *= 2) {
+    const int ry = 8 / rx;
+    if (g.tiles_m % ry != 0 || g.tiles_n % rx != 0) continue;
+    const double fetch = (double)g.M * rx + (double)g.N * ry;
+    if (cols == 0 || fetch < best) {
+      best = fetch;
+      cols = rx;
+    }
+  }
+  return cols;
+}
+
 template <int BM, int BN, int BKB, bool INT4, bool BF16 = false>
-hipError_t launch_tile(GemmArgs g, int64_t k_bytes, int split, hipStream_t s, int gemm_stage) {
+hipError_t launch_tile(GemmArgs g, int64_t k_bytes, const GemmPlan& plan, hipStream_t s, int gemm_stage) {
+  const int split = plan.split;
   g.nk_total = (int)(k_bytes / BKB);
   g.tiles_m = (int)ceil_div(g.M, BM);
   g.tiles_n = (int)ceil_div(g.N, BN);
   g.split = split;
   const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
-  if (split <= 1) return launch_kernel<BM, BN, BKB, INT4, BF16, false>(g, (unsigned)tiles, s, gemm_stage);
+  if (split <= 1) return launch_kernel<BM, BN, BKB, INT4, BF16, kWholeK>(g, (unsigned)tiles, s, gemm_stage);
+  if constexpr (BM == 128 && BN == 128 && !INT4) {
+    if (plan.images) {
+      if (!g.partial) return hipErrorInvalidValue;
+      g.xcd_cols = split % 8 == 0 ? -2 : slice_placement<BM>(g, tiles);
+      const bool timed = gemm_stage >= 0;
+      if (timed) stage_begin(gemm_stage, s);
+      hipError_t e = launch_kernel<BM, BN, BKB, INT4, BF16, kImages>(g, (unsigned)(tiles * split), s, -1);
+      if (e == hipSuccess) {
+        combine_images_kernel<BF16><<<dim3((unsigned)(tiles * 64)), dim3(256), 0, s>>>(g);
+        e = hipGetLastError();
+      }
+      if (timed) stage_end(gemm_stage, s);
+      return e;
+    }
+  }
+  if (plan.images) return hipErrorInvalidValue;
   if constexpr (BF16 || BM == 192 || BM != BN || (INT4 && BM != 128)) {
     return hipErrorInvalidValue;   // splits exist for the 128x128 tiles and the 256x256 INT8 tile
   } else {
     if (!g.partial || !g.flags || tiles * (split - 1) > kMaxSplitSlots) return hipErrorInvalidValue;
     g.tag = next_exchange_tag();   // the process-wide launch tag sequence
-    // one rectangle of the tile grid per XCD where the grid divides evenly: the split that
-    // fetches the fewest operand bytes (A row bands once per XCD column, B bands once per XCD row)
-    g.xcd_cols = 0;
-    if (BM == 128 && 8 % split == 0 && g.tiles_m % (8 / split) == 0) {
-      // a slice per group of XCDs: the fewest operand bytes of all (ViT-B proj g_w, 36 tiles in
-      // 8 slices: 50.5 -> 45 us; the 256x256 split measured slower this way, 385 against 360 us
-      // on the ViT-L g_w GEMM, and keeps the rectangles)
-      g.xcd_cols = -1;
-    } else if (tiles % 8 == 0) {
-      double best = 0.0;
-      for (int rx = 1; rx <= 8; rx *= 2) {
-        const int ry = 8 / rx;
-        if (g.tiles_m % ry != 0 || g.tiles_n % rx != 0) continue;
-        const double fetch = (double)g.M * rx + (double)g.N * ry;
-        if (g.xcd_cols == 0 || fetch < best) {
-          best = fetch;
-          g.xcd_cols = rx;
-        }
-      }
-    }
+    g.xcd_cols = slice_placement<BM>(g, tiles);
     // an image normally arrives before its owner has finished its own slice; the bound only
     // has to cover workgroups that start late: never less than the whole GEMM takes at 200 TOP/s
     int64_t wait_us = g_gemm_wait_us.load();
     const int64_t gemm_us = (int64_t)(2.0 * g.M * g.N * (double)k_bytes * (INT4 ? 2 : 1) / 200e6);
     if (wait_us > 0 && wait_us < gemm_us) wait_us = gemm_us;
     g.wait_ticks = wait_us < 0 ? 0 : wait_us * 100;
-    return launch_kernel<BM, BN, BKB, INT4, false, true>(g, (unsigned)(tiles * split), s, gemm_stage);
+    return launch_kernel<BM, BN, BKB, INT4, false, kHandOver>(g, (unsigned)(tiles * split), s, gemm_stage);
   }
 }
 
@@ -274,20 +340,20 @@ hipError_t launch_igemm(const uint8_t* A, const uint8_t* B, int64_t M, int64_t N
   // up to 3072 codes of K (ViT-B fc2 at 50432 tokens 167 -> 134 us, ViT-B fc1 at 12608 tokens
   // 44.5 -> 39.6 us), and lose 3 % at 4096 codes and a wide output (LLM down-projection)
   g.stream_out = (bits != 4 || k_bytes * 2 <= 3072) ? 1 : 0;
-  const int gs = gemm_stage, sw = plan.split;
+  const int gs = gemm_stage;
   if (bits == 16) {
-    if (plan.bm == 256) return launch_tile<256, 256, 128, false, true>(g, k_bytes, sw, s, gs);
-    if (plan.bm == 128) return launch_tile<128, 128, 128, false, true>(g, k_bytes, sw, s, gs);
+    if (plan.bm == 256) return launch_tile<256, 256, 128, false, true>(g, k_bytes, plan, s, gs);
+    if (plan.bm == 128) return launch_tile<128, 128, 128, false, true>(g, k_bytes, plan, s, gs);
     return hipErrorInvalidValue;
   }
   if (plan.bm == 256)
-    return bits == 4 ? launch_tile<256, 256, 64, true>(g, k_bytes, sw, s, gs)
-                     : launch_tile<256, 256, 128, false>(g, k_bytes, sw, s, gs);
-  if (plan.bm == 192 && bits == 4) return launch_tile<192, 256, 64, true>(g, k_bytes, sw, s, gs);
-  if (plan.bm == 128 && plan.bn == 256 && bits == 4) return launch_tile<128, 256, 64, true>(g, k_bytes, sw, s, gs);
+    return bits == 4 ? launch_tile<256, 256, 64, true>(g, k_bytes, plan, s, gs)
+                     : launch_tile<256, 256, 128, false>(g, k_bytes, plan, s, gs);
+  if (plan.bm == 192 && bits == 4) return launch_tile<192, 256, 64, true>(g, k_bytes, plan, s, gs);
+  if (plan.bm == 128 && plan.bn == 256 && bits == 4) return launch_tile<128, 256, 64, true>(g, k_bytes, plan, s, gs);
   if (plan.bm == 128)
-    return bits == 4 ? launch_tile<128, 128, 64, true>(g, k_bytes, sw, s, gs)
-                     : launch_tile<128, 128, 128, false>(g, k_bytes, sw, s, gs);
+    return bits == 4 ? launch_tile<128, 128, 64, true>(g, k_bytes, plan, s, gs)
+                     : launch_tile<128, 128, 128, false>(g, k_bytes, plan, s, gs);
   return hipErrorInvalidValue;
 }
 

@@ -65,7 +65,15 @@ struct GemmArgs {
   float inv_n;
   int stream_out;        // fp32 output with non-temporal stores
   int xcd_cols;          // split-K: > 0: the tile grid cut into 8 / xcd_cols x xcd_cols rectangles, one per XCD;
-                         // < 0: XCDs dealt to the K slices; 0: band walk
+                         // -1: XCDs dealt to the K slices (split divides 8); -2: K slices dealt to the XCDs
+                         // (8 divides split); 0: band walk
+};
+
+// How the K range of an output tile is worked on (template argument of igemm_kernel).
+enum KSplit {
+  kWholeK = 0,     // one workgroup per tile
+  kHandOver = 1,   // one workgroup per (slice, tile); the last slice's collects the others' sums
+  kImages = 2,     // one workgroup per (slice, tile); all leave their sums to combine_images_kernel
 };
 
 // Workgroup id -> output tile.  Workgroups are dealt round-robin to the 8 XCDs, each
@@ -112,8 +120,8 @@ struct Operands {            // what the matrix instructions of one K slice cons
 // elements of v_mfma_f32_32x32x16_bf16) and fp32 accumulators; the "integer" outputs then
 // carry the accumulators' fp32 bit patterns.
 //
-// SPLITK = false: workgroup b computes output tile b over the whole K range.
-// SPLITK = true: the K range is cut into g.split slices and the grid holds one workgroup
+// SPLIT = kWholeK: workgroup b computes output tile b over the whole K range.
+// SPLIT = kHandOver: the K range is cut into g.split slices and the grid holds one workgroup
 // per (slice, tile), slice-major, so that workgroups running side by side work on
 // neighbouring tiles at the same K offsets and share operand tiles through L2 exactly as
 // without the split.  The workgroup of a tile's last slice owns the tile and writes its
@@ -122,6 +130,10 @@ struct Operands {            // what the matrix instructions of one K slice cons
 // The wait is bounded: an owner that does not see an image in time computes that slice
 // itself (integer sums do not depend on who adds what), so the kernel finishes even if
 // workgroups are not resident together.
+// SPLIT = kImages: the same grid, every workgroup leaves its image (slot = row-major tile index *
+// split + slice) and combine_images_kernel, launched behind, adds them in slice order.  An owner
+// collects images one after the other, 2-3 us each, which many slices cannot afford; and the
+// fp32 sums of the bfloat16 operands must not depend on which workgroup added a piece.
 // Waves per SIMD the register allocation must leave room for: two for the 128x256 INT4 tile
 // (its workgroups come in pairs per compute unit so that one's output stores run under the
 // other's matrix instructions), whatever fits otherwise.
@@ -129,11 +141,11 @@ template <int BM, int BN, bool INT4>
 constexpr int gemm_min_waves_per_simd() { return (INT4 && BM == 128 && BN == 256) ? 2 : 1; }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BKB, bool INT4, bool BF16 = false,
-          bool SPLITK = false>
+          int SPLIT = kWholeK>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (gemm_min_waves_per_simd<BM, BN, INT4>()))
 void igemm_kernel(const GemmArgs g) {
   static_assert(!(INT4 && BF16), "one operand format");
-  static_assert(!(SPLITK && BF16), "fp32 sums would depend on which workgroup added a piece");
+  static_assert(!(SPLIT == kHandOver && BF16), "fp32 sums would depend on which workgroup added a piece");
   using acc_t = std::conditional_t<BF16, v16f, v16i>;
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -345,7 +357,7 @@ void igemm_kernel(const GemmArgs g) {
     // from hoisting the ~100 output addresses out of them (they would be live, in
     // registers, across the main loop).
     int ln = lane;
-    if constexpr (SPLITK) asm volatile("" : "+v"(ln));
+    if constexpr (SPLIT == kHandOver) asm volatile("" : "+v"(ln));
     const int lane = ln;
     const int nl0 = wn0 + (lane & 31);
     if (g.out_f32 && m0 + BM <= g.M && n0 + BN <= g.N) {
@@ -430,7 +442,7 @@ void igemm_kernel(const GemmArgs g) {
     }
   };
 
-  if constexpr (!SPLITK) {
+  if constexpr (SPLIT == kWholeK) {
     int tm, tn;
     tile_of_position(g, xcd_contiguous(blockIdx.x, g.tiles_m * g.tiles_n), tm, tn);
     set_tile(tm, tn);
@@ -444,7 +456,15 @@ void igemm_kernel(const GemmArgs g) {
     const int tiles = g.tiles_m * g.tiles_n, nk = g.nk_total, S = g.split;
     int z = blockIdx.x / tiles;   // slices in dispatch order: owners (z = S - 1) start last
     int tm, tn, t;
-    if (g.xcd_cols < 0) {
+    if (SPLIT == kImages && g.xcd_cols == -2) {
+      // 8 divides S: an XCD works on every eighth slice, all of its tiles, so that both operands
+      // of a slice are fetched by one XCD.
+      const int j = blockIdx.x >> 3;
+      z = (blockIdx.x & 7) + 8 * (j / tiles);
+      t = j % tiles;
+      tm = t / g.tiles_n;
+      tn = t % g.tiles_n;
+    } else if (g.xcd_cols < 0) {
       // S divides 8: the XCDs are dealt to the slices, 8 / S to each, and the XCDs of a slice
       // share its tiles by row bands.  An A row band of a slice is then fetched by one XCD, a B
       // band by 8 / S of them: the whole GEMM fetches A once and B 8 / S times.
@@ -468,6 +488,23 @@ void igemm_kernel(const GemmArgs g) {
       tile_of_position(g, t, tm, tn);
     }
     auto slice_begin = [&](int zz) { return (int)(((int64_t)zz * nk) / S); };
+    if constexpr (SPLIT == kImages) {
+      set_tile(tm, tn);
+      zero_acc();
+      main_loop(slice_begin(z), slice_begin(z + 1));
+      int32_t* mine = g.partial + (int64_t)((tm * g.tiles_n + tn) * S + z) * IMG + tid;
+      static_for<TM * TN>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          if constexpr (BF16) mine[(q * 16 + v) * NT] = __float_as_int(acc[q / TN][q % TN][v]);
+          else mine[(q * 16 + v) * NT] = acc[q / TN][q % TN][v];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      return;
+    }
+    if constexpr (SPLIT == kHandOver) {
     const bool owned = z == S - 1;
     set_tile(tm, tn);
     if (owned) fill_rowfac();
@@ -545,6 +582,39 @@ void igemm_kernel(const GemmArgs g) {
       if (tid == 0)
         __hip_atomic_store(&g.flags[slot], effective_tag(g.tag, g.epoch), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    }
+  }
+}
+
+// Second half of a kImages split on 128x128 tiles: adds the S images of a tile in slice order and
+// writes the output.  One workgroup per accumulator register (of 64) of a tile's image: its 256
+// threads read 1 KB of every image, S loads in flight per thread.  Bound by the launch and one
+// memory round trip (the images are a few MB that the memory-side cache still holds).
+template <bool BF16>
+__global__ __launch_bounds__(256) void combine_images_kernel(const GemmArgs g) {
+  constexpr int IMG = 128 * 128;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int t = blockIdx.x >> 6, reg = blockIdx.x & 63;
+  const int q = reg >> 4, v = reg & 15;
+  const int32_t* img = g.partial + (int64_t)t * g.split * IMG + reg * 256 + tid;   // t: row-major tile index
+  // the layout the epilogue of igemm_kernel writes (2x2 waves, 2x2 tiles of 32x32 per wave)
+  const int m = (t / g.tiles_n) * 128 + (wave & 1) * 64 + (q >> 1) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+  const int n = (t % g.tiles_n) * 128 + (wave >> 1) * 64 + (q & 1) * 32 + (lane & 31);
+  std::conditional_t<BF16, float, int> sum = 0;
+#pragma unroll 8
+  for (int z = 0; z < g.split; ++z) {
+    const int32_t part = img[(int64_t)z * IMG];
+    if constexpr (BF16) sum += __int_as_float(part);
+    else sum += part;
+  }
+  if (m >= g.M || n >= g.N) return;
+  const int64_t o = (int64_t)m * g.N + n;
+  if (g.out_f32) {
+    const float cs = (*g.col_scale) * g.inv_n;
+    g.out_f32[o] = (float)sum * (g.row_scale[(int64_t)m * g.row_stride] * cs);
+  } else {
+    if constexpr (BF16) g.out_i32[o] = __float_as_int(sum);
+    else g.out_i32[o] = sum;
   }
 }
 

@@ -939,6 +939,33 @@ def test_int8_gemm_large_tile_with_k_split(gemm_mode, wait_us):
     check_gw(hot, hot.Config(block=16, keep=8), gy, x, f"large INT8 tile, K split, wait={wait_us}")
 
 
+@pytest.mark.parametrize("L,O,I,bits", [(4096, 128, 128, 8), (4240, 130, 257, 8), (16400, 48, 260, 8),
+                                        (2560, 140, 132, 16), (8208, 64, 200, 16), (2048, 300, 140, 16), (4096, 520, 1000, 16)])
+def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
+    """Few output tiles and a long K: the slices' images are added by a second kernel.  Against the
+    oracle; INT8 also bit for bit against one workgroup per tile, and with a workspace that has no
+    room for the images (the size of a split without them), which takes another plan."""
+    hot = _hot()
+    x, w, gy = make(L, O, I, seed=75)
+    cfg = hot.Config(block=16, keep=8, gw_bits=bits)
+    if bits == 16:
+        check_gw_bf16(hot, cfg, gy, x, "combined images")
+        return
+    check_gw(hot, cfg, gy, x, "combined images")
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, x.cuda(), act, ws)
+    pitch = (L // 2 + 127) // 128 * 128
+    tiles, slices = -(-O // 128) * -(-I // 128), min(8, pitch // 128 // 4)
+    small = hot.HOT_WS_PREFIX_BYTES + (O * pitch + 255) // 256 * 256 + tiles * (slices - 1) * 128 * 128 * 4
+    assert small < ws.numel()
+    outs = []
+    for mode, space in ((0, ws), (1, ws), (0, ws[:small])):
+        gemm_mode(mode)
+        outs.append(hot.hot_linear_backward_gw(cfg, gy.cuda(), act, I, torch.zeros((O, I), device="cuda"), space))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
 def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode):
     """Two different inputs alternate through the same workspace, twelve back-to-back steps
     without a host synchronisation in between: every g_w must equal the one computed without
