@@ -107,9 +107,8 @@ GwLayout gw_layout(const Config& c, int64_t L, int64_t O, int64_t I) {
 SelLayout sel_layout(const Config&, int64_t L, int64_t) {
   SelLayout s;
   s.scalars = 0;
-  s.rowmax = kWsPrefix;
-  s.partial = s.rowmax + (size_t)round_up(L * 4, 256);
-  s.total = s.partial + (size_t)L * 16;
+  s.sums = kWsPrefix;
+  s.total = s.sums + (size_t)(L < kMaxPartials ? L : kMaxPartials) * 16;
   return s;
 }
 
@@ -611,12 +610,7 @@ hot_status hot_select_quantizer(const hot_config* cfg, const float* g_y, int64_t
   uint8_t* base = (uint8_t*)ws;
   float* part = (float*)(base + kHeaderBytes);
   double* result = (double*)(base + l.scalars + 64);
-  float* rowmax = (float*)(base + l.rowmax);
-  double* partial = (double*)(base + l.partial);
-
-  int npart = 0;
-  HOT_TRY(launch_row_quant(g_y, L, O, c.n, c.gx_bits, c.rounding, 3, nullptr, 0, rowmax, part, &npart, s));
-  HOT_TRY(launch_quant_error(g_y, L, O, c.n, c.gx_bits, c.rounding, rowmax, part, npart, partial, result, s));
+  HOT_TRY(launch_select(g_y, L, O, c.n, c.gx_bits, c.rounding, part, (double*)(base + l.sums), result, s));
   double host[2] = {0.0, 0.0};
   HOT_TRY(hipMemcpyAsync(host, result, sizeof(host), hipMemcpyDeviceToHost, s));
   HOT_TRY(hipStreamSynchronize(s));

@@ -54,16 +54,6 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// One butterfly stage across lanes: the lane whose MASK bit is clear holds the
-// lower element a, its partner the upper element b; (a, b) -> (a + b, a - b).
-// The upper lane adds its own value with the sign flipped: p + (-v) is p - v exactly.
-template <int MASK>
-__device__ __forceinline__ float butterfly_lanes(float v, bool upper) {
-  const float p = lane_xor<MASK>(v);
-  const float s = __int_as_float(__float_as_int(v) ^ (upper ? (int)0x80000000 : 0));
-  return p + s;
-}
-
 // In-register Walsh-Hadamard butterflies of a length-N array (Sec. 3.1), stages
 // h = 1, 2, 4, ... in that order: element j with bit h clear pairs with j + h.
 template <int N>
@@ -81,26 +71,71 @@ __device__ __forceinline__ void fwht_regs(float (&v)[N]) {
   }
 }
 
-// Stages h = 1 .. N/2 of the transform for the 4 elements this lane holds;
-// `lane` is the lane's index within the row (its low bits select the block half).
+// Row transform: a lane holds 4 consecutive elements of a row, 16 lanes hold 64 of them.  Stages
+// h = 1, 2 are in-lane; h = 4, 8, 16, 32 pair lane groups of four, named here by their logical
+// index b (elements 4 b .. 4 b + 3).  A stage across lanes is one instruction, own = partner * c +
+// own with c = +-1 and the partner read through a DPP permute (v_fmac_f32_dpp; the product by +-1
+// is exact, so it rounds as the addition does):
+//   - DPP offers the exchanges id ^ 1, ^ 2, ^ 7 (half mirror) and ^ 15 (mirror), but ^ 4 and ^ 8
+//     only as two of them, so lanes take the elements of another lane of their group of 16: lane
+//     id holds logical index b with id = b0 ^ 2 b1 ^ 7 b2 ^ 15 b3, and flipping one bit of b is one
+//     of the four exchanges.  A group still reads and writes the same consecutive bytes.
+//   - the upper lane of a pair gets own - partner, the negative of the butterfly's difference; what
+//     it holds is negated once per set bit of b, and `flip` (a sign bit) puts that right where the
+//     values are used (their magnitudes are unaffected).
 template <int N>
-__device__ __forceinline__ void fwht_row4(float4& q, int lane) {
-  float x = q.x + q.y, y = q.x - q.y, z = q.z + q.w, w = q.z - q.w;  // h = 1
-  q.x = x + z; q.z = x - z; q.y = y + w; q.w = y - w;                // h = 2
-#define HOT_STAGE(MASK)                                      \
-  {                                                          \
-    const bool up = (lane & MASK) != 0;                      \
-    q.x = butterfly_lanes<MASK>(q.x, up);                    \
-    q.y = butterfly_lanes<MASK>(q.y, up);                    \
-    q.z = butterfly_lanes<MASK>(q.z, up);                    \
-    q.w = butterfly_lanes<MASK>(q.w, up);                    \
-  }
-  HOT_STAGE(1)  // h = 4
-  HOT_STAGE(2)  // h = 8
-  if constexpr (N >= 32) HOT_STAGE(4)   // h = 16
-  if constexpr (N >= 64) HOT_STAGE(8)   // h = 32
-#undef HOT_STAGE
+struct RowLane {
+  int id;                // this thread's logical index within the row (replaces its thread index)
+  float c4, c8, c16, c32;
+  uint32_t flip;
+};
+
+template <int N>
+__device__ __forceinline__ RowLane<N> row_lane(int thread) {
+  static_assert(N == 16 || N == 32 || N == 64, "block sizes");
+  RowLane<N> r;
+  int b = thread;
+  if (N >= 32 && (thread & 4)) b ^= 3;
+  if (N >= 64 && (thread & 8)) b ^= 4;
+  r.id = b;
+  r.c4 = (b & 1) ? -1.0f : 1.0f;
+  r.c8 = (b & 2) ? -1.0f : 1.0f;
+  r.c16 = (b & 4) ? -1.0f : 1.0f;
+  r.c32 = (b & 8) ? -1.0f : 1.0f;
+  r.flip = (__builtin_popcount((unsigned)b & (N / 4 - 1)) & 1) ? 0x80000000u : 0u;
+  return r;
 }
+
+__device__ __forceinline__ float flip_sign(float v, uint32_t flip) {
+  return __uint_as_float(__float_as_uint(v) ^ flip);
+}
+
+#define HOT_ROW_DPP(CTRL, C)                                                     \
+  "v_fmac_f32_dpp %0, %0, " C " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
+  "v_fmac_f32_dpp %1, %1, " C " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
+  "v_fmac_f32_dpp %2, %2, " C " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
+  "v_fmac_f32_dpp %3, %3, " C " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+
+// Stages h = 1 .. N/2 for the 4 elements this lane holds.  Four independent chains keep the two
+// wait states a DPP read of a just-written register needs; s_nop covers the block's first one (and
+// the five states after a vector write of the execution mask).
+template <int N>
+__device__ __forceinline__ void fwht_row4(float4& q, const RowLane<N>& l) {
+  const float x = q.x + q.y, y = q.x - q.y, z = q.z + q.w, w = q.z - q.w;  // h = 1
+  q.x = x + z; q.z = x - z; q.y = y + w; q.w = y - w;                      // h = 2
+  if constexpr (N == 16)
+    asm volatile("s_nop 4\n\t" HOT_ROW_DPP("quad_perm:[1,0,3,2]", "%4") HOT_ROW_DPP("quad_perm:[2,3,0,1]", "%5") "s_nop 1"
+                 : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w) : "v"(l.c4), "v"(l.c8));
+  else if constexpr (N == 32)
+    asm volatile("s_nop 4\n\t" HOT_ROW_DPP("quad_perm:[1,0,3,2]", "%4") HOT_ROW_DPP("quad_perm:[2,3,0,1]", "%5")
+                 HOT_ROW_DPP("row_half_mirror", "%6") "s_nop 1"
+                 : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w) : "v"(l.c4), "v"(l.c8), "v"(l.c16));
+  else
+    asm volatile("s_nop 4\n\t" HOT_ROW_DPP("quad_perm:[1,0,3,2]", "%4") HOT_ROW_DPP("quad_perm:[2,3,0,1]", "%5")
+                 HOT_ROW_DPP("row_half_mirror", "%6") HOT_ROW_DPP("row_mirror", "%7") "s_nop 1"
+                 : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w) : "v"(l.c4), "v"(l.c8), "v"(l.c16), "v"(l.c32));
+}
+#undef HOT_ROW_DPP
 
 __device__ __forceinline__ float absmax4(const float4& q) {
   return fmaxf(fmaxf(fabsf(q.x), fabsf(q.y)), fmaxf(fabsf(q.z), fabsf(q.w)));

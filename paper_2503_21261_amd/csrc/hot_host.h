@@ -97,7 +97,7 @@ struct FusedLayout {
   size_t least, total;                // as in GwLayout
 };
 struct SelLayout {
-  size_t scalars, rowmax, partial, total;
+  size_t scalars, sums, total;
 };
 struct WeightLayout {
   int64_t pitch;
@@ -137,10 +137,9 @@ constexpr int kMaxExchange = kMaxPartials / 4;
 //   mode 0: per-token: codes + scales[rows].
 //   mode 1: abs-max of the rotated tensor: partials[0..*npartials) written.
 //   mode 2: quantise with the tensor-wide abs-max = max(partials); scales[0] written.
-//   mode 3: abs-max per row into scales[rows] and tensor-wide into partials.
 // codes: rows x pitch bytes, `bits` = 4 (two codes per byte, even index in the
 // low nibble) or 8; bytes from cols*bits/8 up to pitch are zero-filled.
-// *npartials is written by modes 1/3 (host value) and read by mode 2.
+// *npartials is written by mode 1 (host value) and read by mode 2.
 hipError_t launch_row_quant(const float* t, int64_t rows, int64_t cols, int n, int bits,
                             int rounding, int mode, uint8_t* codes, int64_t pitch, float* scales,
                             float* partials, int* npartials, hipStream_t s);
@@ -206,11 +205,10 @@ hipError_t launch_igemm(const uint8_t* A, const uint8_t* B, int64_t M, int64_t N
 hipError_t launch_unpack(const uint8_t* codes, int64_t rows, int64_t K, int64_t pitch, int bits,
                          int transpose, int8_t* out, hipStream_t s);
 
-// Squared quantisation error of the rotated t [rows x cols] with per-token and
-// per-tensor scales (rowmax[rows] and partials from launch_row_quant mode 3):
-// result[0] = sum per-token, result[1] = sum per-tensor (double, fixed order).
-hipError_t launch_quant_error(const float* t, int64_t rows, int64_t cols, int n, int bits,
-                              int rounding, const float* rowmax, const float* partials,
-                              int npartials, double* partial, double* result, hipStream_t s);
+// Squared quantisation error of the rotated t [rows x cols]: result[0] = sum with per-token scales,
+// result[1] = with one scale for the tensor (double, fixed order).  Scratch: partials, kMaxPartials
+// floats; sums, two doubles for each of min(rows, kMaxPartials) workgroups.
+hipError_t launch_select(const float* t, int64_t rows, int64_t cols, int n, int bits, int rounding,
+                         float* partials, double* sums, double* result, hipStream_t s);
 
 }  // namespace hot

@@ -2,71 +2,160 @@
 // scales: the measurement behind Layer-wise Quantizer Selection (Sec. 5.2.2).
 // Calibration-time only; sums are double and combined in a fixed order so the
 // result is reproducible run to run.
-#include "hot_device.h"
+//
+// Two passes over g_y, rows held in registers as in row_quant_kernel.h: the first finds each row's
+// abs-max and sums the per-token error on the spot, the second sums the per-tensor error.  A third
+// kernel adds the workgroups' sums.  HBM-bound in the first pass at about the arithmetic's own
+// rate (per element and pass: the butterflies, ten instructions of quantisation and four fp64 ones:
+// the product of code and scale is exact in fp64, so it goes into a fused multiply-add).
+// 16384 x 4096, 64-element blocks: 58 + 49 + 6 us (4.6 and 5.5 TB/s); with one error pass for both
+// scales, a separate multiply and two instructions per stage across lanes it was 49 + 88 + 20 us.
 #include "hot_host.h"
+#include "row_quant_kernel.h"
 
 namespace hot {
 
-__device__ __forceinline__ double sq_err(float t, float inv, float scale, int qmax, int rounding) {
-  const int q = quant_code(t, inv, qmax, rounding);
-  const double e = (double)t - (double)q * (double)scale;
-  return e * e;
+// The quantiser's code as a float (quant_code's value), the random fraction m / 2048 as the
+// difference of two floats of which 1/2048 is the unit in the last place.
+template <int ROUNDING>
+__device__ __forceinline__ float quant_code_float(float t, float inv, float qmax) {
+  const float v = t * inv;
+  float q;
+  if constexpr (ROUNDING == 0) {
+    q = rintf(v);
+  } else {
+    const float f = floorf(v);
+    const float rnd = __uint_as_float(0x45800000u | (__float_as_uint(v) & 0x7FFu)) - 4096.0f;
+    q = v - f > rnd ? f + 1.0f : f;
+  }
+  return fminf(fmaxf(q, -qmax), qmax);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
+// sum + the squared errors (t - q(t) * scale)^2 of four elements.  inv and scale carry the sign the
+// lane's values are held with.
+template <int ROUNDING>
+__device__ __forceinline__ double add_sq_err4(double sum, const float4& t, float inv, double scale, float qmax) {
+  const float e[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-  for (int m = 1; m < 64; m *= 2) v += __shfl_xor(v, m);
-  return v;
+  for (int i = 0; i < 4; ++i) {
+    const double d = fma(-(double)quant_code_float<ROUNDING>(e[i], inv, qmax), scale, (double)e[i]);
+    sum = fma(d, d, sum);
+  }
+  return sum;
 }
 
-// One row per workgroup iteration; partial[2*row + {0,1}] = that row's sums.
-template <int N>
-__global__ __launch_bounds__(256) void quant_error_rows_kernel(
-    const float* __restrict__ t, int64_t rows, int cols, int bits, int rounding,
-    const float* __restrict__ rowmax, const float* __restrict__ partials, int npartials,
-    double* __restrict__ partial) {
-  __shared__ double s_sum[2][4];
+struct SelectArgs {
+  const float* t;
+  int64_t rows;
+  int cols, bits, rounding;
+  float* partials;   // per-token pass: out, the workgroups' maxima; per-tensor pass: in
+  int npartials;
+  double* sums;      // [workgroup of the pass]
+};
+
+// End of a pass: the workgroup's error sum and (per-token pass) abs-max.
+template <bool TOKEN>
+__device__ __forceinline__ void leave_sums(const SelectArgs& a, double sum, float running) {
+  __shared__ double s_sum[4];
+  __shared__ float s_run[4];
   const int tid = threadIdx.x;
-  const int qmax = (1 << (bits - 1)) - 1;
-  const int nvec = cols / 4;
-  const float amax_ten = block_max_of(partials, npartials);
-  const float inv_ten = quant_inv(amax_ten, qmax), sc_ten = quant_scale(amax_ten, qmax);
-  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-    const float4* src = reinterpret_cast<const float4*>(t + row * (int64_t)cols);
-    const float amax_tok = rowmax[row];
-    const float inv_tok = quant_inv(amax_tok, qmax), sc_tok = quant_scale(amax_tok, qmax);
-    double e_tok = 0.0, e_ten = 0.0;
-    for (int base = 0; base < nvec; base += 256) {  // uniform trip count keeps lanes converged
-      const int i = base + tid;
-      float4 q = i < nvec ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-      fwht_row4<N>(q, tid);
-      if (i < nvec) {
-        e_tok += sq_err(q.x, inv_tok, sc_tok, qmax, rounding) + sq_err(q.y, inv_tok, sc_tok, qmax, rounding) +
-                 sq_err(q.z, inv_tok, sc_tok, qmax, rounding) + sq_err(q.w, inv_tok, sc_tok, qmax, rounding);
-        e_ten += sq_err(q.x, inv_ten, sc_ten, qmax, rounding) + sq_err(q.y, inv_ten, sc_ten, qmax, rounding) +
-                 sq_err(q.z, inv_ten, sc_ten, qmax, rounding) + sq_err(q.w, inv_ten, sc_ten, qmax, rounding);
-      }
-    }
-    e_tok = wave_sum(e_tok);
-    e_ten = wave_sum(e_ten);
-    if ((tid & 63) == 0) { s_sum[0][tid >> 6] = e_tok; s_sum[1][tid >> 6] = e_ten; }
-    __syncthreads();
-    if (tid == 0) {
-      partial[2 * row + 0] = (s_sum[0][0] + s_sum[0][1]) + (s_sum[0][2] + s_sum[0][3]);
-      partial[2 * row + 1] = (s_sum[1][0] + s_sum[1][1]) + (s_sum[1][2] + s_sum[1][3]);
-    }
-    __syncthreads();
+#pragma unroll
+  for (int m = 1; m < 64; m *= 2) sum += __shfl_xor(sum, m);
+  if constexpr (TOKEN) running = wave_max(running);
+  if ((tid & 63) == 0) { s_sum[tid >> 6] = sum; s_run[tid >> 6] = running; }
+  __syncthreads();
+  if (tid == 0) {
+    a.sums[blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    if constexpr (TOKEN) a.partials[blockIdx.x] = fmaxf(fmaxf(s_run[0], s_run[1]), fmaxf(s_run[2], s_run[3]));
   }
 }
 
-// Single workgroup: result[c] = sum over rows of partial[2*row + c], fixed order.
-__global__ __launch_bounds__(256) void quant_error_final_kernel(const double* __restrict__ partial,
-                                                                int64_t rows,
-                                                                double* __restrict__ result) {
+template <int N, int ITER, int TPR, bool TOKEN>
+__global__ __launch_bounds__(256) void select_rows_kernel(const SelectArgs a) {
+  constexpr int RPB = 256 / TPR;
+  __shared__ float s_max[4];
+  const int tid = threadIdx.x, rl = tid / TPR;
+  const RowLane<N> lane = row_lane<N>(tid % TPR);
+  const int tr = lane.id;
+  const int qmax = (1 << (a.bits - 1)) - 1;
+  const int64_t nrb = (a.rows + RPB - 1) / RPB;
+  float amax = 0.0f, running = 0.0f;
+  if constexpr (!TOKEN) amax = block_max_of(a.partials, a.npartials);
+  double sum = 0.0;
+  for (int64_t rb0 = blockIdx.x; rb0 < nrb; rb0 += gridDim.x) {
+    // the second pass starts where the first one ended (what the memory-side cache still holds)
+    const int64_t row = (TOKEN ? rb0 : nrb - 1 - rb0) * RPB + rl;
+    const bool row_ok = row < a.rows;
+    const float4* src = reinterpret_cast<const float4*>(a.t + row * (int64_t)a.cols);
+    float4 v[ITER];
+    float m = 0.0f;
+#pragma unroll
+    for (int it = 0; it < ITER; ++it)
+      v[it] = (row_ok && (it * TPR + tr) * 4 < a.cols) ? src[it * TPR + tr] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+      fwht_row4<N>(v[it], lane);
+      m = fmaxf(m, absmax4(v[it]));
+    }
+    if constexpr (TOKEN) {
+      amax = row_max<TPR>(m, s_max);
+      running = fmaxf(running, amax);
+    }
+    const float inv = flip_sign(quant_inv(amax, qmax), lane.flip);
+    const double scale = (double)flip_sign(quant_scale(amax, qmax), lane.flip);
+    if (a.rounding == 0) {   // elements past the row's end are zeros with zero error
+#pragma unroll
+      for (int it = 0; it < ITER; ++it) sum = add_sq_err4<0>(sum, v[it], inv, scale, (float)qmax);
+    } else {
+#pragma unroll
+      for (int it = 0; it < ITER; ++it) sum = add_sq_err4<1>(sum, v[it], inv, scale, (float)qmax);
+    }
+  }
+  leave_sums<TOKEN>(a, sum, running);
+}
+
+// Rows too long for registers: one per workgroup, read twice in the per-token pass.
+template <int N, bool TOKEN>
+__global__ __launch_bounds__(256) void select_stream_kernel(const SelectArgs a) {
+  __shared__ float s_max[4];
+  const int tid = threadIdx.x;
+  const int qmax = (1 << (a.bits - 1)) - 1;
+  const RowLane<N> lane = row_lane<N>(tid);
+  const int nvec = a.cols / 4;
+  float amax = 0.0f, running = 0.0f;
+  if constexpr (!TOKEN) amax = block_max_of(a.partials, a.npartials);
+  double sum = 0.0;
+  for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    const float4* src = reinterpret_cast<const float4*>(a.t + row * (int64_t)a.cols);
+    auto transformed = [&](int base) {   // uniform trip counts keep the lanes of a butterfly together
+      float4 q = base + lane.id < nvec ? src[base + lane.id] : make_float4(0.f, 0.f, 0.f, 0.f);
+      fwht_row4<N>(q, lane);
+      return q;
+    };
+    if constexpr (TOKEN) {
+      float m = 0.0f;
+      for (int base = 0; base < nvec; base += 256) m = fmaxf(m, absmax4(transformed(base)));
+      amax = row_max<256>(m, s_max);
+      running = fmaxf(running, amax);
+    }
+    const float inv = flip_sign(quant_inv(amax, qmax), lane.flip);
+    const double scale = (double)flip_sign(quant_scale(amax, qmax), lane.flip);
+    for (int base = 0; base < nvec; base += 256) {
+      const float4 q = transformed(base);
+      sum = a.rounding == 0 ? add_sq_err4<0>(sum, q, inv, scale, (float)qmax)
+                            : add_sq_err4<1>(sum, q, inv, scale, (float)qmax);
+    }
+  }
+  leave_sums<TOKEN>(a, sum, running);
+}
+
+// Single workgroup: result[c] = sum of sums[c][0 .. count), fixed order.
+__global__ __launch_bounds__(256) void select_final_kernel(const double* __restrict__ sums, int count,
+                                                           double* __restrict__ result) {
   __shared__ double s_sum[2][256];
   const int tid = threadIdx.x;
   double a = 0.0, b = 0.0;
-  for (int64_t row = tid; row < rows; row += 256) { a += partial[2 * row]; b += partial[2 * row + 1]; }
+  for (int i = tid; i < count; i += 256) { a += sums[i]; b += sums[count + i]; }
   s_sum[0][tid] = a;
   s_sum[1][tid] = b;
   __syncthreads();
@@ -77,20 +166,45 @@ __global__ __launch_bounds__(256) void quant_error_final_kernel(const double* __
   if (tid == 0) { result[0] = s_sum[0][0]; result[1] = s_sum[1][0]; }
 }
 
-hipError_t launch_quant_error(const float* t, int64_t rows, int64_t cols, int n, int bits,
-                              int rounding, const float* rowmax, const float* partials,
-                              int npartials, double* partial, double* result, hipStream_t s) {
-  const unsigned grid = (unsigned)(rows < 4096 ? rows : 4096);
-  switch (n) {
-    case 16: quant_error_rows_kernel<16><<<dim3(grid), dim3(256), 0, s>>>(t, rows, (int)cols, bits, rounding, rowmax, partials, npartials, partial); break;
-    case 32: quant_error_rows_kernel<32><<<dim3(grid), dim3(256), 0, s>>>(t, rows, (int)cols, bits, rounding, rowmax, partials, npartials, partial); break;
-    case 64: quant_error_rows_kernel<64><<<dim3(grid), dim3(256), 0, s>>>(t, rows, (int)cols, bits, rounding, rowmax, partials, npartials, partial); break;
-    default: return hipErrorInvalidValue;
+namespace {
+
+template <int N>
+hipError_t launch_passes(SelectArgs a, double* result, hipStream_t s) {
+  double* const sums = a.sums;
+  unsigned grid = 0;
+  const bool held = with_row_layout(a.cols, [&](auto iter_c, auto tpr_c) {
+    constexpr int ITER = decltype(iter_c)::value, TPR = decltype(tpr_c)::value;
+    const int64_t nrb = ceil_div(a.rows, 256 / TPR);
+    grid = (unsigned)(nrb < kMaxPartials ? nrb : kMaxPartials);
+    a.npartials = (int)grid;
+    select_rows_kernel<N, ITER, TPR, true><<<dim3(grid), dim3(256), 0, s>>>(a);
+    a.sums = sums + grid;
+    select_rows_kernel<N, ITER, TPR, false><<<dim3(grid), dim3(256), 0, s>>>(a);
+  });
+  if (!held) {
+    grid = (unsigned)(a.rows < kMaxPartials ? a.rows : kMaxPartials);
+    a.npartials = (int)grid;
+    select_stream_kernel<N, true><<<dim3(grid), dim3(256), 0, s>>>(a);
+    a.sums = sums + grid;
+    select_stream_kernel<N, false><<<dim3(grid), dim3(256), 0, s>>>(a);
   }
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  quant_error_final_kernel<<<dim3(1), dim3(256), 0, s>>>(partial, rows, result);
+  select_final_kernel<<<dim3(1), dim3(256), 0, s>>>(sums, (int)grid, result);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_select(const float* t, int64_t rows, int64_t cols, int n, int bits, int rounding,
+                         float* partials, double* sums, double* result, hipStream_t s) {
+  const SelectArgs a{t, rows, (int)cols, bits, rounding, partials, 0, sums};
+  switch (n) {
+    case 16: return launch_passes<16>(a, result, s);
+    case 32: return launch_passes<32>(a, result, s);
+    case 64: return launch_passes<64>(a, result, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace hot

@@ -282,6 +282,24 @@ def test_select_quantizer_matches_oracle(kind, n):
         assert choice == hot.HOT_Q_PER_TENSOR
 
 
+@pytest.mark.parametrize("L,O,n,bits,rounding", [(37, 16, 16, 4, 1), (35, 64, 64, 8, 1), (17, 96, 32, 4, 0),
+                                                 (9, 128, 64, 4, 1), (33, 192, 64, 8, 0), (5, 16448, 64, 4, 1),
+                                                 (3, 16384, 32, 4, 1)])
+def test_row_layouts(L, O, n, bits, rounding):
+    """Rows held by 16, 32, 64 and 256 threads and streamed ones, with partly filled workgroups and
+    rows that end inside a thread group: the quantised rows and the selection's two sums."""
+    hot = _hot()
+    cfg = hot.Config(block=n, keep=n // 2, gx_bits=bits, rounding=rounding)
+    _, w, gy = make(L, O, 24, seed=23)
+    for per_token in (True, False):
+        check_gx(hot, cfg, gy, w, per_token, "row layouts")
+    choice, m_tok, m_ten = hot.hot_select_quantizer(cfg, gy.cuda(), hot.alloc_workspace(cfg, L, O, 24))
+    ref_choice, r_tok, r_ten = oracle.select_quantizer(gy.numpy(), n, bits=bits, rounding=rounding,
+                                                       threshold=cfg.lqs_threshold)
+    np.testing.assert_allclose([m_tok, m_ten], [r_tok, r_ten], rtol=1e-10)
+    assert choice == int(ref_choice)
+
+
 def test_select_quantizer_zero_gradient():
     hot = _hot()
     cfg = hot.Config()
