@@ -363,9 +363,8 @@ void igemm_kernel(const GemmArgs g) {
     if (g.out_f32 && m0 + BM <= g.M && n0 + BN <= g.N) {
       // A tile that lies inside the output (all but the last tile row and column): no bound
       // checks, and one address per lane for the whole tile: the row within the tile is a
-      // uniform offset on the base pointer, the column block a constant.  The checked form
-      // below costs a dozen instructions and two branches per element, 13 us per 256x256
-      // tile where this one takes 3.
+      // uniform offset on the base pointer, the column block a constant (3 us per 256x256
+      // tile; a checked form with two branches per element took 13).
       const unsigned lane_byte = 4u * (unsigned)((wm0 + 4 * (lane >> 5)) * g.N + nl0);   // < 2^32: inside one tile
       char* const tile = reinterpret_cast<char*>(g.out_f32 + ((int64_t)m0 * g.N + n0));
       auto store_tile = [&](auto nt_c) {
@@ -408,20 +407,39 @@ void igemm_kernel(const GemmArgs g) {
       if (g.stream_out) store_tile(std::true_type{});
       else store_tile(std::false_type{});
     } else if (g.out_f32) {
-      float* obase = g.out_f32 + ((int64_t)m0 * g.N + n0);
+      // The last tile row and column: buffer stores, whose hardware drops what lies past the
+      // descriptor's end: no compare or branch per element, and the row is in the (scalar) base.
+      // A descriptor ends with the output; columns past it start at half the range, which no
+      // descriptor reaches (16 N bytes stay below it: N < 2^27).  Passes of a layer, against a compare and a
+      // branch per element: 3136 tokens 448 x 1792 59.7 -> 56.3 us, 197 tokens 768 x 768
+      // 32.4 -> 31.3, 12608 tokens 3072 x 768 164 -> 161.
+      constexpr unsigned kEnd = 0x80000000u;
+      const int wrow = m0 + __builtin_amdgcn_readfirstlane(wm0);
+      unsigned col_byte[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
+      for (int j = 0; j < TN; ++j)
+        col_byte[j] = n0 + nl0 + j * 32 < g.N ? 4u * (unsigned)(4 * (lane >> 5) * g.N + nl0 + j * 32) : kEnd;
+      auto store_tile = [&](auto nt_c) {
+        constexpr int AUX = decltype(nt_c)::value ? 2 : 0;   // 2: non-temporal
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int ml = wm0 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          if (m0 + ml >= g.M) continue;
-          const float rs = s_rowfac[ml];
-          const int row_off = ml * g.N + nl0;
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            if (n0 + nl0 + j * 32 < g.N) obase[row_off + j * 32] = (float)acc[i][j][v] * rs;
+          for (int v = 0; v < 16; ++v) {
+            const int row = i * 32 + 8 * (v >> 2) + (v & 3);
+            const int64_t first = (int64_t)(wrow + row) * g.N + n0;
+            const int64_t span = 4 * ((int64_t)g.M * g.N - first);
+            const unsigned bytes = span <= 0 ? 0u : (span < (int64_t)kEnd ? (unsigned)span : kEnd);
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g.out_f32 + first, 0, (int)bytes, 0x00027000);
+            const float rs = s_rowfac[wm0 + row + 4 * (lane >> 5)];
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)acc[i][j][v] * rs), rsrc,
+                                                    (int)col_byte[j], 0, AUX);
+          }
         }
-      }
+      };
+      if (g.stream_out) store_tile(std::true_type{});
+      else store_tile(std::false_type{});
     } else {
       int32_t* obase = g.out_i32 + ((int64_t)m0 * g.N + n0);
 #pragma unroll

@@ -901,8 +901,8 @@ def test_gemm_work_distribution(gemm_mode, mode, wait_us):
     owner ever waits, every missing slice is computed by the owner itself (what happens when
     the other workgroup is late); modes 10-13: every GEMM on one given tile shape (128x128,
     192x256, 256x256, 128x256), whatever the planner would pick.  Shapes: few tiles with long
-    K, many tiles, ragged tiles (interior tiles take the unchecked epilogue, edge tiles the
-    checked one), K too short to split."""
+    K, many tiles, ragged tiles (interior tiles take the unchecked epilogue, edge tiles
+    bounds-checked buffer stores), K too short to split."""
     hot = _hot()
     gemm_mode(mode)
     hot.hot_debug_set_exchange_wait_us(wait_us)
@@ -914,6 +914,25 @@ def test_gemm_work_distribution(gemm_mode, mode, wait_us):
         if O % n == 0:
             check_gx(hot, cfg, gy, w, True, f"gemm mode={mode} wait={wait_us}")
             check_gx(hot, hot.Config(block=n, keep=r, gx_bits=8), gy, w, False, f"gemm mode={mode} wait={wait_us}")
+
+
+@pytest.mark.parametrize("mode", [10, 11, 12, 13])
+@pytest.mark.parametrize("L,I", [(1, 1), (5, 33), (129, 257), (383, 300), (255, 771)])
+def test_edge_tiles_end_with_the_output(gemm_mode, mode, L, I):
+    """The last tile row and column of every tile shape: each element that exists is written (the
+    bits of float(accumulator) * scales), and nothing in front of the output or behind it."""
+    hot = _hot()
+    gemm_mode(mode)
+    x, w, gy = make(L, 96, I, seed=77)
+    cfg, pad = hot.Config(block=16, keep=8), 4096
+    ws = hot.alloc_workspace(cfg, L, 96, I)
+    room = torch.full((L * I + 2 * pad,), -7.0, device="cuda")
+    gx = room[pad:pad + L * I].view(L, I)
+    hot.hot_linear_backward_gx(cfg, gy.cuda(), w.cuda(), hot.HOT_Q_PER_TOKEN, gx, ws)
+    taps = hot.hot_debug_gx_operands(cfg, ws, L, 96, I, hot.HOT_Q_PER_TOKEN)
+    torch.cuda.synchronize()
+    assert_output_is_dequantised_accumulator(gx, taps["acc"], taps["sg"], taps["sw"], 16, f"edges mode={mode}")
+    assert bool((room[:pad] == -7.0).all()) and bool((room[pad + L * I:] == -7.0).all())
 
 
 @pytest.mark.parametrize("mode,wait_us", [(3, 200), (4, 0)])
