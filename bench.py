@@ -50,6 +50,8 @@ def stage_model(L, O, I, n, r, gx_bits, per_token, gw_bits=8, Lr=None):
         "gy_fused_absmax": dict(bytes=4 * L * O + (4 * L * ((O + 127) // 128) if per_token else 0)),
         "gy_fused_quant": dict(bytes=4 * L * O + cb * L * O + Lr * O + 4 * L),
         "gx_igemm": dict(ops=2 * L * O * I, bytes=cb * (L * O + I * O) + 4 * L * I, peak=INT8_PEAK_TOPS),
+        "gx_and_gw_igemm": dict(ops=2 * L * O * I + 2 * O * I * Lr, peak=INT8_PEAK_TOPS,
+                                bytes=cb * (L * O + I * O) + 4 * L * I + wb * Lr * (O + I) + 4 * O * I),
         "gw_igemm": dict(ops=2 * O * I * Lr, bytes=wb * Lr * (O + I) + 4 * O * I,
                          peak=BF16_PEAK_TOPS if gw_bits == 16 else INT8_PEAK_TOPS),
     }

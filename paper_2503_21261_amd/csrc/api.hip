@@ -336,16 +336,16 @@ namespace {
 
 // One GEMM on K-contiguous operands of `pitch` bytes, planned for its shape, with the
 // scratch region at base + partial_off and the flag slots of the workspace prefix.
-hipError_t gemm(const Config& c, const uint8_t* A, const uint8_t* B, int64_t M, int64_t N, int64_t pitch,
-                int bits, uint8_t* base, size_t partial_off, int32_t* out_i32, float* out_f32,
-                const float* row_scale, int row_stride, const float* col_scale, int n, hipStream_t s,
-                int stage = -1, bool images = false) {
-  return launch_igemm(A, B, M, N, pitch, pitch, bits, plan_gemm(M, N, pitch, bits, true, images),
-                      (int32_t*)(base + partial_off), (unsigned long long*)(base + kGemmFlagsOffset),
-                      out_i32, out_f32, row_scale, row_stride, col_scale, n, s, stage, c.epoch);
+GemmCall gemm_call(const Config& c, const uint8_t* A, const uint8_t* B, int64_t M, int64_t N, int64_t pitch,
+                   int bits, uint8_t* base, size_t partial_off, int32_t* out_i32, float* out_f32,
+                   const float* row_scale, int row_stride, const float* col_scale) {
+  return GemmCall{A, B, M, N, pitch, bits, (int32_t*)(base + partial_off),
+                  (unsigned long long*)(base + kGemmFlagsOffset), out_i32, out_f32, row_scale, row_stride,
+                  col_scale, c.n, c.epoch};
 }
-
-
+hipError_t gemm(const GemmCall& g, hipStream_t s, int stage = -1, bool images = false) {
+  return launch_igemm(g, plan_gemm(g.M, g.N, g.k_bytes, g.bits, true, images), s, stage);
+}
 
 // g_x path, first half: the rotated, quantised g_y operand (codes at g.qg, scales at g.sg).
 hot_status gx_rows(const Config& c, const float* g_y, int64_t L, int64_t O, hot_quantizer gy_quantizer,
@@ -384,8 +384,8 @@ hot_status gx_operands(const Config& c, const float* g_y, const float* w, int64_
 hot_status gx_gemm(const Config& c, const uint8_t* qw, const float* s_w, int64_t L, int64_t I,
                    hot_quantizer gy_quantizer, float* g_x, uint8_t* base, const GxLayout& g,
                    size_t partial_off, hipStream_t s) {
-  HOT_TRY(gemm(c, base + g.qg, qw, L, I, g.pitch, c.gx_bits, base, partial_off, nullptr, g_x,
-               (const float*)(base + g.sg), gy_quantizer == HOT_Q_PER_TOKEN ? 1 : 0, s_w, c.n, s, kStGxGemm));
+  HOT_TRY(gemm(gemm_call(c, base + g.qg, qw, L, I, g.pitch, c.gx_bits, base, partial_off, nullptr, g_x,
+                         (const float*)(base + g.sg), gy_quantizer == HOT_Q_PER_TOKEN ? 1 : 0, s_w), s, kStGxGemm));
   return HOT_OK;
 }
 
@@ -532,8 +532,8 @@ hot_status hot_linear_backward_gw(const hot_config* cfg, const float* g_y, const
   HOT_TRY(begin_call(c, ws, s));
   st = gw_operand(c, g_y, L, O, qg, g.pitch, s_g, part_g, s);
   if (st != HOT_OK) return st;
-  HOT_TRY(gemm(c, qg, abase + a.codes, O, I, g.pitch, c.gw_bits, base, g.partial, nullptr, g_w, s_g, 0,
-               (const float*)abase, c.n, s, kStGwGemm, ws_bytes >= g.total));
+  HOT_TRY(gemm(gemm_call(c, qg, abase + a.codes, O, I, g.pitch, c.gw_bits, base, g.partial, nullptr, g_w, s_g, 0,
+                         (const float*)abase), s, kStGwGemm, ws_bytes >= g.total));
   return HOT_OK;
 }
 
@@ -567,11 +567,16 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
     if (st != HOT_OK) return st;
     st = gw_operand(c, g_y, L, O, base + f.qgh, f.gw.pitch, (float*)(base + f.s_gh), (float*)(base + kHeaderBytes), s);
     if (st != HOT_OK) return st;
-    st = gx_gemm(c, base + f.gx.qw, (const float*)(base + f.gx.scalars), L, I, gy_quantizer, g_x, base, f.gx,
-                 f.partial, s);
-    if (st != HOT_OK) return st;
-    HOT_TRY(gemm(c, base + f.qgh, (const uint8_t*)act_buf + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial,
-                 nullptr, g_w, (const float*)(base + f.s_gh), 0, (const float*)act_buf, c.n, s, kStGwGemm, images));
+    const GemmCall gx = gemm_call(c, base + f.gx.qg, base + f.gx.qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr,
+                                  g_x, (const float*)(base + f.gx.sg), gy_quantizer == HOT_Q_PER_TOKEN ? 1 : 0,
+                                  (const float*)(base + f.gx.scalars));
+    const GemmCall gw = gemm_call(c, base + f.qgh, (const uint8_t*)act_buf + a.codes, O, I, f.gw.pitch, c.gw_bits, base,
+                                  f.partial, nullptr, g_w, (const float*)(base + f.s_gh), 0, (const float*)act_buf);
+    bool both = false;
+    if (g_backward_strategy.load() != 3) HOT_TRY(launch_gemm_pair(gw, images, gx, s, kStGemmPair, &both));
+    if (both) return HOT_OK;
+    HOT_TRY(gemm(gx, s, kStGxGemm));
+    HOT_TRY(gemm(gw, s, kStGwGemm, images));
     return HOT_OK;
   }
   float* s_w = (float*)(base + f.gx.scalars);
@@ -589,10 +594,10 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
                            part_a, s, kStWAbsmax, kStWQuant));
   HOT_TRY(launch_gy_fused(g_y, L, O, c, per_token, qg, f.gx.pitch, s_g, qgh, f.gw.pitch, s_gh, part_a,
                           part_b, (float*)(base + f.rowpart), s, kStGyFusedAbsmax, kStGyFusedQuant));
-  HOT_TRY(gemm(c, qg, qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr, g_x, s_g,
-               per_token ? 1 : 0, s_w, c.n, s, kStGxGemm));
-  HOT_TRY(gemm(c, qgh, abase + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial, nullptr, g_w, s_gh,
-               0, (const float*)abase, c.n, s, kStGwGemm, images));
+  HOT_TRY(gemm(gemm_call(c, qg, qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr, g_x, s_g,
+                         per_token ? 1 : 0, s_w), s, kStGxGemm));
+  HOT_TRY(gemm(gemm_call(c, qgh, abase + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial, nullptr, g_w, s_gh,
+                         0, (const float*)abase), s, kStGwGemm, images));
   return HOT_OK;
 }
 
@@ -715,8 +720,8 @@ hot_status hot_debug_gx_operands(const hot_config* cfg, void* ws, int64_t L, int
                            hipMemcpyDeviceToDevice, s));
   if (w_scale) HOT_TRY(hipMemcpyAsync(w_scale, base + g.scalars, 4, hipMemcpyDeviceToDevice, s));
   if (acc)
-    HOT_TRY(gemm(c, base + g.qg, base + g.qw, L, I, g.pitch, c.gx_bits, base, g.partial, acc, nullptr,
-                 nullptr, 0, nullptr, c.n, s));
+    HOT_TRY(gemm(gemm_call(c, base + g.qg, base + g.qw, L, I, g.pitch, c.gx_bits, base, g.partial, acc, nullptr,
+                           nullptr, 0, nullptr), s));
   return HOT_OK;
 }
 
@@ -735,8 +740,8 @@ hot_status hot_debug_gw_operands(const hot_config* cfg, void* ws, const void* ac
   if (gy_codes) HOT_TRY(launch_unpack(base + g.qg, O, g.Lr, g.pitch, c.gw_bits, 1, gy_codes, s));
   if (gy_scale) HOT_TRY(hipMemcpyAsync(gy_scale, base + g.scalars, 4, hipMemcpyDeviceToDevice, s));
   if (acc)
-    HOT_TRY(gemm(c, base + g.qg, (const uint8_t*)act_buf + a.codes, O, I, g.pitch, c.gw_bits, base,
-                 g.partial, acc, nullptr, nullptr, 0, nullptr, c.n, s));
+    HOT_TRY(gemm(gemm_call(c, base + g.qg, (const uint8_t*)act_buf + a.codes, O, I, g.pitch, c.gw_bits, base,
+                           g.partial, acc, nullptr, nullptr, 0, nullptr), s));
   return HOT_OK;
 }
 
@@ -761,8 +766,8 @@ hot_status hot_debug_fused_operands(const hot_config* cfg, void* ws, const void*
   if (gyT_codes) HOT_TRY(launch_unpack(base + f.qgh, O, f.gw.Lr, f.gw.pitch, 8, 1, gyT_codes, s));
   if (gyT_scale) HOT_TRY(hipMemcpyAsync(gyT_scale, base + f.s_gh, 4, hipMemcpyDeviceToDevice, s));
   if (acc_gw)
-    HOT_TRY(gemm(c, base + f.qgh, (const uint8_t*)act_buf + a.codes, O, I, f.gw.pitch, 8, base, f.partial,
-                 acc_gw, nullptr, nullptr, 0, nullptr, c.n, s));
+    HOT_TRY(gemm(gemm_call(c, base + f.qgh, (const uint8_t*)act_buf + a.codes, O, I, f.gw.pitch, 8, base, f.partial,
+                           acc_gw, nullptr, nullptr, 0, nullptr), s));
   return HOT_OK;
 }
 

@@ -118,7 +118,7 @@ WeightLayout weight_layout(const Config& c, int64_t O, int64_t I);
 
 // Kernel roles for the optional stage timer (names in profile.hip).
 enum Stage {
-  kStUnused = 0, kStActAbsmax, kStActQuant, kStWAbsmax, kStWQuant, kStGyRowQuant, kStGyRowAbsmax,
+  kStGemmPair = 0, kStActAbsmax, kStActQuant, kStWAbsmax, kStWQuant, kStGyRowQuant, kStGyRowAbsmax,
   kStGyRowQuant2, kStGxGemm, kStGyTAbsmax, kStGyTQuant, kStGwGemm, kStWGyRow, kStGyFusedAbsmax,
   kStGyFusedQuant
 };
@@ -187,18 +187,31 @@ hipError_t launch_w_and_rows(const float* w, int64_t O, int64_t I, const Config&
                              int64_t pitch, float* s_w, float* slots, const float* g_y, int64_t L,
                              uint8_t* qg, float* s_g, hipStream_t s, int stage, bool* done);
 
-// C[M x N] = A[M x K] . B[N x K]^T on K-contiguous code rows (pitch bytes each,
-// k_bytes = K * bits / 8 rounded up to the pitch alignment).
+// One GEMM: C[M x N] = A[M x K] . B[N x K]^T on K-contiguous code rows of k_bytes each
+// (K * bits / 8 rounded up to the pitch alignment).
 //   out_i32 != NULL: raw int32 accumulators, row-major [M x N].
 //   out_f32 != NULL: out = acc * row_scale[m * row_stride] * (*col_scale) / n.
-// plan.split > 1 needs `partial` (plan.partial_bytes) and `flags` (kMaxSplitSlots slots
+// A split of K needs `partial` (plan.partial_bytes) and `flags` (kMaxSplitSlots slots
 // that only such launches ever write).  `epoch`: device address of the workspace epoch when
 // the launch tag is to be derived from it (replayable calls), else null.
-hipError_t launch_igemm(const uint8_t* A, const uint8_t* B, int64_t M, int64_t N, int64_t k_bytes,
-                        int64_t pitch, int bits, const GemmPlan& plan, int32_t* partial,
-                        unsigned long long* flags, int32_t* out_i32, float* out_f32,
-                        const float* row_scale, int row_stride, const float* col_scale, int n,
-                        hipStream_t s, int gemm_stage = -1, const unsigned long long* epoch = nullptr);
+struct GemmCall {
+  const uint8_t *A, *B;
+  int64_t M, N, k_bytes;
+  int bits;
+  int32_t* partial;
+  unsigned long long* flags;
+  int32_t* out_i32;
+  float* out_f32;
+  const float* row_scale;
+  int row_stride;
+  const float* col_scale;
+  int n;
+  const unsigned long long* epoch;
+};
+hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage = -1);
+// Both GEMMs of a layer in one launch where all their workgroups are resident at once: `w` with its
+// own plan on 128x128 tiles, `x` (INT4) on unsplit tiles.  *done says whether the launch was made.
+hipError_t launch_gemm_pair(const GemmCall& w, bool images, const GemmCall& x, hipStream_t s, int stage, bool* done);
 
 // Unpack K-contiguous codes [rows x pitch] into one int8 per code.
 //   transpose = 0: out[row * K + k];  transpose = 1: out[k * rows + row].

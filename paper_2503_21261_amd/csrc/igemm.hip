@@ -269,6 +269,22 @@ int slice_placement(const GemmArgs& g, int64_t tiles) {
   return cols;
 }
 
+// What a hand-over launch needs beyond the tile grid: its tag, placement and bounded wait.
+template <int BM>
+hipError_t prepare_hand_over(GemmArgs& g, int64_t k_bytes, bool int4) {
+  const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
+  if (!g.partial || !g.flags || tiles * (g.split - 1) > kMaxSplitSlots) return hipErrorInvalidValue;
+  g.tag = next_exchange_tag();   // the process-wide launch tag sequence
+  g.xcd_cols = slice_placement<BM>(g, tiles);
+  // an image normally arrives before its owner has finished its own slice; the bound only
+  // has to cover workgroups that start late: never less than the whole GEMM takes at 200 TOP/s
+  int64_t wait_us = g_gemm_wait_us.load();
+  const int64_t gemm_us = (int64_t)(2.0 * g.M * g.N * (double)k_bytes * (int4 ? 2 : 1) / 200e6);
+  if (wait_us > 0 && wait_us < gemm_us) wait_us = gemm_us;
+  g.wait_ticks = wait_us < 0 ? 0 : wait_us * 100;
+  return hipSuccess;
+}
+
 template <int BM, int BN, int BKB, bool INT4, bool BF16 = false>
 hipError_t launch_tile(GemmArgs g, int64_t k_bytes, const GemmPlan& plan, hipStream_t s, int gemm_stage) {
   const int split = plan.split;
@@ -297,49 +313,123 @@ hipError_t launch_tile(GemmArgs g, int64_t k_bytes, const GemmPlan& plan, hipStr
   if constexpr (BF16 || BM == 192 || BM != BN || (INT4 && BM != 128)) {
     return hipErrorInvalidValue;   // splits exist for the 128x128 tiles and the 256x256 INT8 tile
   } else {
-    if (!g.partial || !g.flags || tiles * (split - 1) > kMaxSplitSlots) return hipErrorInvalidValue;
-    g.tag = next_exchange_tag();   // the process-wide launch tag sequence
-    g.xcd_cols = slice_placement<BM>(g, tiles);
-    // an image normally arrives before its owner has finished its own slice; the bound only
-    // has to cover workgroups that start late: never less than the whole GEMM takes at 200 TOP/s
-    int64_t wait_us = g_gemm_wait_us.load();
-    const int64_t gemm_us = (int64_t)(2.0 * g.M * g.N * (double)k_bytes * (INT4 ? 2 : 1) / 200e6);
-    if (wait_us > 0 && wait_us < gemm_us) wait_us = gemm_us;
-    g.wait_ticks = wait_us < 0 ? 0 : wait_us * 100;
+    const hipError_t e = prepare_hand_over<BM>(g, k_bytes, INT4);
+    if (e != hipSuccess) return e;
     return launch_kernel<BM, BN, BKB, INT4, false, kHandOver>(g, (unsigned)(tiles * split), s, gemm_stage);
   }
 }
 
-}  // namespace
-
-hipError_t launch_igemm(const uint8_t* A, const uint8_t* B, int64_t M, int64_t N, int64_t k_bytes,
-                        int64_t pitch, int bits, const GemmPlan& plan, int32_t* partial,
-                        unsigned long long* flags, int32_t* out_i32, float* out_f32,
-                        const float* row_scale, int row_stride, const float* col_scale, int n,
-                        hipStream_t s, int gemm_stage, const unsigned long long* epoch) {
-  if (M <= 0 || N <= 0) return hipSuccess;
+GemmArgs gemm_args(const GemmCall& c) {
   GemmArgs g;
-  g.A = A;
-  g.B = B;
-  g.M = (int)M;
-  g.N = (int)N;
-  g.pitch = pitch;
-  g.out_i32 = out_i32;
-  g.out_f32 = out_i32 ? nullptr : out_f32;  // int32 wins; callers ask one at a time
-  g.partial = partial;
-  g.flags = flags;
+  g.A = c.A;
+  g.B = c.B;
+  g.M = (int)c.M;
+  g.N = (int)c.N;
+  g.pitch = c.k_bytes;
+  g.out_i32 = c.out_i32;
+  g.out_f32 = c.out_i32 ? nullptr : c.out_f32;  // int32 wins; callers ask one at a time
+  g.partial = c.partial;
+  g.flags = c.flags;
   g.tag = 0;
-  g.epoch = epoch;
+  g.epoch = c.epoch;
   g.wait_ticks = 0;
-  g.row_scale = row_scale;
-  g.row_stride = row_stride;
-  g.col_scale = col_scale;
-  g.inv_n = 1.0f / (float)n;
+  g.row_scale = c.row_scale;
+  g.row_stride = c.row_stride;
+  g.col_scale = c.col_scale;
+  g.inv_n = 1.0f / (float)c.n;
   g.xcd_cols = 0;
   // measured on MI355X: streaming stores win for INT8 / bfloat16 operands and for INT4 GEMMs of
   // up to 3072 codes of K (ViT-B fc2 at 50432 tokens 167 -> 134 us, ViT-B fc1 at 12608 tokens
   // 44.5 -> 39.6 us), and lose 3 % at 4096 codes and a wide output (LLM down-projection)
-  g.stream_out = (bits != 4 || k_bytes * 2 <= 3072) ? 1 : 0;
+  g.stream_out = (c.bits != 4 || c.k_bytes * 2 <= 3072) ? 1 : 0;
+  return g;
+}
+
+// The g_w GEMM's workgroups (first: each runs longer, and a hand-over's owners wait for the others)
+// and the g_x GEMM's in one launch.  Each alone leaves most units idle behind its prologue, its
+// few K stages and its epilogue, and a launch behind another costs 5 us however little it does:
+// layer passes of 512 tokens 768 x 768 31.2 -> 25.7 us, 3136 x 448 x 1792 56.3 -> 48.4, 3330 x 1008 x
+// 771 70.2 -> 56.3.
+template <int BN, bool BF16, int SPLIT>
+__global__ __launch_bounds__(256, 2) void gemm_pair_kernel(const GemmArgs gw, const GemmArgs gx, const int gw_wgs) {
+  if ((int)blockIdx.x < gw_wgs) igemm_body<128, 128, 2, 2, 128, false, BF16, SPLIT>(gw, (int)blockIdx.x);
+  else igemm_body<128, BN, 2, 2, 64, true, false, kWholeK>(gx, (int)blockIdx.x - gw_wgs);
+}
+
+template <int BN, bool BF16, int SPLIT>
+hipError_t launch_pair_kernel(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, int gx_wgs, hipStream_t s) {
+  constexpr size_t lds_w = 2 * (128 + 128) * 128, lds_x = 2 * (128 + BN) * 64;
+  constexpr size_t lds = lds_w > lds_x ? lds_w : lds_x;
+  auto kern = gemm_pair_kernel<BN, BF16, SPLIT>;
+  static std::atomic<bool> attr_set{false};
+  if (!attr_set.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set.store(true, std::memory_order_release);
+  }
+  kern<<<dim3((unsigned)(gw_wgs + gx_wgs)), dim3(256), lds, s>>>(gw, gx, gw_wgs);
+  return hipGetLastError();
+}
+
+template <int BN>
+hipError_t launch_pair_tile(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, int gx_wgs, int bits, int split, bool images,
+                            hipStream_t s) {
+  hipError_t e;
+  if (bits == 16)
+    e = images ? launch_pair_kernel<BN, true, kImages>(gw, gx, gw_wgs, gx_wgs, s)
+               : launch_pair_kernel<BN, true, kWholeK>(gw, gx, gw_wgs, gx_wgs, s);
+  else if (images) e = launch_pair_kernel<BN, false, kImages>(gw, gx, gw_wgs, gx_wgs, s);
+  else if (split > 1) e = launch_pair_kernel<BN, false, kHandOver>(gw, gx, gw_wgs, gx_wgs, s);
+  else e = launch_pair_kernel<BN, false, kWholeK>(gw, gx, gw_wgs, gx_wgs, s);
+  if (e != hipSuccess || !images) return e;
+  const unsigned grid = (unsigned)((int64_t)gw.tiles_m * gw.tiles_n * 64);
+  if (bits == 16) combine_images_kernel<true><<<dim3(grid), dim3(256), 0, s>>>(gw);
+  else combine_images_kernel<false><<<dim3(grid), dim3(256), 0, s>>>(gw);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, hipStream_t s, int stage, bool* done) {
+  *done = false;
+  if (g_gemm_mode.load() != 0 || cx.bits != 4 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
+  const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images);
+  if (p.bm != 128 || p.bn != 128) return hipSuccess;
+  const int64_t w = p.tiles * p.split, cap = 2 * (int64_t)compute_units();
+  // Two workgroups per unit are resident (LDS of the g_w tile, registers); 128x128 g_x tiles while
+  // they fit beside the g_w workgroups, else half as many of 128x256.
+  const int64_t rows = ceil_div(cx.M, 128), x128 = rows * ceil_div(cx.N, 128), x256 = rows * ceil_div(cx.N, 256);
+  if (w + x256 > cap) return hipSuccess;
+  const bool narrow = w + x128 <= cap;
+  GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
+  gw.nk_total = (int)(cw.k_bytes / 128);
+  gw.tiles_m = (int)ceil_div(cw.M, 128);
+  gw.tiles_n = (int)ceil_div(cw.N, 128);
+  gw.split = p.split;
+  if (p.images) {
+    if (!gw.partial) return hipErrorInvalidValue;
+    gw.xcd_cols = p.split % 8 == 0 ? -2 : slice_placement<128>(gw, p.tiles);
+  } else if (p.split > 1) {
+    const hipError_t e = prepare_hand_over<128>(gw, cw.k_bytes, false);
+    if (e != hipSuccess) return e;
+  }
+  gx.nk_total = (int)(cx.k_bytes / 64);
+  gx.tiles_m = (int)rows;
+  gx.tiles_n = (int)ceil_div(cx.N, narrow ? 128 : 256);
+  gx.split = 1;
+  stage_begin(stage, s);
+  const hipError_t e = narrow ? launch_pair_tile<128>(gw, gx, (int)w, (int)x128, cw.bits, p.split, p.images, s)
+                              : launch_pair_tile<256>(gw, gx, (int)w, (int)x256, cw.bits, p.split, p.images, s);
+  stage_end(stage, s);
+  *done = true;
+  return e;
+}
+
+hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage) {
+  if (c.M <= 0 || c.N <= 0) return hipSuccess;
+  const GemmArgs g = gemm_args(c);
+  const int64_t k_bytes = c.k_bytes;
+  const int bits = c.bits;
   const int gs = gemm_stage;
   if (bits == 16) {
     if (plan.bm == 256) return launch_tile<256, 256, 128, false, true>(g, k_bytes, plan, s, gs);

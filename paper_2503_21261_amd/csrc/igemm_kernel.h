@@ -140,10 +140,10 @@ struct Operands {            // what the matrix instructions of one K slice cons
 template <int BM, int BN, bool INT4>
 constexpr int gemm_min_waves_per_simd() { return (INT4 && BM == 128 && BN == 256) ? 2 : 1; }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BKB, bool INT4, bool BF16 = false,
-          int SPLIT = kWholeK>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (gemm_min_waves_per_simd<BM, BN, INT4>()))
-void igemm_kernel(const GemmArgs g) {
+// Body for workgroup `bid` of a GEMM's workgroups (the whole grid, or a part of a grid whose other
+// workgroups do unrelated work).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BKB, bool INT4, bool BF16, int SPLIT>
+__device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
   static_assert(!(INT4 && BF16), "one operand format");
   static_assert(!(SPLIT == kHandOver && BF16), "fp32 sums would depend on which workgroup added a piece");
   using acc_t = std::conditional_t<BF16, v16f, v16i>;
@@ -462,7 +462,7 @@ void igemm_kernel(const GemmArgs g) {
 
   if constexpr (SPLIT == kWholeK) {
     int tm, tn;
-    tile_of_position(g, xcd_contiguous(blockIdx.x, g.tiles_m * g.tiles_n), tm, tn);
+    tile_of_position(g, xcd_contiguous(bid, g.tiles_m * g.tiles_n), tm, tn);
     set_tile(tm, tn);
     fill_rowfac();
     zero_acc();
@@ -472,13 +472,13 @@ void igemm_kernel(const GemmArgs g) {
   } else {
     constexpr int IMG = BM * BN;
     const int tiles = g.tiles_m * g.tiles_n, nk = g.nk_total, S = g.split;
-    int z = blockIdx.x / tiles;   // slices in dispatch order: owners (z = S - 1) start last
+    int z = bid / tiles;   // slices in dispatch order: owners (z = S - 1) start last
     int tm, tn, t;
     if (SPLIT == kImages && g.xcd_cols == -2) {
       // 8 divides S: an XCD works on every eighth slice, all of its tiles, so that both operands
       // of a slice are fetched by one XCD.
-      const int j = blockIdx.x >> 3;
-      z = (blockIdx.x & 7) + 8 * (j / tiles);
+      const int j = bid >> 3;
+      z = (bid & 7) + 8 * (j / tiles);
       t = j % tiles;
       tm = t / g.tiles_n;
       tn = t % g.tiles_n;
@@ -486,7 +486,7 @@ void igemm_kernel(const GemmArgs g) {
       // S divides 8: the XCDs are dealt to the slices, 8 / S to each, and the XCDs of a slice
       // share its tiles by row bands.  An A row band of a slice is then fetched by one XCD, a B
       // band by 8 / S of them: the whole GEMM fetches A once and B 8 / S times.
-      const int per = 8 / S, x = blockIdx.x & 7, j = blockIdx.x >> 3;   // XCD, index within it
+      const int per = 8 / S, x = bid & 7, j = bid >> 3;   // XCD, index within it
       z = x / per;
       t = (x % per) * (tiles / per) + j;
       tm = t / g.tiles_n;
@@ -496,13 +496,13 @@ void igemm_kernel(const GemmArgs g) {
       // rectangle of the tile grid, in every slice the same one: an operand row band is then
       // fetched by the xcd_cols XCDs that share it and by no other (with the band walk below the
       // bands of a small grid end up on three to eight of them).
-      t = blockIdx.x - z * tiles;          // tiles is a multiple of 8 here: XCD = t % 8
+      t = bid - z * tiles;          // tiles is a multiple of 8 here: XCD = t % 8
       const int x = t & 7, j = t >> 3;
       const int rm = g.tiles_m / (8 / g.xcd_cols), rn = g.tiles_n / g.xcd_cols;
       tm = (x / g.xcd_cols) * rm + j % rm;
       tn = (x % g.xcd_cols) * rn + j / rm;
     } else {
-      t = xcd_contiguous(blockIdx.x - z * tiles, tiles);
+      t = xcd_contiguous(bid - z * tiles, tiles);
       tile_of_position(g, t, tm, tn);
     }
     auto slice_begin = [&](int zz) { return (int)(((int64_t)zz * nk) / S); };
@@ -602,6 +602,13 @@ void igemm_kernel(const GemmArgs g) {
     }
     }
   }
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BKB, bool INT4, bool BF16 = false,
+          int SPLIT = kWholeK>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (gemm_min_waves_per_simd<BM, BN, INT4>()))
+void igemm_kernel(const GemmArgs g) {
+  igemm_body<BM, BN, WAVES_M, WAVES_N, BKB, INT4, BF16, SPLIT>(g, (int)blockIdx.x);
 }
 
 // Second half of a kImages split on 128x128 tiles: adds the S images of a tile in slice order and

@@ -1003,6 +1003,45 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
+@pytest.mark.parametrize("L,O,I,n,S,gw_bits", [
+    (512, 768, 768, 16, 0, 8),        # one slice per g_w tile
+    (3136, 448, 1792, 16, 49, 8),     # g_w slices handed over, 128x256 g_x tiles, padded blocks
+    (3330, 1008, 771, 16, 333, 8),    # ragged in every direction
+    (2048, 128, 130, 32, 0, 8),       # g_w images added by a second kernel
+    (2048, 256, 320, 16, 0, 16),      # bfloat16 images
+    (64, 96, 40, 32, 0, 16),          # bfloat16, one slice
+    (16, 16, 1, 16, 0, 8)])           # one workgroup each
+@pytest.mark.parametrize("wait_us", [200, 0])
+def test_both_gemms_in_one_launch_and_apart(gemm_mode, L, O, I, n, S, gw_bits, wait_us):
+    """Small layers run both GEMMs in one launch; strategy 3 gives each its own.  The same bits, and
+    nothing written outside the outputs."""
+    hot = _hot()
+    x, w, gy = make(L, O, I, seed=79)
+    cfg, pad = hot.Config(block=n, keep=n // 2, sample_tokens=S, gw_bits=gw_bits), 1024
+    xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, xd, act, ws)
+    outs = []
+    try:
+        for strategy in (0, 3):
+            hot.hot_debug_set_backward_strategy(strategy)
+            hot.hot_debug_set_exchange_wait_us(wait_us)
+            for q in (hot.HOT_Q_PER_TOKEN, hot.HOT_Q_PER_TENSOR):
+                room = torch.full((L * I + O * I + 3 * pad,), -7.0, device="cuda")
+                at = pad + L * I + pad + (-(L * I)) % 4
+                gx, gw = room[pad:pad + L * I].view(L, I), room[at:at + O * I].view(O, I)
+                hot.hot_linear_backward(cfg, gyd, wd, act, q, gx, gw, ws)
+                torch.cuda.synchronize()
+                for a, b in ((0, pad), (pad + L * I, at), (at + O * I, room.numel())):
+                    assert bool((room[a:b] == -7.0).all())
+                outs.append((gx.clone(), gw.clone()))
+    finally:
+        hot.hot_debug_set_backward_strategy(0)
+        hot.hot_debug_set_exchange_wait_us(200)
+    for a, b in zip(outs[:2], outs[2:]):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
 def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode):
     """Two different inputs alternate through the same workspace, twelve back-to-back steps
     without a host synchronisation in between: every g_w must equal the one computed without
