@@ -563,10 +563,27 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
     // kernel starts right behind the g_x GEMM, whose last 256 MB of output are then still on
     // their way from that cache to HBM (a streaming read behind a 1 GB write runs at 73 % of
     // its rate); the g_w GEMM, which moves few bytes, runs there instead.
-    st = gx_operands(c, g_y, w, L, O, I, gy_quantizer, base, f.gx, s);
-    if (st != HOT_OK) return st;
-    st = gw_operand(c, g_y, L, O, base + f.qgh, f.gw.pitch, (float*)(base + f.s_gh), (float*)(base + kHeaderBytes), s);
-    if (st != HOT_OK) return st;
+    const bool per_token = gy_quantizer == HOT_Q_PER_TOKEN;
+    float* const slots = (float*)(base + kHeaderBytes);
+    float* const slots2 = (float*)(base + kHeaderBytes + kPartialBytes);
+    float* const s_g = (float*)(base + f.gx.sg);
+    float* const rowpart = (float*)(base + f.rowpart);
+    bool all = false;
+    int npart = 0;
+    if (g_backward_strategy.load() != 3)
+      HOT_TRY(launch_operands(w, O, I, c, base + f.gx.qw, f.gx.pitch, (float*)(base + f.gx.scalars), slots, g_y, L,
+                              per_token, base + f.gx.qg, s_g, rowpart, &npart, base + f.qgh, f.gw.pitch,
+                              (float*)(base + f.s_gh), slots2, s, kStWGyRow, &all));
+    if (all) {
+      if (!per_token)
+        HOT_STAGE(kStGyRowQuant2, launch_row_quant(g_y, L, O, c.n, c.gx_bits, c.rounding, 2, base + f.gx.qg, f.gx.pitch,
+                                                   s_g, rowpart, &npart, s));
+    } else {
+      st = gx_operands(c, g_y, w, L, O, I, gy_quantizer, base, f.gx, s);
+      if (st != HOT_OK) return st;
+      st = gw_operand(c, g_y, L, O, base + f.qgh, f.gw.pitch, (float*)(base + f.s_gh), slots, s);
+      if (st != HOT_OK) return st;
+    }
     const GemmCall gx = gemm_call(c, base + f.gx.qg, base + f.gx.qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr,
                                   g_x, (const float*)(base + f.gx.sg), gy_quantizer == HOT_Q_PER_TOKEN ? 1 : 0,
                                   (const float*)(base + f.gx.scalars));

@@ -1,5 +1,5 @@
-// First launch of the g_x path (Sec. 5.1) when both of its operands are produced in one
-// kernel: the leading workgroups transform and quantise the weights (H.w, one scale, the
+// Operands made by shared launches.  First launch of the g_x path (Sec. 5.1) when both of its
+// operands are produced in one kernel (and below, those of both GEMMs of a small layer): the leading workgroups transform and quantise the weights (H.w, one scale, the
 // single-pass column kernel with its abs-max exchange), the rest rotate and quantise the
 // rows of g_y per token.  The two jobs are independent; sharing a launch lets the rows
 // stream from HBM while the few weight workgroups sit in the latencies of their exchange,
@@ -86,7 +86,142 @@ hipError_t front_n(FrontArgs& f, hipStream_t s, int stage, bool* done) {
   return hipSuccess;
 }
 
+// All operands of a small layer's two GEMMs in one launch: the weight tiles and the tiles of g_y's
+// token-direction view (each set exchanging its own maxima, all resident at once), then the rows of
+// g_y (per token, or the abs-max pass of one scale per tensor).  Three launches otherwise, each far
+// from filling the chip; bound by one tile's chain of load, exchange, quantise, store.  The settings
+// are branches, not instantiations: registers are those of the widest (KB blocks per wave on both
+// sides), which with KB = 1 leaves five workgroups per unit (three for 64-row
+// blocks).  Layer passes: 512 tokens 768 x 768 25.7 -> 21.9 us, 3136 x 448 x 1792 48.4 -> 43.0, 3330 x 1008 x
+// 771 with one g_y scale 56.3 -> 48.4.
+template <int N, int KB>
+__global__ __launch_bounds__(256, 2) void operands_kernel(const OnepassArgs wa, const int w_tiles, const OnepassArgs ga,
+                                                          const int g_tiles, const int half, const RowQuantArgs ra,
+                                                          const int layout) {
+  constexpr int VEC = onepass_vec(N);
+  int bid = (int)blockIdx.x;
+  if (bid < w_tiles) {
+    if (VEC == 1 || wa.C % VEC != 0) onepass_body<N, 1, kKeepAll4, KB>(wa, bid, w_tiles);
+    else onepass_body<N, VEC, kKeepAll4, KB>(wa, bid, w_tiles);
+    return;
+  }
+  bid -= w_tiles;
+  if (bid < g_tiles) {
+    if (half) onepass_body<N, VEC, kKeepLowHalf, KB>(ga, bid, g_tiles);
+    else onepass_body<N, VEC, kKeepGeneric, KB>(ga, bid, g_tiles);
+    return;
+  }
+  bid -= g_tiles;
+  const int nbid = (int)gridDim.x - w_tiles - g_tiles;
+  switch (layout) {
+#define HOT_LAYOUT(ITER, TPR) \
+  case ITER * 1000 + TPR: row_quant_body<N, ITER, TPR>(ra, bid, nbid); break;
+    HOT_LAYOUT(1, 16) HOT_LAYOUT(1, 32) HOT_LAYOUT(1, 64) HOT_LAYOUT(2, 64) HOT_LAYOUT(3, 64) HOT_LAYOUT(4, 64)
+    HOT_LAYOUT(2, 256) HOT_LAYOUT(3, 256) HOT_LAYOUT(4, 256)
+#undef HOT_LAYOUT
+  }
+}
+
+struct OperandArgs {
+  OnepassArgs wa, ga;
+  int half;
+  RowQuantArgs ra;
+  int layout;
+  int64_t nrb;
+};
+
+template <int N, int KB>
+hipError_t try_operands(const OperandArgs& f, hipStream_t s, int stage, bool* done) {
+  constexpr int VEC = onepass_vec(N);
+  if (*done) return hipSuccess;
+  const int wv = f.wa.C % VEC == 0 ? VEC : 1;
+  const int64_t wt = ceil_div(f.wa.C, 64 * wv) * ceil_div(f.wa.rt.nblk, 4 * KB);
+  const int64_t gt = ceil_div(f.ga.C, 64 * VEC) * ceil_div(f.ga.rt.nblk, 4 * KB);
+  if (wt > kMaxExchange || gt > kMaxExchange) return hipSuccess;
+  const int bpb = f.ga.r > N / 2 ? f.ga.r : N / 2;   // code bytes per block and column, of either side at most
+  size_t lds = (size_t)(64 * VEC) * (4 * KB * bpb + 4);
+  if (lds < onepass_stage_bytes<N, VEC, kKeepGeneric>()) lds = onepass_stage_bytes<N, VEC, kKeepGeneric>();
+  constexpr size_t lds_max = (size_t)(64 * VEC) * (4 * KB * N + 4);   // never below the staging bytes
+  auto kern = operands_kernel<N, KB>;
+  int64_t resident;
+  {
+    static std::mutex mu;
+    static int per_cu = -1, cus = 0;
+    static size_t lds_seen = 0;
+    std::lock_guard<std::mutex> lock(mu);
+    if (per_cu < 0 || lds != lds_seen) {
+      int dev = 0, nb = 0;
+      hipError_t e = hipGetDevice(&dev);
+      if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+      if (e == hipSuccess && per_cu < 0 && lds_max > 48 * 1024)
+        e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+      if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 256, lds);
+      if (e != hipSuccess) return e;
+      per_cu = nb;
+      lds_seen = lds;
+    }
+    resident = (int64_t)per_cu * cus;
+  }
+  if (wt + gt > resident) return hipSuccess;
+  stage_begin(stage, s);
+  kern<<<dim3((unsigned)(wt + gt + f.nrb)), dim3(256), lds, s>>>(f.wa, (int)wt, f.ga, (int)gt, f.half, f.ra, f.layout);
+  stage_end(stage, s);
+  *done = true;
+  return hipGetLastError();
+}
+
+template <int N>
+hipError_t operands_n(const OperandArgs& f, hipStream_t s, int stage, bool* done) {
+  // one block per wave: the most workgroups, the shortest chain; two where one leaves more than
+  // 512 workgroups (the exchange's slots) on a side
+  hipError_t e = try_operands<N, 1>(f, s, stage, done);
+  if (e == hipSuccess) e = try_operands<N, 2>(f, s, stage, done);
+  return e;
+}
+
+// Bounded wait (100 MHz ticks) of the single-pass workgroups over `bytes` of input.
+long long wait_ticks(int64_t wait_us, int64_t bytes) {
+  const int64_t stream_us = bytes / 1000000;   // as in the column kernel's own launcher
+  return (wait_us > 0 && wait_us < stream_us ? stream_us : wait_us) * 100;
+}
+
 }  // namespace
+
+hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw, int64_t pitch, float* s_w,
+                           float* slots_w, const float* g_y, int64_t L, bool per_token, uint8_t* qg, float* s_g,
+                           float* row_partials, int* npartials, uint8_t* qgh, int64_t pitch_h, float* s_gh,
+                           float* slots_g, hipStream_t s, int stage, bool* done) {
+  *done = false;
+  const int64_t wait_us = exchange_wait_us();
+  if (wait_us < 0 || cfg.gx_bits != 4 || cfg.gw_bits != 8 || O > 4096) return hipSuccess;
+  KeepMap id;
+  for (int k = 0; k < 64; ++k) id.pos[k] = (int8_t)(k < cfg.n ? k : -1);
+  const RowTiling rt = row_tiling(cfg, L);
+  OperandArgs f;
+  f.wa = OnepassArgs{w, RowTiling{O / cfg.n, 0, 1}, I, id, cfg.n, cfg.rounding,
+                     reinterpret_cast<unsigned long long*>(slots_w), next_exchange_tag(), cfg.epoch,
+                     wait_ticks(wait_us, O * I * 4), qw, pitch, s_w};
+  f.ga = OnepassArgs{g_y, rt, O, cfg.map, cfg.r, cfg.rounding, reinterpret_cast<unsigned long long*>(slots_g),
+                     next_exchange_tag(), cfg.epoch, wait_ticks(wait_us, rt.nblk * cfg.n * O * 4), qgh, pitch_h, s_gh};
+  f.half = cfg.lowpass_default && cfg.r * 2 == cfg.n;
+  f.layout = 0;
+  f.nrb = 0;
+  with_row_layout(O, [&](auto iter_c, auto tpr_c) {
+    constexpr int ITER = decltype(iter_c)::value, TPR = decltype(tpr_c)::value;
+    f.layout = ITER * 1000 + TPR;
+    f.nrb = ceil_div(L, 256 / TPR);
+  });
+  if (!per_token && f.nrb > kMaxPartials) f.nrb = kMaxPartials;
+  if (f.nrb > (1 << 20)) return hipSuccess;
+  f.ra = RowQuantArgs{g_y, L, (int)O, 4, cfg.rounding, per_token ? 0 : 1, qg, pitch, s_g, row_partials, 0};
+  *npartials = (int)f.nrb;
+  switch (cfg.n) {
+    case 16: return operands_n<16>(f, s, stage, done);
+    case 32: return operands_n<32>(f, s, stage, done);
+    case 64: return operands_n<64>(f, s, stage, done);
+  }
+  return hipSuccess;
+}
 
 hipError_t launch_w_and_rows(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw,
                              int64_t pitch, float* s_w, float* slots, const float* g_y, int64_t L,

@@ -187,6 +187,16 @@ hipError_t launch_w_and_rows(const float* w, int64_t O, int64_t I, const Config&
                              int64_t pitch, float* s_w, float* slots, const float* g_y, int64_t L,
                              uint8_t* qg, float* s_g, hipStream_t s, int stage, bool* done);
 
+// All three operands of a small layer in one launch (INT4 g_x, INT8 g_w, O up to 4096, both column
+// jobs' workgroups resident at once): those of launch_w_and_rows and the token-direction view of g_y
+// ([O x pitch_h] codes, *s_gh).  With one g_y scale per tensor the rows' part is the abs-max pass only:
+// row_partials[0 .. *npartials), for mode 2 of launch_row_quant.  slots_*: kMaxPartials floats each;
+// row_partials: L floats at least.  *done as above.
+hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw, int64_t pitch, float* s_w,
+                           float* slots_w, const float* g_y, int64_t L, bool per_token, uint8_t* qg, float* s_g,
+                           float* row_partials, int* npartials, uint8_t* qgh, int64_t pitch_h, float* s_gh,
+                           float* slots_g, hipStream_t s, int stage, bool* done);
+
 // One GEMM: C[M x N] = A[M x K] . B[N x K]^T on K-contiguous code rows of k_bytes each
 // (K * bits / 8 rounded up to the pitch alignment).
 //   out_i32 != NULL: raw int32 accumulators, row-major [M x N].

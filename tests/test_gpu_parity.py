@@ -1003,21 +1003,28 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
-@pytest.mark.parametrize("L,O,I,n,S,gw_bits", [
-    (512, 768, 768, 16, 0, 8),        # one slice per g_w tile
-    (3136, 448, 1792, 16, 49, 8),     # g_w slices handed over, 128x256 g_x tiles, padded blocks
-    (3330, 1008, 771, 16, 333, 8),    # ragged in every direction
-    (2048, 128, 130, 32, 0, 8),       # g_w images added by a second kernel
-    (2048, 256, 320, 16, 0, 16),      # bfloat16 images
-    (64, 96, 40, 32, 0, 16),          # bfloat16, one slice
-    (16, 16, 1, 16, 0, 8)])           # one workgroup each
+@pytest.mark.parametrize("L,O,I,n,S,gw_bits,keep_idx", [
+    (512, 768, 768, 16, 0, 8, None),        # one slice per g_w tile
+    (3136, 448, 1792, 16, 49, 8, [0, 1, 2, 4, 8, 5, 3, 12]),   # slices handed over, 128x256 g_x tiles, padded blocks
+    (3330, 1008, 771, 16, 333, 8, None),    # ragged in every direction, one column per lane
+    (8192, 640, 65, 16, 0, 8, None),        # two blocks per wave
+    (8192, 640, 64, 32, 0, 8, None),
+    (16384, 640, 33, 64, 0, 8, None),
+    (1024, 64, 130, 64, 0, 8, list(range(64))),   # every row kept, in natural order
+    (333, 4096, 40, 32, 333, 8, [7, 1, 30]),      # longest row, three rows kept
+    (2048, 128, 130, 32, 0, 8, None),       # g_w images added by a second kernel
+    (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
+    (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
+    (16, 16, 1, 16, 0, 8, None)])           # one workgroup each
 @pytest.mark.parametrize("wait_us", [200, 0])
-def test_both_gemms_in_one_launch_and_apart(gemm_mode, L, O, I, n, S, gw_bits, wait_us):
-    """Small layers run both GEMMs in one launch; strategy 3 gives each its own.  The same bits, and
-    nothing written outside the outputs."""
+def test_small_layers_in_few_launches_and_apart(gemm_mode, L, O, I, n, S, gw_bits, keep_idx, wait_us):
+    """Small layers have their operands made in one launch and both GEMMs run in another; strategy 3
+    gives every kernel its own.  The same bits, and nothing written outside the outputs."""
     hot = _hot()
     x, w, gy = make(L, O, I, seed=79)
-    cfg, pad = hot.Config(block=n, keep=n // 2, sample_tokens=S, gw_bits=gw_bits), 1024
+    cfg = hot.Config(block=n, keep=len(keep_idx) if keep_idx else n // 2, sample_tokens=S, gw_bits=gw_bits,
+                     keep_idx=keep_idx)
+    pad = 1024
     xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
     act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
     hot.hot_compress_activation(cfg, xd, act, ws)
