@@ -65,6 +65,9 @@ hot_status resolve_config(const hot_config* cfg, Config* out) {
     out->keep[j] = k;
     out->map.pos[k] = (int8_t)j;
   }
+  int32_t lp[64];
+  out->lp_l1 = cfg->keep_idx && r * 2 == n && hot_lowpass_l1_rows(n, r, lp) == HOT_OK &&
+               memcmp(lp, cfg->keep_idx, sizeof(int32_t) * (size_t)r) == 0;
   return HOT_OK;
 }
 

@@ -17,11 +17,11 @@ __global__ __launch_bounds__(256) void col_bf16_kernel(const float* __restrict__
                                                        int64_t C, KeepMap map, int r, int kbw,
                                                        uint8_t* __restrict__ out, int64_t pitch,
                                                        float* __restrict__ scale) {
-  static_assert(KIND == kKeepLowHalf || KIND == kKeepGeneric, "kept list");
+  static_assert(KIND == kKeepLowHalf || KIND == kKeepLpL1 || KIND == kKeepGeneric, "kept list");
   constexpr int CT = 64;
   extern __shared__ __align__(16) uint8_t tile[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int bpb = 2 * (KIND == kKeepLowHalf ? N / 2 : r);   // bytes per block and column
+  const int bpb = 2 * (KIND == kKeepGeneric ? r : N / 2);   // bytes per block and column
   const int TB = 4 * kbw * bpb, TBP = TB + 4;
   const int64_t nblk = rt.nblk;
   const int64_t tiles_x = (C + CT - 1) / CT;
@@ -43,11 +43,11 @@ __global__ __launch_bounds__(256) void col_bf16_kernel(const float* __restrict__
     block_rows<N>(rt, gb, first, valid);
     load_block_kept<N, 1, KIND>(x + first * C + c0, C, valid, v);
     uint8_t* dst = tile + lane * TBP + slot * bpb;
-    if constexpr (KIND == kKeepLowHalf) {
+    if constexpr (KIND != kKeepGeneric) {
 #pragma unroll
       for (int j2 = 0; j2 < N / 4; ++j2) {
-        const uint32_t lo = bf16_rne(v[0][lowpass_row(N, 2 * j2) >> 1]);
-        const uint32_t hi = bf16_rne(v[0][lowpass_row(N, 2 * j2 + 1) >> 1]);
+        const uint32_t lo = bf16_rne(v[0][kept_index<N, KIND>(2 * j2)]);
+        const uint32_t hi = bf16_rne(v[0][kept_index<N, KIND>(2 * j2 + 1)]);
         reinterpret_cast<uint32_t*>(dst)[j2] = lo | (hi << 16);
       }
     } else {
@@ -76,6 +76,7 @@ hipError_t launch_n(const float* x, const RowTiling& rt, int64_t C, const Config
   const size_t lds = (size_t)64 * (4 * kbw * bpb + 4);
   const dim3 grid((unsigned)tiles(kbw));
   if (low) col_bf16_kernel<N, kKeepLowHalf><<<grid, dim3(256), lds, s>>>(x, rt, C, cfg.map, cfg.r, kbw, out, pitch, scale);
+  else if (cfg.lp_l1) col_bf16_kernel<N, kKeepLpL1><<<grid, dim3(256), lds, s>>>(x, rt, C, cfg.map, cfg.r, kbw, out, pitch, scale);
   else col_bf16_kernel<N, kKeepGeneric><<<grid, dim3(256), lds, s>>>(x, rt, C, cfg.map, cfg.r, kbw, out, pitch, scale);
   return hipGetLastError();
 }

@@ -28,11 +28,13 @@ void set_exchange_wait_us(int us) { g_exchange_wait_us.store(us); }
 int exchange_wait_us() { return g_exchange_wait_us.load(); }
 uint64_t next_exchange_tag() { return next_tag(); }
 
-ColPlan plan_col(int64_t nblk, int64_t C, int n, int r, int bits, bool lowpass_default, bool identity) {
+ColPlan plan_col(const Config& cfg, int64_t nblk, int64_t C, int r, int bits, bool identity) {
+  const int n = cfg.n;
   ColPlan p;
   if (bits == 4) p.kind = kKeepAll4;
   else if (identity && r == n) p.kind = kKeepAll8;
-  else if (lowpass_default && r * 2 == n) p.kind = kKeepLowHalf;
+  else if (!identity && cfg.lowpass_default && r * 2 == n) p.kind = kKeepLowHalf;
+  else if (!identity && cfg.lp_l1) p.kind = kKeepLpL1;
   else p.kind = kKeepGeneric;
   const int bpb = bits == 4 ? n / 2 : r;
   const int vdiv = (C % 4 == 0) ? 4 : (C % 2 == 0 ? 2 : 1);
@@ -94,9 +96,8 @@ hipError_t launch_quant(const ColArgs& a, const ColPlan& p, hipStream_t s) {
 
 // Single-pass launch with KB blocks per wave; *done stays false (nothing launched) when
 // that grid would not be resident all at once or the lane would hold too many values.
-template <int N, int KIND, int KB>
+template <int N, int VEC, int KIND, int KB>
 hipError_t try_onepass(const ColArgs& a, hipStream_t s, int sq, int round, bool* done) {
-  constexpr int VEC = onepass_vec(N);
   if constexpr (onepass_kept_regs<N, VEC, KIND, KB>() > kOnepassMaxKept) {
     return hipSuccess;
   } else {
@@ -163,9 +164,20 @@ hipError_t try_onepass(const ColArgs& a, hipStream_t s, int sq, int round, bool*
 // blocks per wave against 44.8 us with 7).
 template <int N, int KIND>
 hipError_t launch_onepass(const ColArgs& a, hipStream_t s, int sq, bool* done) {
+  constexpr int VEC = onepass_vec(N);
   hipError_t e = hipSuccess;
+  if constexpr (VEC == 2) {
+    if (a.C % 2 != 0) {   // one column per lane, up to twice the blocks
 #define HOT_TRY_KB(KB, ROUND) \
-  if (e == hipSuccess && !*done) e = try_onepass<N, KIND, KB>(a, s, sq, ROUND, done);
+  if (e == hipSuccess && !*done) e = try_onepass<N, 1, KIND, KB>(a, s, sq, ROUND, done);
+      HOT_TRY_KB(4, 0) HOT_TRY_KB(8, 0) HOT_TRY_KB(16, 0) HOT_TRY_KB(20, 0)
+      HOT_TRY_KB(1, 2) HOT_TRY_KB(2, 2) HOT_TRY_KB(4, 2) HOT_TRY_KB(8, 2) HOT_TRY_KB(16, 2) HOT_TRY_KB(20, 2)
+      return e;
+    }
+  }
+#undef HOT_TRY_KB
+#define HOT_TRY_KB(KB, ROUND) \
+  if (e == hipSuccess && !*done) e = try_onepass<N, VEC, KIND, KB>(a, s, sq, ROUND, done);
   HOT_TRY_KB(1, 0) HOT_TRY_KB(2, 0) HOT_TRY_KB(4, 0) HOT_TRY_KB(8, 0) HOT_TRY_KB(10, 0)
   HOT_TRY_KB(1, 1) HOT_TRY_KB(2, 1) HOT_TRY_KB(3, 1) HOT_TRY_KB(4, 1) HOT_TRY_KB(5, 1) HOT_TRY_KB(7, 1)
   HOT_TRY_KB(8, 1) HOT_TRY_KB(10, 1)
@@ -201,6 +213,7 @@ template <int N>
 hipError_t launch_n(const ColArgs& a, const ColPlan& p, hipStream_t s, int sa, int sq) {
   switch (p.kind) {
     case kKeepLowHalf: return launch_nk<N, kKeepLowHalf>(a, p, s, sa, sq);
+    case kKeepLpL1: return launch_nk<N, kKeepLpL1>(a, p, s, sa, sq);
     case kKeepAll8: return launch_nk<N, kKeepAll8>(a, p, s, sa, sq);
     case kKeepAll4: return launch_nk<N, kKeepAll4>(a, p, s, sa, sq);
     default: return launch_nk<N, kKeepGeneric>(a, p, s, sa, sq);
@@ -215,7 +228,7 @@ hipError_t launch_col_quant(const float* x, const RowTiling& rows, int64_t C, co
                             int stage_absmax, int stage_quant) {
   if (rows.nblk <= 0 || C <= 0) return hipSuccess;
   if (bits == 4 && !(identity && r == cfg.n)) return hipErrorInvalidValue;
-  const ColPlan p = plan_col(rows.nblk, C, cfg.n, r, bits, cfg.lowpass_default && !identity, identity);
+  const ColPlan p = plan_col(cfg, rows.nblk, C, r, bits, identity);
   const ColArgs a{x, rows, C, map, r, cfg.rounding, codes, pitch, scale, partials, cfg.epoch};
   switch (cfg.n) {
     case 16: return launch_n<16>(a, p, s, stage_absmax, stage_quant);

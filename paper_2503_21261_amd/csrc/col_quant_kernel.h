@@ -45,6 +45,40 @@ __host__ __device__ constexpr int lowpass_row(int n, int j) {
   return r;
 }
 
+// The first half of the LP_L1 list (the order hot_lowpass_l1_rows states) as a compile-time table.
+template <int N>
+struct LpL1Rows {
+  int row[N / 2];
+  static constexpr int changes(int n, int k) {   // sign changes along row k of the n-point matrix
+    int c = 0, prev = 0;
+    for (int j = 0; j < n; ++j) {
+      int neg = 0;
+      for (int b = k & j; b; b &= b - 1) neg ^= 1;
+      c += j > 0 && neg != prev;
+      prev = neg;
+    }
+    return c;
+  }
+  constexpr LpL1Rows() : row() {
+    constexpr int gw = N == 16 ? 4 : 8;
+    int key[N] = {};
+    for (int k = 0; k < N; ++k) {
+      const int sv = changes(N / gw, k / gw), sh = changes(gw, k % gw);
+      key[k] = (((sv + sh) * 64 + (sv > sh ? sv : sh)) * 64 + sv) * 64 + k;
+    }
+    for (int k = 0; k < N; ++k) {
+      int rank = 0;
+      for (int i = 0; i < N; ++i) rank += key[i] < key[k];
+      if (rank < N / 2) row[rank] = k;
+    }
+  }
+};
+template <int N>
+__host__ __device__ constexpr int lp_l1_row(int j) {
+  constexpr LpL1Rows<N> t;
+  return t.row[j];
+}
+
 // First row of block gb and how many of its N rows are real tokens (the rest are zeros).
 template <int N>
 __device__ __forceinline__ void block_rows(const RowTiling& t, int64_t gb, int64_t& first, int& valid) {
@@ -66,6 +100,7 @@ enum KeepKind {
   kKeepLowHalf = 1,   // the n/2 rows of lowest sequency, in sequency order; INT8
   kKeepAll8 = 2,      // all rows, natural order; INT8
   kKeepAll4 = 3,      // all rows, natural order; INT4, two codes per byte
+  kKeepLpL1 = 4,      // the n/2 first rows of the LP_L1 list, in its order; INT8
 };
 
 // Load one block (N rows x VEC columns per lane) and transform it in registers.
@@ -204,7 +239,19 @@ __device__ __forceinline__ void fwht_even_rows(const float (&v)[N], float (&s)[N
 // Values a lane keeps per column of a block: only the kept half when that is known at
 // compile time.
 template <int N, int KIND>
-constexpr int kept_vals() { return KIND == kKeepLowHalf ? N / 2 : N; }
+constexpr int kept_vals() { return KIND == kKeepLowHalf || KIND == kKeepLpL1 ? N / 2 : N; }
+
+// Where the kept form holds output row j of a compile-time kept list.
+template <int N, int KIND>
+__host__ __device__ constexpr int kept_index(int j) { return KIND == kKeepLowHalf ? lowpass_row(N, j) >> 1 : j; }
+
+// Full transform of a column, in kept form: the rows of the list only.
+template <int N>
+__device__ __forceinline__ void fwht_lp_l1(float (&full)[N], float (&v)[N / 2]) {
+  fwht_regs<N>(full);
+#pragma unroll
+  for (int j = 0; j < N / 2; ++j) v[j] = full[lp_l1_row<N>(j)];
+}
 
 // The N rows of one block as loaded (zeros when `ok` is false; nothing is dereferenced
 // then).  `rows` is wave-uniform (the block's first row at the tile's first column), `col`
@@ -236,6 +283,17 @@ __device__ __forceinline__ void transform_kept(const typename VecT<VEC>::type (&
     }
 #pragma unroll
     for (int vi = 0; vi < VEC; ++vi) fwht_regs<N / 2>(v[vi]);
+  } else if constexpr (KIND == kKeepLpL1) {
+    float full[VEC][N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      float o[VEC];
+      unpack_vec<VEC>(q[k], o);
+#pragma unroll
+      for (int vi = 0; vi < VEC; ++vi) full[vi][k] = o[vi];
+    }
+#pragma unroll
+    for (int vi = 0; vi < VEC; ++vi) fwht_lp_l1<N>(full[vi], v[vi]);
   } else {
 #pragma unroll
     for (int k = 0; k < N; ++k) {
@@ -250,11 +308,11 @@ __device__ __forceinline__ void transform_kept(const typename VecT<VEC>::type (&
 }
 
 // Load one block and return its transformed values in kept form: all N natural rows, or
-// (kKeepLowHalf) the even natural rows, row 2j' at index j'.
+// (kKeepLowHalf) the even natural rows, row 2j' at index j', or (kKeepLpL1) the listed rows.
 template <int N, int VEC, int KIND>
 __device__ __forceinline__ void load_block_kept(const float* __restrict__ src, int64_t C, int valid,
                                                 float (&v)[VEC][kept_vals<N, KIND>()]) {
-  if constexpr (KIND == kKeepLowHalf) {
+  if constexpr (KIND == kKeepLowHalf || KIND == kKeepLpL1) {
     float full[VEC][N];
     using VT = typename VecT<VEC>::type;
     VT q[N];
@@ -267,7 +325,10 @@ __device__ __forceinline__ void load_block_kept(const float* __restrict__ src, i
       for (int vi = 0; vi < VEC; ++vi) full[vi][k] = o[vi];
     }
 #pragma unroll
-    for (int vi = 0; vi < VEC; ++vi) fwht_even_rows<N>(full[vi], v[vi]);
+    for (int vi = 0; vi < VEC; ++vi) {
+      if constexpr (KIND == kKeepLowHalf) fwht_even_rows<N>(full[vi], v[vi]);
+      else fwht_lp_l1<N>(full[vi], v[vi]);
+    }
   } else {
     load_block_fwht<N, VEC>(src, C, valid, v);
   }
@@ -276,7 +337,7 @@ __device__ __forceinline__ void load_block_kept(const float* __restrict__ src, i
 template <int N, int VEC, int KIND>
 __device__ __forceinline__ float kept_form_absmax(const float (&v)[VEC][kept_vals<N, KIND>()],
                                                   const KeepMap& map) {
-  if constexpr (KIND == kKeepLowHalf) {
+  if constexpr (KIND == kKeepLowHalf || KIND == kKeepLpL1) {
     float m = 0.0f;
 #pragma unroll
     for (int k = 0; k < N / 2; ++k) {
@@ -293,7 +354,7 @@ template <int N, int VEC, int KIND>
 __device__ __forceinline__ void store_kept_form_codes(const float (&v)[VEC][kept_vals<N, KIND>()],
                                                       uint8_t* tile, int lane, int off, int TBP,
                                                       const KeepMap& map, float inv, int rounding) {
-  if constexpr (KIND == kKeepLowHalf) {
+  if constexpr (KIND == kKeepLowHalf || KIND == kKeepLpL1) {
 #pragma unroll
     for (int vi = 0; vi < VEC; ++vi) {
       uint32_t* dst = reinterpret_cast<uint32_t*>(tile + (vi * 64 + lane) * TBP + off);
@@ -301,7 +362,7 @@ __device__ __forceinline__ void store_kept_form_codes(const float (&v)[VEC][kept
       for (int j4 = 0; j4 < N / 8; ++j4) {
         int c[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) c[e] = quant_code(v[vi][lowpass_row(N, j4 * 4 + e) >> 1], inv, 127, rounding);
+        for (int e = 0; e < 4; ++e) c[e] = quant_code(v[vi][kept_index<N, KIND>(j4 * 4 + e)], inv, 127, rounding);
         dst[j4] = pack4_codes8(c[0], c[1], c[2], c[3]);
       }
     }
@@ -448,7 +509,7 @@ __device__ __forceinline__ void pack_kept_codes(const float (&v)[kept_vals<N, KI
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = j4 * 4 + e;
-        c[e] = quant_code(v[KIND == kKeepLowHalf ? (lowpass_row(N, j) >> 1) : j], inv, 127, ROUNDING);
+        c[e] = quant_code(v[kept_index<N, KIND>(j)], inv, 127, ROUNDING);
       }
       out[j4] = pack4_codes8(c[0], c[1], c[2], c[3]);
     }
@@ -477,7 +538,7 @@ constexpr int kOnepassMaxKept = 160;
 // per-lane staging for the recomputation of another workgroup's maximum, used by one wave
 // at a time (that path is rare; a small footprint keeps more workgroups per compute unit).
 template <int N, int VEC, int KIND>
-constexpr size_t onepass_stage_bytes() { return (size_t)kept_vals<N, KIND>() * 64 * VEC * 4; }
+constexpr size_t onepass_stage_bytes() { return (size_t)(KIND == kKeepLowHalf ? N / 2 : N) * 64 * VEC * 4; }
 
 // Whether a lane of the single-pass kernel stores its codes straight from registers: the
 // kept list is known at compile time and the lane's KB blocks give at least 48 consecutive
@@ -617,7 +678,7 @@ __device__ __forceinline__ void onepass_body(const OnepassArgs& a, const int bid
     // Recompute the missing tiles' maxima with few registers: rows are read one (pair) at
     // a time in a rolled loop and staged in this thread's own LDS column (the code tile is
     // not in use yet), then transformed from there.
-    constexpr int NS = kept_vals<N, KIND>();
+    constexpr int NS = KIND == kKeepLowHalf ? N / 2 : N;
     float* stage = reinterpret_cast<float*>(tile) + lane * VEC;
     for (int turn = 0; turn < 4; ++turn) {   // the four waves take turns at the staging column
       if (turn == w) {
@@ -664,7 +725,15 @@ __device__ __forceinline__ void onepass_body(const OnepassArgs& a, const int bid
             }
 #pragma unroll
             for (int vi = 0; vi < VEC; ++vi) fwht_regs<NS>(t[vi]);
-            amax = fmaxf(amax, kept_form_absmax<N, VEC, KIND>(t, map));
+            if constexpr (KIND == kKeepLpL1) {
+#pragma unroll
+              for (int vi = 0; vi < VEC; ++vi) {
+#pragma unroll
+                for (int j = 0; j < N / 2; ++j) amax = fmaxf(amax, fabsf(t[vi][lp_l1_row<N>(j)]));
+              }
+            } else {
+              amax = fmaxf(amax, kept_form_absmax<N, VEC, KIND>(t, map));
+            }
           }
         }
       }
@@ -810,7 +879,8 @@ __global__ __launch_bounds__(256, 2) void col_quant_onepass_kernel(const Onepass
   onepass_body<N, VEC, KIND, KB>(a, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// Columns per lane of the single-pass kernel: two for 16-row blocks, else one.
+// Columns per lane of the single-pass kernel: two for 16-row blocks (one where the width is odd),
+// else one.
 __host__ __device__ constexpr int onepass_vec(int n) { return n == 16 ? 2 : 1; }
 
 // Host-side launch parameters shared by the two passes.
@@ -823,6 +893,6 @@ struct ColPlan {
   size_t lds_q;
 };
 
-ColPlan plan_col(int64_t nblk, int64_t C, int n, int r, int bits, bool lowpass_default, bool identity);
+ColPlan plan_col(const Config& cfg, int64_t nblk, int64_t C, int r, int bits, bool identity);
 
 }  // namespace hot

@@ -96,7 +96,7 @@ hipError_t front_n(FrontArgs& f, hipStream_t s, int stage, bool* done) {
 // 771 with one g_y scale 56.3 -> 48.4.
 template <int N, int KB>
 __global__ __launch_bounds__(256, 2) void operands_kernel(const OnepassArgs wa, const int w_tiles, const OnepassArgs ga,
-                                                          const int g_tiles, const int half, const RowQuantArgs ra,
+                                                          const int g_tiles, const int g_kind, const RowQuantArgs ra,
                                                           const int layout) {
   constexpr int VEC = onepass_vec(N);
   int bid = (int)blockIdx.x;
@@ -107,7 +107,8 @@ __global__ __launch_bounds__(256, 2) void operands_kernel(const OnepassArgs wa, 
   }
   bid -= w_tiles;
   if (bid < g_tiles) {
-    if (half) onepass_body<N, VEC, kKeepLowHalf, KB>(ga, bid, g_tiles);
+    if (g_kind == kKeepLowHalf) onepass_body<N, VEC, kKeepLowHalf, KB>(ga, bid, g_tiles);
+    else if (g_kind == kKeepLpL1) onepass_body<N, VEC, kKeepLpL1, KB>(ga, bid, g_tiles);
     else onepass_body<N, VEC, kKeepGeneric, KB>(ga, bid, g_tiles);
     return;
   }
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void operands_kernel(const OnepassArgs wa, 
 
 struct OperandArgs {
   OnepassArgs wa, ga;
-  int half;
+  int g_kind;
   RowQuantArgs ra;
   int layout;
   int64_t nrb;
@@ -164,7 +165,7 @@ hipError_t try_operands(const OperandArgs& f, hipStream_t s, int stage, bool* do
   }
   if (wt + gt > resident) return hipSuccess;
   stage_begin(stage, s);
-  kern<<<dim3((unsigned)(wt + gt + f.nrb)), dim3(256), lds, s>>>(f.wa, (int)wt, f.ga, (int)gt, f.half, f.ra, f.layout);
+  kern<<<dim3((unsigned)(wt + gt + f.nrb)), dim3(256), lds, s>>>(f.wa, (int)wt, f.ga, (int)gt, f.g_kind, f.ra, f.layout);
   stage_end(stage, s);
   *done = true;
   return hipGetLastError();
@@ -203,7 +204,7 @@ hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& c
                      wait_ticks(wait_us, O * I * 4), qw, pitch, s_w};
   f.ga = OnepassArgs{g_y, rt, O, cfg.map, cfg.r, cfg.rounding, reinterpret_cast<unsigned long long*>(slots_g),
                      next_exchange_tag(), cfg.epoch, wait_ticks(wait_us, rt.nblk * cfg.n * O * 4), qgh, pitch_h, s_gh};
-  f.half = cfg.lowpass_default && cfg.r * 2 == cfg.n;
+  f.g_kind = cfg.lowpass_default && cfg.r * 2 == cfg.n ? kKeepLowHalf : (cfg.lp_l1 ? kKeepLpL1 : kKeepGeneric);
   f.layout = 0;
   f.nrb = 0;
   with_row_layout(O, [&](auto iter_c, auto tpr_c) {

@@ -34,6 +34,7 @@ struct Config {
   int keep[64];   // r natural-order indices, in output order
   KeepMap map;    // inverse of keep
   bool lowpass_default;
+  bool lp_l1;     // keep_idx is the first half of the LP_L1 list
   bool replayable;   // launch tags derived from the workspace epoch (HIP graph replays)
   const unsigned long long* epoch;   // device address of that epoch for the current call, or null
 };

@@ -819,6 +819,24 @@ def test_column_quantiser_paths(exchange_wait, wait_us):
             check_gx(hot, hot.Config(block=n, keep=r, keep_idx=keep_idx, gx_bits=8), gy, w, False, f"wait={wait_us}")
 
 
+@pytest.mark.parametrize("wait_us", [200, 0, -1])
+@pytest.mark.parametrize("n,L,O,I,lp", [
+    (16, 1040, 48, 771, False),     # odd width: one column per lane, 4 blocks per wave
+    (16, 8208, 16, 1025, False),    # an odd number of blocks on more of them
+    (16, 49 * 40, 64, 131, True),   # odd width, listed rows, padded blocks
+    (16, 8192, 640, 384, True), (32, 4096, 96, 130, True), (64, 8192, 64, 257, True), (64, 64, 64, 1, True)])
+def test_column_quantiser_odd_widths_and_lp_l1_rows(exchange_wait, n, L, O, I, lp, wait_us):
+    """The compile-time LP_L1 list and the one-column-per-lane form of 16-row blocks: single pass, single
+    pass with every other maximum recomputed, two passes; and the bfloat16 operand of the same list."""
+    hot = _hot()
+    exchange_wait(wait_us)
+    x, w, gy = make(L, O, I, seed=81)
+    keep = dict(keep=n // 2, keep_idx=hot.hot_lowpass_l1_rows(n, n // 2) if lp else None, sample_tokens=49 if L % 49 == 0 else 0)
+    check_gw(hot, hot.Config(block=n, **keep), gy, x, f"odd / LP_L1 wait={wait_us}")
+    if wait_us == 200 and not keep["sample_tokens"]:
+        check_gw_bf16(hot, hot.Config(block=n, gw_bits=16, **keep), gy, x, "odd / LP_L1 bf16")
+
+
 def test_single_pass_16_row_blocks_with_an_odd_block_count():
     """16-row blocks leave 8 code bytes per block and column, which the single-pass kernel
     stores two blocks at a time; with an odd number of blocks the last pair's second half is
@@ -1015,6 +1033,8 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     (2048, 128, 130, 32, 0, 8, None),       # g_w images added by a second kernel
     (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
     (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
+    (2048, 256, 130, 32, 0, 8, "lp_l1"),    # the compile-time LP_L1 list
+    (1040, 128, 96, 16, 0, 8, "lp_l1"),
     (16, 16, 1, 16, 0, 8, None)])           # one workgroup each
 @pytest.mark.parametrize("wait_us", [200, 0])
 def test_small_layers_in_few_launches_and_apart(gemm_mode, L, O, I, n, S, gw_bits, keep_idx, wait_us):
@@ -1022,6 +1042,8 @@ def test_small_layers_in_few_launches_and_apart(gemm_mode, L, O, I, n, S, gw_bit
     gives every kernel its own.  The same bits, and nothing written outside the outputs."""
     hot = _hot()
     x, w, gy = make(L, O, I, seed=79)
+    if keep_idx == "lp_l1":
+        keep_idx = hot.hot_lowpass_l1_rows(n, n // 2)
     cfg = hot.Config(block=n, keep=len(keep_idx) if keep_idx else n // 2, sample_tokens=S, gw_bits=gw_bits,
                      keep_idx=keep_idx)
     pad = 1024
