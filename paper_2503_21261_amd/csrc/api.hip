@@ -571,19 +571,20 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
     float* const slots2 = (float*)(base + kHeaderBytes + kPartialBytes);
     float* const s_g = (float*)(base + f.gx.sg);
     float* const rowpart = (float*)(base + f.rowpart);
-    bool all = false;
+    OperandsMade made = kOperandsNone;
     int npart = 0;
     if (g_backward_strategy.load() != 3)
       HOT_TRY(launch_operands(w, O, I, c, base + f.gx.qw, f.gx.pitch, (float*)(base + f.gx.scalars), slots, g_y, L,
                               per_token, base + f.gx.qg, s_g, rowpart, &npart, base + f.qgh, f.gw.pitch,
-                              (float*)(base + f.s_gh), slots2, s, kStWGyRow, &all));
-    if (all) {
-      if (!per_token)
-        HOT_STAGE(kStGyRowQuant2, launch_row_quant(g_y, L, O, c.n, c.gx_bits, c.rounding, 2, base + f.gx.qg, f.gx.pitch,
-                                                   s_g, rowpart, &npart, s));
-    } else {
+                              (float*)(base + f.s_gh), slots2, s, kStWGyRow, &made));
+    if (made == kOperandsNone) {
       st = gx_operands(c, g_y, w, L, O, I, gy_quantizer, base, f.gx, s);
       if (st != HOT_OK) return st;
+    } else if (!per_token) {
+      HOT_STAGE(kStGyRowQuant2, launch_row_quant(g_y, L, O, c.n, c.gx_bits, c.rounding, 2, base + f.gx.qg, f.gx.pitch,
+                                                 s_g, rowpart, &npart, s));
+    }
+    if (made != kOperandsAll) {
       st = gw_operand(c, g_y, L, O, base + f.qgh, f.gw.pitch, (float*)(base + f.s_gh), slots, s);
       if (st != HOT_OK) return st;
     }

@@ -156,6 +156,8 @@ hipError_t try_onepass(const ColArgs& a, hipStream_t s, int sq, int round, bool*
 
 // The smallest number of blocks per wave (most workgroups, most loads in flight) whose grid
 // is resident at once; none fits a tensor whose kept values exceed the register files.
+// Odd widths of 16-row blocks take one column per lane (12608 x 3073: 66.7 us in two passes, 44.7
+// in one; the LP_L1 list kept at run time 57.2 for 12608 x 3072, at compile time 36.2).
 // A shape whose lanes hold enough consecutive output bytes to store them directly (no
 // pass through the LDS tile after the exchange, measured 2 us shorter on the ViT-B
 // activations) is preferred while it leaves between 1.25 and 2 workgroups per compute unit, and

@@ -101,8 +101,14 @@ __global__ __launch_bounds__(256, 2) void operands_kernel(const OnepassArgs wa, 
   constexpr int VEC = onepass_vec(N);
   int bid = (int)blockIdx.x;
   if (bid < w_tiles) {
-    if (VEC == 1 || wa.C % VEC != 0) onepass_body<N, 1, kKeepAll4, KB>(wa, bid, w_tiles);
-    else onepass_body<N, VEC, kKeepAll4, KB>(wa, bid, w_tiles);
+    const bool wide = wa.C % VEC == 0;
+    if (ra.bits == 4) {
+      if (wide) onepass_body<N, VEC, kKeepAll4, KB>(wa, bid, w_tiles);
+      else onepass_body<N, 1, kKeepAll4, KB>(wa, bid, w_tiles);
+    } else {
+      if (wide) onepass_body<N, VEC, kKeepAll8, KB>(wa, bid, w_tiles);
+      else onepass_body<N, 1, kKeepAll8, KB>(wa, bid, w_tiles);
+    }
     return;
   }
   bid -= w_tiles;
@@ -129,17 +135,19 @@ struct OperandArgs {
   RowQuantArgs ra;
   int layout;
   int64_t nrb;
+  bool with_g;   // the token-direction view is part of the launch
 };
 
 template <int N, int KB>
-hipError_t try_operands(const OperandArgs& f, hipStream_t s, int stage, bool* done) {
+hipError_t try_operands(const OperandArgs& f, hipStream_t s, int stage, OperandsMade* made) {
   constexpr int VEC = onepass_vec(N);
-  if (*done) return hipSuccess;
+  if (*made) return hipSuccess;
   const int wv = f.wa.C % VEC == 0 ? VEC : 1;
   const int64_t wt = ceil_div(f.wa.C, 64 * wv) * ceil_div(f.wa.rt.nblk, 4 * KB);
-  const int64_t gt = ceil_div(f.ga.C, 64 * VEC) * ceil_div(f.ga.rt.nblk, 4 * KB);
+  const int64_t gt = f.with_g ? ceil_div(f.ga.C, 64 * VEC) * ceil_div(f.ga.rt.nblk, 4 * KB) : 0;
   if (wt > kMaxExchange || gt > kMaxExchange) return hipSuccess;
-  const int bpb = f.ga.r > N / 2 ? f.ga.r : N / 2;   // code bytes per block and column, of either side at most
+  // code bytes per block and column, of either side at most
+  const int bpb_w = f.ra.bits == 4 ? N / 2 : N, bpb = f.with_g && f.ga.r > bpb_w ? f.ga.r : bpb_w;
   size_t lds = (size_t)(64 * VEC) * (4 * KB * bpb + 4);
   if (lds < onepass_stage_bytes<N, VEC, kKeepGeneric>()) lds = onepass_stage_bytes<N, VEC, kKeepGeneric>();
   constexpr size_t lds_max = (size_t)(64 * VEC) * (4 * KB * N + 4);   // never below the staging bytes
@@ -167,16 +175,21 @@ hipError_t try_operands(const OperandArgs& f, hipStream_t s, int stage, bool* do
   stage_begin(stage, s);
   kern<<<dim3((unsigned)(wt + gt + f.nrb)), dim3(256), lds, s>>>(f.wa, (int)wt, f.ga, (int)gt, f.g_kind, f.ra, f.layout);
   stage_end(stage, s);
-  *done = true;
+  *made = f.with_g ? kOperandsAll : kOperandsOfGx;
   return hipGetLastError();
 }
 
 template <int N>
-hipError_t operands_n(const OperandArgs& f, hipStream_t s, int stage, bool* done) {
+hipError_t operands_n(OperandArgs f, bool all, bool of_gx, hipStream_t s, int stage, OperandsMade* made) {
   // one block per wave: the most workgroups, the shortest chain; two where one leaves more than
   // 512 workgroups (the exchange's slots) on a side
-  hipError_t e = try_operands<N, 1>(f, s, stage, done);
-  if (e == hipSuccess) e = try_operands<N, 2>(f, s, stage, done);
+  hipError_t e = hipSuccess;
+  f.with_g = true;
+  if (all) e = try_operands<N, 1>(f, s, stage, made);
+  if (all && e == hipSuccess) e = try_operands<N, 2>(f, s, stage, made);
+  f.with_g = false;
+  if (of_gx && e == hipSuccess) e = try_operands<N, 1>(f, s, stage, made);
+  if (of_gx && e == hipSuccess) e = try_operands<N, 2>(f, s, stage, made);
   return e;
 }
 
@@ -191,10 +204,13 @@ long long wait_ticks(int64_t wait_us, int64_t bytes) {
 hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw, int64_t pitch, float* s_w,
                            float* slots_w, const float* g_y, int64_t L, bool per_token, uint8_t* qg, float* s_g,
                            float* row_partials, int* npartials, uint8_t* qgh, int64_t pitch_h, float* s_gh,
-                           float* slots_g, hipStream_t s, int stage, bool* done) {
-  *done = false;
+                           float* slots_g, hipStream_t s, int stage, OperandsMade* made) {
+  *made = kOperandsNone;
   const int64_t wait_us = exchange_wait_us();
-  if (wait_us < 0 || cfg.gx_bits != 4 || cfg.gw_bits != 8 || O > 4096) return hipSuccess;
+  if (wait_us < 0 || O > 4096) return hipSuccess;
+  // INT4 with a scale per token has w_and_rows_kernel, whose rows keep more waves (INT8, 6304 tokens
+  // 3072 x 768: 118 -> 114 us a layer pass)
+  const bool all = cfg.gw_bits == 8, of_gx = cfg.gx_bits == 8 || !per_token;
   KeepMap id;
   for (int k = 0; k < 64; ++k) id.pos[k] = (int8_t)(k < cfg.n ? k : -1);
   const RowTiling rt = row_tiling(cfg, L);
@@ -214,12 +230,12 @@ hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& c
   });
   if (!per_token && f.nrb > kMaxPartials) f.nrb = kMaxPartials;
   if (f.nrb > (1 << 20)) return hipSuccess;
-  f.ra = RowQuantArgs{g_y, L, (int)O, 4, cfg.rounding, per_token ? 0 : 1, qg, pitch, s_g, row_partials, 0};
+  f.ra = RowQuantArgs{g_y, L, (int)O, cfg.gx_bits, cfg.rounding, per_token ? 0 : 1, qg, pitch, s_g, row_partials, 0};
   *npartials = (int)f.nrb;
   switch (cfg.n) {
-    case 16: return operands_n<16>(f, s, stage, done);
-    case 32: return operands_n<32>(f, s, stage, done);
-    case 64: return operands_n<64>(f, s, stage, done);
+    case 16: return operands_n<16>(f, all, of_gx, s, stage, made);
+    case 32: return operands_n<32>(f, all, of_gx, s, stage, made);
+    case 64: return operands_n<64>(f, all, of_gx, s, stage, made);
   }
   return hipSuccess;
 }

@@ -188,15 +188,17 @@ hipError_t launch_w_and_rows(const float* w, int64_t O, int64_t I, const Config&
                              int64_t pitch, float* s_w, float* slots, const float* g_y, int64_t L,
                              uint8_t* qg, float* s_g, hipStream_t s, int stage, bool* done);
 
-// All three operands of a small layer in one launch (INT4 g_x, INT8 g_w, O up to 4096, both column
-// jobs' workgroups resident at once): those of launch_w_and_rows and the token-direction view of g_y
-// ([O x pitch_h] codes, *s_gh).  With one g_y scale per tensor the rows' part is the abs-max pass only:
+// All three operands of a small layer in one launch (INT8 g_w, O up to 4096, both column jobs'
+// workgroups resident at once): those of launch_w_and_rows and the token-direction view of g_y
+// ([O x pitch_h] codes, *s_gh); or, where that view does not fit or is bfloat16, the first two (`*made` = kOperandsOfGx)
+// unless launch_w_and_rows is made for them.  With one g_y scale per tensor the rows' part is the abs-max pass only:
 // row_partials[0 .. *npartials), for mode 2 of launch_row_quant.  slots_*: kMaxPartials floats each;
-// row_partials: L floats at least.  *done as above.
+// row_partials: L floats at least.
+enum OperandsMade { kOperandsNone = 0, kOperandsOfGx = 1, kOperandsAll = 2 };
 hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw, int64_t pitch, float* s_w,
                            float* slots_w, const float* g_y, int64_t L, bool per_token, uint8_t* qg, float* s_g,
                            float* row_partials, int* npartials, uint8_t* qgh, int64_t pitch_h, float* s_gh,
-                           float* slots_g, hipStream_t s, int stage, bool* done);
+                           float* slots_g, hipStream_t s, int stage, OperandsMade* made);
 
 // One GEMM: C[M x N] = A[M x K] . B[N x K]^T on K-contiguous code rows of k_bytes each
 // (K * bits / 8 rounded up to the pitch alignment).
@@ -221,7 +223,7 @@ struct GemmCall {
 };
 hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage = -1);
 // Both GEMMs of a layer in one launch where all their workgroups are resident at once: `w` with its
-// own plan on 128x128 tiles, `x` (INT4) on unsplit tiles.  *done says whether the launch was made.
+// own plan on 128x128 tiles, `x` on unsplit tiles.  *done says whether the launch was made.
 hipError_t launch_gemm_pair(const GemmCall& w, bool images, const GemmCall& x, hipStream_t s, int stage, bool* done);
 
 // Unpack K-contiguous codes [rows x pitch] into one int8 per code.

@@ -350,17 +350,17 @@ GemmArgs gemm_args(const GemmCall& c) {
 // few K stages and its epilogue, and a launch behind another costs 5 us however little it does:
 // layer passes of 512 tokens 768 x 768 31.2 -> 25.7 us, 3136 x 448 x 1792 56.3 -> 48.4, 3330 x 1008 x
 // 771 70.2 -> 56.3.
-template <int BN, bool BF16, int SPLIT>
+template <int BN, bool INT4, bool BF16, int SPLIT>
 __global__ __launch_bounds__(256, 2) void gemm_pair_kernel(const GemmArgs gw, const GemmArgs gx, const int gw_wgs) {
   if ((int)blockIdx.x < gw_wgs) igemm_body<128, 128, 2, 2, 128, false, BF16, SPLIT>(gw, (int)blockIdx.x);
-  else igemm_body<128, BN, 2, 2, 64, true, false, kWholeK>(gx, (int)blockIdx.x - gw_wgs);
+  else igemm_body<128, BN, 2, 2, INT4 ? 64 : 128, INT4, false, kWholeK>(gx, (int)blockIdx.x - gw_wgs);
 }
 
-template <int BN, bool BF16, int SPLIT>
+template <int BN, bool INT4, bool BF16, int SPLIT>
 hipError_t launch_pair_kernel(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, int gx_wgs, hipStream_t s) {
-  constexpr size_t lds_w = 2 * (128 + 128) * 128, lds_x = 2 * (128 + BN) * 64;
+  constexpr size_t lds_w = 2 * (128 + 128) * 128, lds_x = 2 * (128 + BN) * (INT4 ? 64 : 128);
   constexpr size_t lds = lds_w > lds_x ? lds_w : lds_x;
-  auto kern = gemm_pair_kernel<BN, BF16, SPLIT>;
+  auto kern = gemm_pair_kernel<BN, INT4, BF16, SPLIT>;
   static std::atomic<bool> attr_set{false};
   if (!attr_set.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -371,16 +371,16 @@ hipError_t launch_pair_kernel(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs
   return hipGetLastError();
 }
 
-template <int BN>
+template <int BN, bool INT4>
 hipError_t launch_pair_tile(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, int gx_wgs, int bits, int split, bool images,
                             hipStream_t s) {
   hipError_t e;
   if (bits == 16)
-    e = images ? launch_pair_kernel<BN, true, kImages>(gw, gx, gw_wgs, gx_wgs, s)
-               : launch_pair_kernel<BN, true, kWholeK>(gw, gx, gw_wgs, gx_wgs, s);
-  else if (images) e = launch_pair_kernel<BN, false, kImages>(gw, gx, gw_wgs, gx_wgs, s);
-  else if (split > 1) e = launch_pair_kernel<BN, false, kHandOver>(gw, gx, gw_wgs, gx_wgs, s);
-  else e = launch_pair_kernel<BN, false, kWholeK>(gw, gx, gw_wgs, gx_wgs, s);
+    e = images ? launch_pair_kernel<BN, INT4, true, kImages>(gw, gx, gw_wgs, gx_wgs, s)
+               : launch_pair_kernel<BN, INT4, true, kWholeK>(gw, gx, gw_wgs, gx_wgs, s);
+  else if (images) e = launch_pair_kernel<BN, INT4, false, kImages>(gw, gx, gw_wgs, gx_wgs, s);
+  else if (split > 1) e = launch_pair_kernel<BN, INT4, false, kHandOver>(gw, gx, gw_wgs, gx_wgs, s);
+  else e = launch_pair_kernel<BN, INT4, false, kWholeK>(gw, gx, gw_wgs, gx_wgs, s);
   if (e != hipSuccess || !images) return e;
   const unsigned grid = (unsigned)((int64_t)gw.tiles_m * gw.tiles_n * 64);
   if (bits == 16) combine_images_kernel<true><<<dim3(grid), dim3(256), 0, s>>>(gw);
@@ -392,15 +392,19 @@ hipError_t launch_pair_tile(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, 
 
 hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, hipStream_t s, int stage, bool* done) {
   *done = false;
-  if (g_gemm_mode.load() != 0 || cx.bits != 4 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
+  if (g_gemm_mode.load() != 0 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
   const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images);
   if (p.bm != 128 || p.bn != 128) return hipSuccess;
   const int64_t w = p.tiles * p.split, cap = 2 * (int64_t)compute_units();
+  const int64_t most = 2 * cap;
   // Two workgroups per unit are resident (LDS of the g_w tile, registers); 128x128 g_x tiles while
-  // they fit beside the g_w workgroups, else half as many of 128x256.
+  // they fit beside the g_w workgroups, else (INT4) half as many of 128x256,
+  // which pay up to twice the resident count: the g_x tiles start where g_w slices end, no launch
+  // and no drained chip between them (12608 tokens 3072 x 768, 432 + 297 workgroups: 155 -> 141 us a layer
+  // pass; with 594 tiles of 128x128 instead 151).
   const int64_t rows = ceil_div(cx.M, 128), x128 = rows * ceil_div(cx.N, 128), x256 = rows * ceil_div(cx.N, 256);
-  if (w + x256 > cap) return hipSuccess;
-  const bool narrow = w + x128 <= cap;
+  const bool int4 = cx.bits == 4, narrow = w + x128 <= cap;
+  if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
   GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
@@ -413,13 +417,14 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
     const hipError_t e = prepare_hand_over<128>(gw, cw.k_bytes, false);
     if (e != hipSuccess) return e;
   }
-  gx.nk_total = (int)(cx.k_bytes / 64);
+  gx.nk_total = (int)(cx.k_bytes / (int4 ? 64 : 128));
   gx.tiles_m = (int)rows;
   gx.tiles_n = (int)ceil_div(cx.N, narrow ? 128 : 256);
   gx.split = 1;
   stage_begin(stage, s);
-  const hipError_t e = narrow ? launch_pair_tile<128>(gw, gx, (int)w, (int)x128, cw.bits, p.split, p.images, s)
-                              : launch_pair_tile<256>(gw, gx, (int)w, (int)x256, cw.bits, p.split, p.images, s);
+  const hipError_t e = !narrow ? launch_pair_tile<256, true>(gw, gx, (int)w, (int)x256, cw.bits, p.split, p.images, s)
+                       : int4  ? launch_pair_tile<128, true>(gw, gx, (int)w, (int)x128, cw.bits, p.split, p.images, s)
+                               : launch_pair_tile<128, false>(gw, gx, (int)w, (int)x128, cw.bits, p.split, p.images, s);
   stage_end(stage, s);
   *done = true;
   return e;

@@ -1033,19 +1033,21 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     (2048, 128, 130, 32, 0, 8, None),       # g_w images added by a second kernel
     (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
     (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
+    (8208, 2304, 768, 16, 0, 8, None),      # more workgroups than are resident at once
+    (16400, 4096, 100, 16, 0, 8, None),     # the token-direction view in a launch of its own
     (2048, 256, 130, 32, 0, 8, "lp_l1"),    # the compile-time LP_L1 list
     (1040, 128, 96, 16, 0, 8, "lp_l1"),
     (16, 16, 1, 16, 0, 8, None)])           # one workgroup each
-@pytest.mark.parametrize("wait_us", [200, 0])
-def test_small_layers_in_few_launches_and_apart(gemm_mode, L, O, I, n, S, gw_bits, keep_idx, wait_us):
+@pytest.mark.parametrize("gx_bits,wait_us", [(4, 200), (4, 0), (8, 200), (8, 0)])
+def test_small_layers_in_few_launches_and_apart(gemm_mode, L, O, I, n, S, gw_bits, keep_idx, gx_bits, wait_us):
     """Small layers have their operands made in one launch and both GEMMs run in another; strategy 3
     gives every kernel its own.  The same bits, and nothing written outside the outputs."""
     hot = _hot()
     x, w, gy = make(L, O, I, seed=79)
     if keep_idx == "lp_l1":
         keep_idx = hot.hot_lowpass_l1_rows(n, n // 2)
-    cfg = hot.Config(block=n, keep=len(keep_idx) if keep_idx else n // 2, sample_tokens=S, gw_bits=gw_bits,
-                     keep_idx=keep_idx)
+    cfg = hot.Config(block=n, keep=len(keep_idx) if keep_idx else n // 2, sample_tokens=S, gx_bits=gx_bits,
+                     gw_bits=gw_bits, keep_idx=keep_idx)
     pad = 1024
     xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
     act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
