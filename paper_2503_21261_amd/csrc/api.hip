@@ -350,6 +350,17 @@ hipError_t gemm(const GemmCall& g, hipStream_t s, int stage = -1, bool images = 
   return launch_igemm(g, plan_gemm(g.M, g.N, g.k_bytes, g.bits, true, images), s, stage);
 }
 
+// Both GEMMs of a layer, in one launch where that pays (they share the scratch: only one of them
+// then splits K).
+hot_status both_gemms(const GemmCall& gx, const GemmCall& gw, bool images, hipStream_t s) {
+  bool both = false;
+  if (g_backward_strategy.load() != 3) HOT_TRY(launch_gemm_pair(gw, images, gx, s, kStGemmPair, &both));
+  if (both) return HOT_OK;
+  HOT_TRY(gemm(gx, s, kStGxGemm));
+  HOT_TRY(gemm(gw, s, kStGwGemm, images));
+  return HOT_OK;
+}
+
 // g_x path, first half: the rotated, quantised g_y operand (codes at g.qg, scales at g.sg).
 hot_status gx_rows(const Config& c, const float* g_y, int64_t L, int64_t O, hot_quantizer gy_quantizer,
                    uint8_t* base, const GxLayout& g, hipStream_t s) {
@@ -593,12 +604,7 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
                                   (const float*)(base + f.gx.scalars));
     const GemmCall gw = gemm_call(c, base + f.qgh, (const uint8_t*)act_buf + a.codes, O, I, f.gw.pitch, c.gw_bits, base,
                                   f.partial, nullptr, g_w, (const float*)(base + f.s_gh), 0, (const float*)act_buf);
-    bool both = false;
-    if (g_backward_strategy.load() != 3) HOT_TRY(launch_gemm_pair(gw, images, gx, s, kStGemmPair, &both));
-    if (both) return HOT_OK;
-    HOT_TRY(gemm(gx, s, kStGxGemm));
-    HOT_TRY(gemm(gw, s, kStGwGemm, images));
-    return HOT_OK;
+    return both_gemms(gx, gw, images, s);
   }
   float* s_w = (float*)(base + f.gx.scalars);
   float* s_gh = (float*)(base + f.s_gh);
@@ -615,11 +621,10 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
                            part_a, s, kStWAbsmax, kStWQuant));
   HOT_TRY(launch_gy_fused(g_y, L, O, c, per_token, qg, f.gx.pitch, s_g, qgh, f.gw.pitch, s_gh, part_a,
                           part_b, (float*)(base + f.rowpart), s, kStGyFusedAbsmax, kStGyFusedQuant));
-  HOT_TRY(gemm(gemm_call(c, qg, qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr, g_x, s_g,
-                         per_token ? 1 : 0, s_w), s, kStGxGemm));
-  HOT_TRY(gemm(gemm_call(c, qgh, abase + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial, nullptr, g_w, s_gh,
-                         0, (const float*)abase), s, kStGwGemm, images));
-  return HOT_OK;
+  return both_gemms(gemm_call(c, qg, qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr, g_x, s_g,
+                                 per_token ? 1 : 0, s_w),
+                    gemm_call(c, qgh, abase + a.codes, O, I, f.gw.pitch, c.gw_bits, base, f.partial, nullptr, g_w, s_gh,
+                              0, (const float*)abase), images, s);
 }
 
 hot_status hot_select_quantizer(const hot_config* cfg, const float* g_y, int64_t L, int64_t O,

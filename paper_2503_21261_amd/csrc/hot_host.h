@@ -222,7 +222,7 @@ struct GemmCall {
   const unsigned long long* epoch;
 };
 hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage = -1);
-// Both GEMMs of a layer in one launch where all their workgroups are resident at once: `w` with its
+// Both GEMMs of a layer in one launch, up to a few thousand workgroups together: `w` with its
 // own plan on 128x128 tiles, `x` on unsplit tiles.  *done says whether the launch was made.
 hipError_t launch_gemm_pair(const GemmCall& w, bool images, const GemmCall& x, hipStream_t s, int stage, bool* done);
 

@@ -396,14 +396,16 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images);
   if (p.bm != 128 || p.bn != 128) return hipSuccess;
   const int64_t w = p.tiles * p.split, cap = 2 * (int64_t)compute_units();
-  const int64_t most = 2 * cap;
-  // Two workgroups per unit are resident (LDS of the g_w tile, registers); 128x128 g_x tiles while
-  // they fit beside the g_w workgroups, else (INT4) half as many of 128x256,
-  // which pay up to twice the resident count: the g_x tiles start where g_w slices end, no launch
-  // and no drained chip between them (12608 tokens 3072 x 768, 432 + 297 workgroups: 155 -> 141 us a layer
-  // pass; with 594 tiles of 128x128 instead 151).
+  const int64_t most = 8 * cap;
+  // Two workgroups per unit are resident (LDS of the g_w tile, registers).  While all are: 128x128
+  // g_x tiles, the most workgroups.  Beyond that 128x256 (INT4): the g_x tiles start where g_w
+  // slices end, no launch and no drained chip between them (12608 tokens 3072 x 768, 432 + 297
+  // workgroups: 155 -> 141 us a layer pass; with 594 tiles of 128x128 151).  Backward calls apart and
+  // together: 8192 tokens 1024 x 4096 114 -> 94 us, 50432 x 768 x 768 145 -> 128, 25216 x 768 x 3072 173 ->
+  // 156, 50432 x 768 x 3072 (2364 + 432 workgroups) 307 -> 302, INT8 12608 x 768 x 3072 117 -> 105; the
+  // gain is one tail and one launch, nothing measurable beyond a few thousand workgroups.
   const int64_t rows = ceil_div(cx.M, 128), x128 = rows * ceil_div(cx.N, 128), x256 = rows * ceil_div(cx.N, 256);
-  const bool int4 = cx.bits == 4, narrow = w + x128 <= cap;
+  const bool int4 = cx.bits == 4, narrow = w + x128 <= (int4 ? cap : most);
   if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
   GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
   gw.nk_total = (int)(cw.k_bytes / 128);

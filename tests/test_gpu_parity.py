@@ -1034,6 +1034,7 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
     (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
     (8208, 2304, 768, 16, 0, 8, None),      # more workgroups than are resident at once
+    (33024, 768, 768, 16, 0, 8, None),      # behind the shared g_y passes
     (16400, 4096, 100, 16, 0, 8, None),     # the token-direction view in a launch of its own
     (2048, 256, 130, 32, 0, 8, "lp_l1"),    # the compile-time LP_L1 list
     (1040, 128, 96, 16, 0, 8, "lp_l1"),
