@@ -46,12 +46,24 @@ def _labels(names, bench_json):
     P = len(seq)
     if P == 0 or len(names) < 2 * P:
         return None
-    # the periodic tail: the longest suffix with names[i] == names[i + P], cut to whole steps
-    start = len(names) - P
-    while start > 0 and names[start - 1] == names[start - 1 + P]:
+    # a g_w GEMM whose K slices are added by a second kernel is one entry of the sequence
+    main = [i for i, name in enumerate(names) if not name.startswith("combine_images")]
+    seen = [names[i] for i in main]
+    if len(seen) < 2 * P:
+        return None
+    # the periodic tail: the longest suffix with seen[i] == seen[i + P], cut to whole steps
+    start = len(seen) - P
+    while start > 0 and seen[start - 1] == seen[start - 1 + P]:
         start -= 1
-    start += (len(names) - start) % P
-    return [None if i < start else seq[(i - start) % P] for i in range(len(names))]
+    start += (len(seen) - start) % P
+    labels = [None] * len(names)
+    for at, i in enumerate(main):
+        if at >= start:
+            labels[i] = seq[(at - start) % P]
+    for i, name in enumerate(names):
+        if name.startswith("combine_images") and i > 0:
+            labels[i] = labels[i - 1]
+    return labels
 
 
 def _group(rows, names, value, bench_json):
