@@ -401,9 +401,9 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   // g_x tiles, the most workgroups.  Beyond that 128x256 (INT4): the g_x tiles start where g_w
   // slices end, no launch and no drained chip between them (12608 tokens 3072 x 768, 432 + 297
   // workgroups: 155 -> 141 us a layer pass; with 594 tiles of 128x128 151).  Backward calls apart and
-  // together: 8192 tokens 1024 x 4096 114 -> 94 us, 50432 x 768 x 768 145 -> 128, 25216 x 768 x 3072 173 ->
-  // 156, 50432 x 768 x 3072 (2364 + 432 workgroups) 307 -> 302, INT8 12608 x 768 x 3072 117 -> 105; the
-  // gain is one tail and one launch, nothing measurable beyond a few thousand workgroups.
+  // together: 8192 tokens 1024 x 4096 114 -> 94 us, 50432 x 768 x 768 145 -> 128, INT8 12608 x 768 x 3072
+  // 117 -> 105, 25216 x 768 x 3072 (2796 workgroups) 173 -> 156.  The gain is one tail and one launch;
+  // sizes above the line, where the g_x GEMM's own choice of tile matters more, were not timed.
   const int64_t rows = ceil_div(cx.M, 128), x128 = rows * ceil_div(cx.N, 128), x256 = rows * ceil_div(cx.N, 256);
   const bool int4 = cx.bits == 4, narrow = w + x128 <= (int4 ? cap : most);
   if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
