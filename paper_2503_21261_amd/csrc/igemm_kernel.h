@@ -351,7 +351,9 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
   // column lane%32, so each register is stored as 32-float (128-byte) row segments.
   // The row factors come from LDS (filled before the main loop): a global load per row
   // here could not be hoisted above the output stores and would serialise on L2 latency.
-  // Offsets within the tile are 32-bit on top of a uniform base pointer.
+  // The first two forms add a 32-bit byte offset of the lane (at most four rows and the tile's
+  // columns: 16 N + 4 BN) to a uniform 64-bit address, the second under a 2^31-byte descriptor:
+  // both hold up to N = 2^26.  Wider outputs, and the raw accumulators, take the third.
   auto epilogue = [&]() {
     // Split-K runs this after loops: an opaque copy of the lane index keeps the compiler
     // from hoisting the ~100 output addresses out of them (they would be live, in
@@ -360,13 +362,15 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
     if constexpr (SPLIT == kHandOver) asm volatile("" : "+v"(ln));
     const int lane = ln;
     const int nl0 = wn0 + (lane & 31);
-    if (g.out_f32 && m0 + BM <= g.M && n0 + BN <= g.N) {
+    const int wrow = m0 + __builtin_amdgcn_readfirstlane(wm0);   // first row of the wave's part
+    const bool offsets_fit = g.out_f32 && g.N <= 1 << 26;
+    if (offsets_fit && m0 + BM <= g.M && n0 + BN <= g.N) {
       // A tile that lies inside the output (all but the last tile row and column): no bound
       // checks, and one address per lane for the whole tile: the row within the tile is a
       // uniform offset on the base pointer, the column block a constant (3 us per 256x256
       // tile; a checked form with two branches per element took 13).
-      const unsigned lane_byte = 4u * (unsigned)((wm0 + 4 * (lane >> 5)) * g.N + nl0);   // < 2^32: inside one tile
-      char* const tile = reinterpret_cast<char*>(g.out_f32 + ((int64_t)m0 * g.N + n0));
+      const unsigned lane_byte = 4u * (unsigned)(4 * (lane >> 5) * g.N + nl0);
+      char* const tile = reinterpret_cast<char*>(g.out_f32 + ((int64_t)wrow * g.N + n0));
       auto store_tile = [&](auto nt_c) {
         constexpr bool NT = decltype(nt_c)::value;
 #pragma unroll
@@ -406,15 +410,14 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
       // bands of tiles); with a long K per tile they measured slower than plain stores.
       if (g.stream_out) store_tile(std::true_type{});
       else store_tile(std::false_type{});
-    } else if (g.out_f32) {
+    } else if (offsets_fit) {
       // The last tile row and column: buffer stores, whose hardware drops what lies past the
       // descriptor's end: no compare or branch per element, and the row is in the (scalar) base.
       // A descriptor ends with the output; columns past it start at half the range, which no
-      // descriptor reaches (16 N bytes stay below it: N < 2^27).  Passes of a layer, against a compare and a
+      // descriptor reaches and no lane's valid offset either.  Passes of a layer, against a compare and a
       // branch per element: 3136 tokens 448 x 1792 59.7 -> 56.3 us, 197 tokens 768 x 768
       // 32.4 -> 31.3, 12608 tokens 3072 x 768 164 -> 161.
       constexpr unsigned kEnd = 0x80000000u;
-      const int wrow = m0 + __builtin_amdgcn_readfirstlane(wm0);
       unsigned col_byte[TN];
 #pragma unroll
       for (int j = 0; j < TN; ++j)
@@ -441,20 +444,24 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
       if (g.stream_out) store_tile(std::true_type{});
       else store_tile(std::false_type{});
     } else {
-      int32_t* obase = g.out_i32 + ((int64_t)m0 * g.N + n0);
+      const bool raw = !g.out_f32;
+      int32_t* const obase = raw ? g.out_i32 : reinterpret_cast<int32_t*>(g.out_f32);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int ml = wm0 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
           if (m0 + ml >= g.M) continue;
-          const int row_off = ml * g.N + nl0;
+          const int64_t row_off = (int64_t)(m0 + ml) * g.N + n0 + nl0;
+          const float rs = s_rowfac[ml];   // not filled, and not used, for the raw accumulators
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            if (n0 + nl0 + j * 32 < g.N) {
-              if constexpr (BF16) obase[row_off + j * 32] = __float_as_int(acc[i][j][v]);
-              else obase[row_off + j * 32] = INT4 ? (acc[i][j][v] >> 8) : acc[i][j][v];
-            }
+          for (int j = 0; j < TN; ++j) {
+            int32_t bits;
+            if constexpr (BF16) bits = __float_as_int(acc[i][j][v]);
+            else bits = INT4 ? (acc[i][j][v] >> 8) : acc[i][j][v];
+            const int32_t scaled = __float_as_int((float)acc[i][j][v] * rs);
+            if (n0 + nl0 + j * 32 < g.N) obase[row_off + j * 32] = raw ? bits : scaled;
+          }
         }
       }
     }

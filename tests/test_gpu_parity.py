@@ -953,6 +953,35 @@ def test_edge_tiles_end_with_the_output(gemm_mode, mode, L, I):
     assert bool((room[:pad] == -7.0).all()) and bool((room[pad + L * I:] == -7.0).all())
 
 
+@pytest.mark.parametrize("L,I", [(259, 6_000_007), (20, 1 << 26), (20, (1 << 27) + 5)])
+def test_very_wide_outputs(L, I):
+    """Outputs whose rows are 24 MB and more: a row's byte offset within a tile passes 32 bits from
+    5.5 million columns on, half of it 31 bits from 2^27 on.  Every element against the first row
+    (the tokens are multiples of one another by powers of two, which change neither codes nor
+    roundings), that row against the oracle at both ends, around the powers of two and in between."""
+    hot = _hot()
+    n, O = 16, 16
+    _say(f"[wide] L={L} I={I}")
+    base = hot_inputs.normal((O,), 1e-3, 5, "wide")
+    power = torch.arange(L) % 40
+    gy = torch.ldexp(base[None, :].expand(L, O), power[:, None]).contiguous()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    w = torch.randn((O, I), generator=gen, device="cuda").mul_(0.02)
+    picks = sorted({c for p in (0, 1 << 22, I // 3, 1 << 26, 1 << 27, I) for c in range(p - 70, p + 70) if 0 <= c < I})
+    w[3, picks[5]] = 1.5   # the abs-max of the rotated weights lies in the picked columns
+    cfg = hot.Config(block=n, keep=8)
+    ws = hot.alloc_workspace(cfg, L, O, I)
+    gx = torch.full((L, I), float("nan"), device="cuda")
+    hot.hot_linear_backward_gx(cfg, gy.cuda(), w, hot.HOT_Q_PER_TOKEN, gx, ws)
+    torch.cuda.synchronize()
+    ref = oracle.backward_gx(gy[:1].numpy(), w[:, picks].cpu().numpy(), n)
+    assert np.array_equal(gx[:1, picks].cpu().numpy(), dequant_fp32(ref["acc"], ref["sg"], ref["sw"][0], n))
+    assert bool(torch.isfinite(gx[0]).all())
+    for row in range(1, L):
+        assert torch.equal(gx[row], gx[0] * 2.0 ** int(power[row])), f"row {row}"
+
+
 @pytest.mark.parametrize("mode,wait_us", [(3, 200), (4, 0)])
 def test_config2_split_k(gemm_mode, mode, wait_us):
     hot = _hot()
