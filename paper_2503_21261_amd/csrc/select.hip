@@ -44,6 +44,21 @@ __device__ __forceinline__ double add_sq_err4(double sum, const float4& t, float
   return sum;
 }
 
+// The same under a scale whose inverse is infinite (abs-max below qmax / FLT_MAX, 2e-38 for INT4): the
+// quantiser's product is infinite, or, for a zero, a NaN that its conversion to an integer makes 0.
+// Rare; the opaque copies keep the usual case's registers free of what the compiler would share.
+__device__ __forceinline__ double add_saturated_sq_err4(double sum, const float4& t, float inv, double scale, float qmax) {
+  float e[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    asm volatile("" : "+v"(e[i]));
+    const float q = e[i] == 0.0f ? 0.0f : copysignf(qmax, e[i] * inv);
+    const double d = fma(-(double)q, scale, (double)e[i]);
+    sum = fma(d, d, sum);
+  }
+  return sum;
+}
+
 struct SelectArgs {
   const float* t;
   int64_t rows;
@@ -103,7 +118,10 @@ __global__ __launch_bounds__(256) void select_rows_kernel(const SelectArgs a) {
     }
     const float inv = flip_sign(quant_inv(amax, qmax), lane.flip);
     const double scale = (double)flip_sign(quant_scale(amax, qmax), lane.flip);
-    if (a.rounding == 0) {   // elements past the row's end are zeros with zero error
+    if (isinf(inv)) {   // elements past the row's end are zeros with zero error, here as below
+#pragma unroll
+      for (int it = 0; it < ITER; ++it) sum = add_saturated_sq_err4(sum, v[it], inv, scale, (float)qmax);
+    } else if (a.rounding == 0) {
 #pragma unroll
       for (int it = 0; it < ITER; ++it) sum = add_sq_err4<0>(sum, v[it], inv, scale, (float)qmax);
     } else {
@@ -140,6 +158,11 @@ __global__ __launch_bounds__(256) void select_stream_kernel(const SelectArgs a) 
     }
     const float inv = flip_sign(quant_inv(amax, qmax), lane.flip);
     const double scale = (double)flip_sign(quant_scale(amax, qmax), lane.flip);
+    if (isinf(inv)) {
+      for (int base = 0; base < nvec; base += 256)
+        sum = add_saturated_sq_err4(sum, transformed(base), inv, scale, (float)qmax);
+      continue;
+    }
     for (int base = 0; base < nvec; base += 256) {
       const float4 q = transformed(base);
       sum = a.rounding == 0 ? add_sq_err4<0>(sum, q, inv, scale, (float)qmax)

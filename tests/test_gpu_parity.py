@@ -308,6 +308,29 @@ def test_select_quantizer_zero_gradient():
     assert (choice, m_tok, m_ten) == (hot.HOT_Q_PER_TENSOR, 0.0, 0.0)
 
 
+@pytest.mark.parametrize("O,bits,rounding", [(48, 4, 1), (48, 8, 0), (1040, 4, 0), (16448, 4, 1)])
+def test_select_quantizer_scale_without_a_finite_inverse(O, bits, rounding):
+    """A gradient so small that qmax / abs-max overflows: zeros keep code 0 (and no error), every other
+    element saturates.  Rows on few threads, on a wave, and streamed; blocks of zeros, and zeros that the
+    rotation makes."""
+    hot = _hot()
+    n, L, qmax = 16, 5, (1 << (bits - 1)) - 1
+    gy = torch.zeros(L, O)
+    gy[:, 0] = torch.arange(1, L + 1) * 2.0 ** -140
+    gy[:, 1] = gy[:, 0]                 # rotated: twice the value or zero
+    gy[2, 32:48] = -3 * 2.0 ** -140     # rotated: one element and fifteen zeros
+    _say(f"[select] tiny scale O={O} bits={bits} rounding={rounding}")
+    cfg = hot.Config(block=n, keep=8, gx_bits=bits, rounding=rounding)
+    choice, m_tok, m_ten = hot.hot_select_quantizer(cfg, gy.cuda(), hot.alloc_workspace(cfg, L, O, 16))
+    t = oracle.transform_rows(gy.numpy(), n).astype(np.float64)
+    want = []
+    for amax in (np.abs(t).max(1, keepdims=True), np.abs(t).max()):
+        scale = np.float64(np.float32(amax) / np.float32(qmax))
+        want.append(np.square(t - np.sign(t) * qmax * scale).sum() / (n * L * O))
+    np.testing.assert_allclose([m_tok, m_ten], want, rtol=1e-10)
+    assert want[0] < want[1] and choice == int(want[1] - want[0] >= cfg.lqs_threshold * want[1])
+
+
 def test_calls_are_repeatable_and_stream_ordered():
     """Same inputs, same workspace, non-default stream: identical bits every time."""
     hot = _hot()
