@@ -177,7 +177,8 @@ hot_status hot_linear_backward_gx_cached(const hot_config* cfg, const float* g_y
  * With gw_bits = 16 (g_w is the gradient Sec. 4.2 finds sensitive to quantisation) the two
  * low-rank operands are rounded to bfloat16 instead (nearest even, no scales; the
  * activation buffer is then 25 % of fp32), multiplied on the bf16 matrix cores with fp32
- * accumulation and divided by n; no limit on L*r/n.
+ * accumulation and divided by n; no limit on L*r/n.  The sums of a long reduction are made in
+ * slices that follow from the shape alone, so that g_w has the same bits in every call.
  * g_y: device [L x O] (in); act_buf: what hot_compress_activation wrote for the
  * same cfg, L, I (in); g_w: device [O x I] (out).  Requires L % n == 0.
  */
@@ -286,8 +287,9 @@ hot_status hot_debug_set_exchange_wait_us(int us);
  * 128x128 tile applies (integer operands, at least 4 K stages per slice); the slices'
  * partial sums are handed to the last one through the workspace; 10 / 11 / 12 / 13: every
  * GEMM on 128x128 / 192x256 / 256x256 / 128x256 tiles, one workgroup per tile (11 and 13
- * exist for INT4 operands only; INT8 and bfloat16 GEMMs then take 256x256).  Integer results, and therefore all outputs, do not depend on it.
- * Process-wide. */
+ * exist for INT4 operands only; INT8 and bfloat16 GEMMs then take 256x256).  Integer results, and
+ * therefore all outputs, do not depend on it; a bfloat16 GEMM whose sums are made in slices keeps
+ * them, and the 128x128 tile, in every mode.  Process-wide. */
 hot_status hot_debug_set_gemm_mode(int mode);
 
 /* ---- stage timing for benchmarks (off by default) ---- */

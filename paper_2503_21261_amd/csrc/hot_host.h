@@ -63,7 +63,7 @@ constexpr int64_t kMaxK4 = 171196;   // 256 * 7^2 * K < 2^31
 // Tile shape and K split of one GEMM launch.
 struct GemmPlan {
   int bm, bn, bkb;
-  int split;              // workgroups (K slices) per output tile
+  int split;              // K slices; a workgroup per slice and output tile, but for bfloat16 without `images`
   int64_t tiles;
   bool images;            // the slices' sums are added by a second kernel
   size_t partial_bytes;   // split > 1: tiles * (split - 1, or split with `images`) * bm * bn int32

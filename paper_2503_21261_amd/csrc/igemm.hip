@@ -154,6 +154,20 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
   }
   p.bkb = bits == 4 ? 64 : 128;
   const int mode = g_gemm_mode.load();
+  // fp32 sums: the slices of a bfloat16 GEMM follow from its shape alone, whatever the scratch and
+  // the mode, so that its bits do too; without images one workgroup sums them in their order
+  if (bits == 16) images = images && mode == 0;
+  if ((images && mode == 0) || bits == 16) {
+    const int64_t s = image_slices(M, N, k_bytes, bits, cus);
+    if (s) {
+      p.bm = p.bn = 128;
+      p.tiles = ceil_div(M, 128) * ceil_div(N, 128);
+      p.split = (int)s;
+      p.images = images;
+      if (images) p.partial_bytes = image_scratch_bytes(M, N, k_bytes, bits);
+      return p;
+    }
+  }
   if (mode >= 10) {   // a tile forced for measurement: 10 = 128x128, 11 = 192x256 (INT4 only), 12 = 256x256
     const int bm = mode == 10 ? 128 : (mode == 11 && bits == 4 ? 192 : 256);
     p.bm = bm;
@@ -161,17 +175,6 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
     if (mode == 13 && bits == 4) { p.bm = 128; p.bn = 256; }
     p.tiles = ceil_div(M, p.bm) * ceil_div(N, p.bn);
     return p;
-  }
-  if (images && mode == 0) {
-    const int64_t s = image_slices(M, N, k_bytes, bits, cus);
-    if (s) {
-      p.bm = p.bn = 128;
-      p.tiles = ceil_div(M, 128) * ceil_div(N, 128);
-      p.split = (int)s;
-      p.images = true;
-      p.partial_bytes = image_scratch_bytes(M, N, k_bytes, bits);
-      return p;
-    }
   }
   if (scratch && mode == 0) {
     const int64_t s = large_tile_split(M, N, k_bytes, bits, cus);
@@ -310,7 +313,9 @@ hipError_t launch_tile(GemmArgs g, int64_t k_bytes, const GemmPlan& plan, hipStr
     }
   }
   if (plan.images) return hipErrorInvalidValue;
-  if constexpr (BF16 || BM == 192 || BM != BN || (INT4 && BM != 128)) {
+  if constexpr (BF16 && BM == 128) {
+    return launch_kernel<BM, BN, BKB, INT4, BF16, kSliceSums>(g, (unsigned)tiles, s, gemm_stage);
+  } else if constexpr (BF16 || BM == 192 || BM != BN || (INT4 && BM != 128)) {
     return hipErrorInvalidValue;   // splits exist for the 128x128 tiles and the 256x256 INT8 tile
   } else {
     const hipError_t e = prepare_hand_over<BM>(g, k_bytes, INT4);
@@ -395,6 +400,7 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   if (g_gemm_mode.load() != 0 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
   const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images);
   if (p.bm != 128 || p.bn != 128) return hipSuccess;
+  if (cw.bits == 16 && p.split > 1 && !p.images) return hipSuccess;
   const int64_t w = p.tiles * p.split, cap = 2 * (int64_t)compute_units();
   const int64_t most = 8 * cap;
   // Two workgroups per unit are resident (LDS of the g_w tile, registers).  While all are: 128x128

@@ -74,6 +74,7 @@ enum KSplit {
   kWholeK = 0,     // one workgroup per tile
   kHandOver = 1,   // one workgroup per (slice, tile); the last slice's collects the others' sums
   kImages = 2,     // one workgroup per (slice, tile); all leave their sums to combine_images_kernel
+  kSliceSums = 3,  // one workgroup per tile, slice after slice: the sums of kImages in its order
 };
 
 // Workgroup id -> output tile.  Workgroups are dealt round-robin to the 8 XCDs, each
@@ -134,6 +135,10 @@ struct Operands {            // what the matrix instructions of one K slice cons
 // split + slice) and combine_images_kernel, launched behind, adds them in slice order.  An owner
 // collects images one after the other, 2-3 us each, which many slices cannot afford; and the
 // fp32 sums of the bfloat16 operands must not depend on which workgroup added a piece.
+// SPLIT = kSliceSums: the bfloat16 GEMM where kImages has no room for its images, with its bits: a
+// slice's products are summed from zero and the slices' sums added in order, by the tile's own
+// workgroup (a second set of accumulators; 768 x 768 outputs over 6304 reduced tokens take 62 us
+// this way, 25 in images).
 // Waves per SIMD the register allocation must leave room for: two for the 128x256 INT4 tile
 // (its workgroups come in pairs per compute unit so that one's output stores run under the
 // other's matrix instructions), whatever fits otherwise.
@@ -146,6 +151,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int BKB, bool INT4, bool BF1
 __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
   static_assert(!(INT4 && BF16), "one operand format");
   static_assert(!(SPLIT == kHandOver && BF16), "fp32 sums would depend on which workgroup added a piece");
+  static_assert(SPLIT != kSliceSums || BF16, "integer sums have one value in any order");
   using acc_t = std::conditional_t<BF16, v16f, v16i>;
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -467,18 +473,42 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
     }
   };
 
+  const int nk = g.nk_total, S = g.split;
+  auto slice_begin = [&](int zz) { return (int)(((int64_t)zz * nk) / S); };
   if constexpr (SPLIT == kWholeK) {
     int tm, tn;
     tile_of_position(g, xcd_contiguous(bid, g.tiles_m * g.tiles_n), tm, tn);
     set_tile(tm, tn);
     fill_rowfac();
     zero_acc();
-    main_loop(0, g.nk_total);   // has a barrier when there is any stage; else acc = 0 ...
-    if (g.nk_total <= 0) __syncthreads();   // ... and the row factors still need one
+    main_loop(0, nk);   // has a barrier when there is any stage; else acc = 0 ...
+    if (nk <= 0) __syncthreads();   // ... and the row factors still need one
+    epilogue();
+  } else if constexpr (SPLIT == kSliceSums) {
+    int tm, tn;
+    tile_of_position(g, xcd_contiguous(bid, g.tiles_m * g.tiles_n), tm, tn);
+    set_tile(tm, tn);
+    fill_rowfac();
+    acc_t sum[TM][TN] = {};
+    for (int z = 0; z < S; ++z) {
+      zero_acc();
+      main_loop(slice_begin(z), slice_begin(z + 1));
+      __syncthreads();   // LDS is free for the next slice, the row factors are there
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sum[i][j][v] += acc[i][j][v];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = sum[i][j];
     epilogue();
   } else {
     constexpr int IMG = BM * BN;
-    const int tiles = g.tiles_m * g.tiles_n, nk = g.nk_total, S = g.split;
+    const int tiles = g.tiles_m * g.tiles_n;
     int z = bid / tiles;   // slices in dispatch order: owners (z = S - 1) start last
     int tm, tn, t;
     if (SPLIT == kImages && g.xcd_cols == -2) {
@@ -512,7 +542,6 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
       t = xcd_contiguous(bid - z * tiles, tiles);
       tile_of_position(g, t, tm, tn);
     }
-    auto slice_begin = [&](int zz) { return (int)(((int64_t)zz * nk) / S); };
     if constexpr (SPLIT == kImages) {
       set_tile(tm, tn);
       zero_acc();

@@ -1250,6 +1250,47 @@ def test_gw_bf16_small_shapes(case):
     check_gw_bf16(hot, hot.Config(block=n, keep=r, keep_idx=keep_idx, gw_bits=16), gy, x, "bf16 small")
 
 
+@pytest.mark.parametrize("L,O,I", [(2560, 144, 132), (8208, 64, 200), (4096, 528, 1000)])
+def test_gw_bf16_bits_follow_from_the_shape_alone(gemm_mode, L, O, I):
+    """K in slices: fp32 sums depend on where the cuts are, so these must not depend on the room in
+    the workspace, the call, or the work distribution.  The same bits from both calls, with room
+    for the slices' images and without, in every mode, and from the accumulators recomputed."""
+    hot = _hot()
+    x, w, gy = make(L, O, I, seed=76)
+    cfg = hot.Config(block=16, keep=8, gw_bits=16)
+    xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, xd, act, ws)
+    least = hot.HOT_WS_PREFIX_BYTES + -(-O * ((L + 127) // 128 * 128) // 256) * 256   # operand rows, no images
+    outs, names = [], []
+
+    def both(name, space):
+        gx, gw = torch.empty((L, I), device="cuda"), torch.zeros((O, I), device="cuda")
+        hot.hot_linear_backward(cfg, gyd, wd, act, hot.HOT_Q_PER_TOKEN, gx, gw, space)
+        outs.append(gw)
+        names.append(name)
+
+    def gw_alone(name, space):
+        outs.append(hot.hot_linear_backward_gw(cfg, gyd, act, I, torch.zeros((O, I), device="cuda"), space))
+        names.append(name)
+
+    gw_alone("g_w", ws)
+    acc = hot.hot_debug_gw_operands(cfg, ws, act, L, O, I)["acc"]
+    outs.append(acc * (1.0 / 16))
+    names.append("recomputed accumulators")
+    gw_alone("g_w, one byte short of the largest call's workspace", ws[:-1])
+    gw_alone("g_w, no room for images", ws[:least])
+    both("both", ws)
+    both("both, one byte short", ws[:-1])
+    for mode in (1, 2, 10, 12):
+        gemm_mode(mode)
+        gw_alone(f"g_w, mode {mode}", ws)
+        both(f"both, mode {mode}", ws)
+    torch.cuda.synchronize()
+    for name, out in zip(names, outs):
+        assert torch.equal(out, outs[0]), name
+
+
 def test_gw_bf16_config2_full_size():
     hot = _hot()
     wl = hot_inputs.WORKLOADS["cfg2_vitb_fc1"]
