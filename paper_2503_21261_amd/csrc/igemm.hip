@@ -88,6 +88,25 @@ int64_t large_tile_split(int64_t M, int64_t N, int64_t k_bytes, int bits, int cu
   while (s > 1 && (k_bytes / s < 16384 || tiles * (s - 1) > kMaxSplitSlots)) --s;
   return s >= 2 ? s : 0;
 }
+// Cost of a tile shape, fitted to measurements on MI355X (ten layer shapes from 512 to 201728
+// tokens, every INT4 tile timed on each; within 4 % of the measured time, and the measured
+// best tile or one within 2 % of it on all ten): a compute unit works through its share of
+// the tiles, each costing its operations at the rate the tile sustains plus its output bytes
+// at the rate its stores drain, plus a constant per launch.  The share is a whole number of
+// tiles while the resident workgroups (wgs per unit) take them in a few rounds, the last of
+// which idles units, and averages out over many rounds.
+struct Cand { int bm, bn, wgs; double us_per_mop, us_per_kb, us_launch; };
+constexpr Cand kCands4[] = {{128, 128, 3, 0.0979, 0.0324, 4.3}, {128, 256, 2, 0.0880, 0.0310, 3.6},
+                            {192, 256, 1, 0.0860, 0.0392, 5.6}, {256, 256, 1, 0.0821, 0.0385, 0.0}};
+constexpr Cand kCands8[] = {{128, 128, 2, 0.2560, 0.0, 0.0}, {256, 256, 1, 0.1004, 0.0476, 0.0}};
+double tile_mops(const Cand& c, double K) { return 2.0 * c.bm * c.bn * K * 1e-6; }
+double tile_shape_us(const Cand& c, int64_t M, int64_t N, double K, int cus) {
+  const int64_t tiles = ceil_div(M, c.bm) * ceil_div(N, c.bn);
+  const bool few_rounds = tiles <= 4 * (int64_t)cus * c.wgs;
+  const double per_cu = few_rounds ? (double)ceil_div(tiles, cus) : (double)tiles / cus;
+  const double kb = 4.0 * c.bm * c.bn / 1024.0;
+  return per_cu * (tile_mops(c, K) * c.us_per_mop + kb * c.us_per_kb) + c.us_launch;
+}
 // Slices of a GEMM on 128x128 tiles whose partial sums a second kernel adds (kImages); 0 = does
 // not apply.  A slice costs about 0.5 us per 128-byte K stage, an image 0.03 us to write and
 // read back, so the sum of both is least at sqrt(16 stages / tiles) slices, at most about two
@@ -118,18 +137,7 @@ void set_gemm_mode(int mode) { g_gemm_mode.store(mode); }
 void set_gemm_wait_us(int us) { g_gemm_wait_us.store(us); }
 
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images) {
-  // Cost of a tile shape, fitted to measurements on MI355X (ten layer shapes from 512 to 201728
-  // tokens, every INT4 tile timed on each; within 4 % of the measured time, and the measured
-  // best tile or one within 2 % of it on all ten): a compute unit works through its share of
-  // the tiles, each costing its operations at the rate the tile sustains plus its output bytes
-  // at the rate its stores drain, plus a constant per launch.  The share is a whole number of
-  // tiles while the resident workgroups (wgs per unit) take them in a few rounds, the last of
-  // which idles units, and averages out over many rounds.
-  struct Cand { int bm, bn, wgs; double us_per_mop, us_per_kb, us_launch; };
-  static const Cand cands4[] = {{128, 128, 3, 0.0979, 0.0324, 4.3}, {128, 256, 2, 0.0880, 0.0310, 3.6},
-                                {192, 256, 1, 0.0860, 0.0392, 5.6}, {256, 256, 1, 0.0821, 0.0385, 0.0}};
-  static const Cand cands8[] = {{128, 128, 2, 0.2560, 0.0, 0.0}, {256, 256, 1, 0.1004, 0.0476, 0.0}};
-  const Cand* cands = bits == 4 ? cands4 : cands8;
+  const Cand* cands = bits == 4 ? kCands4 : kCands8;
   const int ncand = bits == 4 ? 4 : 2;
   const double K = (double)k_bytes * (bits == 4 ? 2 : 1);
   const int cus = compute_units();
@@ -139,17 +147,12 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
   p.partial_bytes = 0;
   double best = 1e30;
   for (int c = 0; c < ncand; ++c) {
-    const int64_t tiles = ceil_div(M, cands[c].bm) * ceil_div(N, cands[c].bn);
-    const bool few_rounds = tiles <= 4 * (int64_t)cus * cands[c].wgs;
-    const double per_cu = few_rounds ? (double)ceil_div(tiles, cus) : (double)tiles / cus;
-    const double mops = 2.0 * cands[c].bm * cands[c].bn * K * 1e-6;
-    const double kb = 4.0 * cands[c].bm * cands[c].bn / 1024.0;
-    const double t = per_cu * (mops * cands[c].us_per_mop + kb * cands[c].us_per_kb) + cands[c].us_launch;
+    const double t = tile_shape_us(cands[c], M, N, K, cus);
     if (t < best) {
       best = t;
       p.bm = cands[c].bm;
       p.bn = cands[c].bn;
-      p.tiles = tiles;
+      p.tiles = ceil_div(M, p.bm) * ceil_div(N, p.bn);
     }
   }
   p.bkb = bits == 4 ? 64 : 128;
@@ -395,6 +398,42 @@ hipError_t launch_pair_tile(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, 
 
 }  // namespace
 
+namespace {
+
+// Whether g_x (plan of its own: `own`) gains from a place in g_w's launch, where its tiles are 128
+// rows high and do the whole K; `tiles` of them, `together` with all of g_w's workgroups resident at
+// once.  Two things are given up:
+//  - a split of K.  A tile alone then goes through K stage by stage, 0.2-0.6 us each, while the split
+//    cost one hand-over: shared launches win while K is short, longer where the split already put
+//    two workgroups on a unit (they slow each other down), shorter on 128x256 tiles, and where g_w's
+//    own hand-overs, which run beside g_x's stages, take long.  Stages of both sides' equality over
+//    1990 layers of 64 to 32768 tokens, 64 to 8192 inputs and 1024 to 32768 outputs: 40-48 / 60-72 for
+//    INT8 and INT4 on 128x128 tiles, 28-32 / 48 on 128x256, and 32-40 for g_x of 65 to 256 tiles behind
+//    more workgroups than are resident (512 tokens 16384 x 768 93 us apart, 145 together; 1024 tokens
+//    4096 x 512 46 and 34).
+//  - the eight-wave 256x256 INT8 tile.  Against the cost model's time for that one, 128x128 tiles
+//    price at 0.16 us per million operations and unit in this company (16384 tokens 4096 x 1024
+//    286 us apart, 297 together; 8192 tokens 146 and 134).  Split in two it is the slower one all the
+//    same, in three and more the faster (128 tokens 40960 x 512 288 us apart, 251 together; 65536 x 512
+//    321 and 406).
+bool shares_g_w_launch(const GemmPlan& own, const GemmCall& c, const GemmPlan& w, int64_t tiles, bool wide, bool together) {
+  const int cus = compute_units();
+  const int64_t stages = c.k_bytes / own.bkb, workgroups = own.tiles * own.split;
+  if (own.bm == 256 && own.split == 1 && c.bits == 8)
+    return (double)tiles / cus * tile_mops(kCands8[0], (double)c.k_bytes) * 0.16 <
+           tile_shape_us(kCands8[1], c.M, c.N, (double)c.k_bytes, cus);
+  if (own.bm == 256 && c.bits == 8) return own.split == 2;
+  if (own.bm != 128) return true;   // measured faster in every case
+  if (own.split > 1) {
+    if (workgroups <= cus) return stages <= (wide ? 28 : 40) + (together && w.split > 1 ? 24 : 0);
+    if (together) return stages <= (wide ? 48 : 64);
+    return stages <= (own.tiles > cus / 4 ? 32 : (wide ? 48 : 56));
+  }
+  return together || !wide || own.tiles > cus || stages <= 40;   // one tile per unit against two
+}
+
+}  // namespace
+
 hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, hipStream_t s, int stage, bool* done) {
   *done = false;
   if (g_gemm_mode.load() != 0 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
@@ -413,6 +452,9 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   const int64_t rows = ceil_div(cx.M, 128), x128 = rows * ceil_div(cx.N, 128), x256 = rows * ceil_div(cx.N, 256);
   const bool int4 = cx.bits == 4, narrow = w + x128 <= (int4 ? cap : most);
   if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
+  const int64_t x = narrow ? x128 : x256;
+  if (!shares_g_w_launch(plan_gemm(cx.M, cx.N, cx.k_bytes, cx.bits, true, false), cx, p, x, !narrow, w + x <= cap))
+    return hipSuccess;
   GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
@@ -430,9 +472,9 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   gx.tiles_n = (int)ceil_div(cx.N, narrow ? 128 : 256);
   gx.split = 1;
   stage_begin(stage, s);
-  const hipError_t e = !narrow ? launch_pair_tile<256, true>(gw, gx, (int)w, (int)x256, cw.bits, p.split, p.images, s)
-                       : int4  ? launch_pair_tile<128, true>(gw, gx, (int)w, (int)x128, cw.bits, p.split, p.images, s)
-                               : launch_pair_tile<128, false>(gw, gx, (int)w, (int)x128, cw.bits, p.split, p.images, s);
+  const hipError_t e = !narrow ? launch_pair_tile<256, true>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s)
+                       : int4  ? launch_pair_tile<128, true>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s)
+                               : launch_pair_tile<128, false>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s);
   stage_end(stage, s);
   *done = true;
   return e;

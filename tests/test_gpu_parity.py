@@ -1126,6 +1126,50 @@ def test_small_layers_in_few_launches_and_apart(gemm_mode, L, O, I, n, S, gw_bit
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
 
 
+def backward_stages(hot, cfg, gy, w, act, q, ws):
+    """One hot_linear_backward: its outputs and the kernel roles it launched, in order."""
+    (L, O), I = gy.shape, w.shape[1]
+    gx, gw = torch.full((L, I), -7.0, device="cuda"), torch.full((O, I), -7.0, device="cuda")
+    hot.hot_debug_profile_begin()
+    hot.hot_linear_backward(cfg, gy, w, act, q, gx, gw, ws)
+    hot.hot_debug_profile_end()
+    return gx, gw, hot.hot_debug_profile_sequence()
+
+
+@pytest.mark.parametrize("L,O,I,gx_bits,shared", [
+    (512, 768, 768, 4, True),        # 12 K stages of g_x, unsplit next to g_w
+    (512, 2560, 640, 4, True),       # 20, at 20 tiles
+    (128, 5120, 256, 4, True),       # 40 stages, split eight ways on its own
+    (128, 5376, 256, 4, False),      # 42
+    (2048, 8192, 256, 4, True),      # 64, beside hand-overs of g_w
+    (128, 16384, 256, 4, False),     # 128 stages on two tiles
+    (512, 11008, 1024, 4, False),    # 128x256 tiles behind 688 g_w tiles
+    (2048, 4096, 512, 8, True),      # 32 stages on 64 tiles
+    (512, 16384, 256, 8, False),
+    (12800, 4096, 1024, 8, False),   # the 256x256 INT8 tile
+    (4096, 1024, 4096, 8, True),     # the same tile, a short K
+    (128, 32768, 128, 8, True),      # the same tile, split in two
+    (128, 65536, 128, 8, False)])    # in four
+def test_gemms_share_a_launch_while_that_pays(L, O, I, gx_bits, shared):
+    """g_x's GEMM joins g_w's launch, where its tiles do the whole K, only while giving up its own split
+    of K or its own tile costs less than a launch: the roles launched, and the bits of both forms."""
+    hot = _hot()
+    x, w, gy = make(L, O, I, seed=80)
+    cfg = hot.Config(block=16, keep=8, gx_bits=gx_bits)
+    xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, xd, act, ws)
+    gx, gw, roles = backward_stages(hot, cfg, gyd, wd, act, hot.HOT_Q_PER_TOKEN, ws)
+    assert ("gx_and_gw_igemm" in roles) == shared and ("gx_igemm" in roles) == (not shared), roles
+    try:
+        hot.hot_debug_set_backward_strategy(3)
+        gx3, gw3, roles = backward_stages(hot, cfg, gyd, wd, act, hot.HOT_Q_PER_TOKEN, ws)
+    finally:
+        hot.hot_debug_set_backward_strategy(0)
+    assert "gx_igemm" in roles and "gw_igemm" in roles, roles
+    assert torch.equal(gx, gx3) and torch.equal(gw, gw3)
+
+
 def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode):
     """Two different inputs alternate through the same workspace, twelve back-to-back steps
     without a host synchronisation in between: every g_w must equal the one computed without
