@@ -193,6 +193,32 @@ hipError_t operands_n(OperandArgs f, bool all, bool of_gx, hipStream_t s, int st
   return e;
 }
 
+// Whether the rows of g_y may share a launch with the column jobs: they then run at the registers
+// of the widest of them (two waves per SIMD for 64-row blocks, three or four below), which a few
+// megabytes of rows do not notice and long streams do; wide weights, two blocks per wave, take their
+// share of the places on top.  The largest g_y that gained, in elements, and the next size timed, over
+// 1450 layers (us a backward call apart and together):
+//   per token   16-row blocks   any size up to where the shared passes begin; with wide weights 8.4 M
+//                               (4096 tokens 2048 x 4096 104 and 106, 2048 tokens 68 and 66)
+//               32              19 M (25216 x 768 x 768 103 and 100; 50432 x 2048 x 512 384 and 404);
+//                               wide weights 8.4 M (8192 x 2048 x 4096 174 and 176)
+//               64              9.7 M (12608 x 768 x 768 63 and 57; 12608 x 2048 x 512 117 and 128)
+//   one scale   any size, where a lane has more than one 16-byte load in flight; 64-row blocks of 256 columns
+//                               and fewer 26 M (201728 x 256 x 256 233 and 241)
+// Weights of 64-row blocks that need all the exchange's slots lose at every size (1024 tokens
+// 4096 x 4096 87 and 90).
+bool rows_join(const Config& cfg, int64_t L, int64_t O, int64_t I, bool per_token) {
+  const int lanes = cfg.n == 16 && I % 2 == 0 ? 2 : 1;
+  auto weight_tiles = [&](int kb) { return ceil_div(I, 64 * lanes) * ceil_div(O / cfg.n, 4 * kb); };
+  const bool wide = weight_tiles(1) > kMaxExchange;
+  if (cfg.n == 64 && weight_tiles(2) >= kMaxExchange) return false;
+  const int64_t elements = L * O, million = 1000000;
+  if (!per_token) return cfg.n != 64 || O > 256 || elements <= 26 * million;
+  if (cfg.n == 16) return !wide || elements <= 8 * million;
+  if (cfg.n == 32) return elements <= (wide ? 12 : 20) * million;
+  return elements <= 10 * million;
+}
+
 // Bounded wait (100 MHz ticks) of the single-pass workgroups over `bytes` of input.
 long long wait_ticks(int64_t wait_us, int64_t bytes) {
   const int64_t stream_us = bytes / 1000000;   // as in the column kernel's own launcher
@@ -207,7 +233,7 @@ hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& c
                            float* slots_g, hipStream_t s, int stage, OperandsMade* made) {
   *made = kOperandsNone;
   const int64_t wait_us = exchange_wait_us();
-  if (wait_us < 0 || O > 4096) return hipSuccess;
+  if (wait_us < 0 || O > 4096 || !rows_join(cfg, L, O, I, per_token)) return hipSuccess;
   // INT4 with a scale per token has w_and_rows_kernel, whose rows keep more waves (INT8, 6304 tokens
   // 3072 x 768: 118 -> 114 us a layer pass)
   const bool all = cfg.gw_bits == 8, of_gx = cfg.gx_bits == 8 || !per_token;

@@ -1170,6 +1170,45 @@ def test_gemms_share_a_launch_while_that_pays(L, O, I, gx_bits, shared):
     assert torch.equal(gx, gx3) and torch.equal(gw, gw3)
 
 
+@pytest.mark.parametrize("n,L,O,I,gx_bits,per_token,operands", [
+    (64, 8192, 1024, 512, 4, True, "all"),        # 8.4 M elements
+    (64, 6400, 2048, 512, 4, True, "apart"),      # 13 M
+    (64, 6400, 1536, 512, 8, True, "all"),        # 9.8 M
+    (64, 12800, 1024, 512, 8, True, "apart"),     # 13 M
+    (64, 19200, 1024, 512, 8, False, "gx"),       # one scale: rows of any number ...
+    (64, 106496, 256, 64, 8, False, "apart"),     # ... but long narrow ones
+    (64, 256, 4096, 4096, 4, False, "apart"),     # weights of 512 tiles of two blocks
+    (32, 12800, 1536, 512, 8, True, "gx"),        # 20 M
+    (32, 12800, 2048, 512, 8, True, "apart"),     # 26 M
+    (32, 8192, 2048, 4096, 8, True, "apart"),     # wide weights
+    (16, 12800, 2048, 512, 8, True, "gx"),
+    (16, 3584, 2048, 4096, 8, True, "gx"),        # wide weights, 7.3 M
+    (16, 8192, 2048, 4096, 8, True, "apart")])
+def test_operands_share_a_launch_while_that_pays(n, L, O, I, gx_bits, per_token, operands):
+    """The rows of g_y join the column jobs' launch only up to the sizes that gain by it: the roles launched,
+    and the bits of both forms."""
+    hot = _hot()
+    x, w, gy = make(L, O, I, seed=83)
+    cfg = hot.Config(block=n, keep=n // 2, gx_bits=gx_bits)
+    xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, xd, act, ws)
+    q = hot.HOT_Q_PER_TOKEN if per_token else hot.HOT_Q_PER_TENSOR
+    gx, gw, roles = backward_stages(hot, cfg, gyd, wd, act, q, ws)
+    weights_apart, view_apart = "w_col_quant" in roles, "gyT_col_quant" in roles
+    if gx_bits == 4 and per_token:   # the weights and the rows have a shared launch of their own
+        assert view_apart == (operands == "apart"), roles
+    else:
+        assert weights_apart == (operands == "apart") and view_apart == (operands != "all"), roles
+    try:
+        hot.hot_debug_set_backward_strategy(3)
+        gx3, gw3, roles = backward_stages(hot, cfg, gyd, wd, act, q, ws)
+    finally:
+        hot.hot_debug_set_backward_strategy(0)
+    assert "w_col_quant" in roles and "gyT_col_quant" in roles, roles
+    assert torch.equal(gx, gx3) and torch.equal(gw, gw3)
+
+
 def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode):
     """Two different inputs alternate through the same workspace, twelve back-to-back steps
     without a host synchronisation in between: every g_w must equal the one computed without
