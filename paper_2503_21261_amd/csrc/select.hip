@@ -69,10 +69,10 @@ struct SelectArgs {
 };
 
 // End of a pass: the workgroup's error sum and (per-token pass) abs-max.
-template <bool TOKEN>
+template <bool TOKEN, int WAVES = 4>
 __device__ __forceinline__ void leave_sums(const SelectArgs& a, double sum, float running) {
-  __shared__ double s_sum[4];
-  __shared__ float s_run[4];
+  __shared__ double s_sum[WAVES];
+  __shared__ float s_run[WAVES];
   const int tid = threadIdx.x;
 #pragma unroll
   for (int m = 1; m < 64; m *= 2) sum += __shfl_xor(sum, m);
@@ -80,8 +80,15 @@ __device__ __forceinline__ void leave_sums(const SelectArgs& a, double sum, floa
   if ((tid & 63) == 0) { s_sum[tid >> 6] = sum; s_run[tid >> 6] = running; }
   __syncthreads();
   if (tid == 0) {
-    a.sums[blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
-    if constexpr (TOKEN) a.partials[blockIdx.x] = fmaxf(fmaxf(s_run[0], s_run[1]), fmaxf(s_run[2], s_run[3]));
+    double total = 0.0;
+    float most = 0.0f;
+#pragma unroll
+    for (int w = 0; w < WAVES; w += 4) {
+      total += (s_sum[w] + s_sum[w + 1]) + (s_sum[w + 2] + s_sum[w + 3]);
+      most = fmaxf(most, fmaxf(fmaxf(s_run[w], s_run[w + 1]), fmaxf(s_run[w + 2], s_run[w + 3])));
+    }
+    a.sums[blockIdx.x] = total;
+    if constexpr (TOKEN) a.partials[blockIdx.x] = most;
   }
 }
 
@@ -132,10 +139,15 @@ __global__ __launch_bounds__(256) void select_rows_kernel(const SelectArgs a) {
   leave_sums<TOKEN>(a, sum, running);
 }
 
-// Rows too long for registers: one per workgroup, read twice in the per-token pass.
-template <int N, bool TOKEN>
-__global__ __launch_bounds__(256) void select_stream_kernel(const SelectArgs a) {
-  __shared__ float s_max[4];
+// Rows a part at a time, one per workgroup: those too long for 256 threads' registers, in the per-token
+// pass with the first kStreamHeld float4 of a thread kept and only what lies beyond read twice; and
+// the per-tensor pass, which has no use for a whole row, of the longest that registers hold (few of
+// their workgroups fit a unit).  4096 rows of 11392: 129 us with whole rows in both passes, 110 so; of
+// 16448 with nothing kept 164, 148 so.
+constexpr int kStreamHeld = 8;
+template <int N, bool TOKEN, int NT>
+__global__ __launch_bounds__(NT) void select_stream_kernel(const SelectArgs a) {
+  __shared__ float s_max[NT / 64];
   const int tid = threadIdx.x;
   const int qmax = (1 << (a.bits - 1)) - 1;
   const RowLane<N> lane = row_lane<N>(tid);
@@ -143,33 +155,56 @@ __global__ __launch_bounds__(256) void select_stream_kernel(const SelectArgs a) 
   float amax = 0.0f, running = 0.0f;
   if constexpr (!TOKEN) amax = block_max_of(a.partials, a.npartials);
   double sum = 0.0;
-  for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+  for (int64_t r = blockIdx.x; r < a.rows; r += gridDim.x) {
+    const int64_t row = TOKEN ? r : a.rows - 1 - r;   // as in select_rows_kernel
     const float4* src = reinterpret_cast<const float4*>(a.t + row * (int64_t)a.cols);
     auto transformed = [&](int base) {   // uniform trip counts keep the lanes of a butterfly together
       float4 q = base + lane.id < nvec ? src[base + lane.id] : make_float4(0.f, 0.f, 0.f, 0.f);
       fwht_row4<N>(q, lane);
       return q;
     };
+    constexpr int HELD = TOKEN ? kStreamHeld : 0;
+    float4 held[HELD > 0 ? HELD : 1];
     if constexpr (TOKEN) {
       float m = 0.0f;
-      for (int base = 0; base < nvec; base += 256) m = fmaxf(m, absmax4(transformed(base)));
-      amax = row_max<256>(m, s_max);
+#pragma unroll
+      for (int it = 0; it < HELD; ++it) {
+        const int i = it * NT + lane.id;
+        held[it] = i < nvec ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int it = 0; it < HELD; ++it) {
+        fwht_row4<N>(held[it], lane);
+        m = fmaxf(m, absmax4(held[it]));
+      }
+      for (int base = NT * HELD; base < nvec; base += NT) m = fmaxf(m, absmax4(transformed(base)));
+      m = wave_max(m);
+      if ((tid & 63) == 0) s_max[tid >> 6] = m;
+      __syncthreads();
+      amax = 0.0f;
+#pragma unroll
+      for (int w = 0; w < NT / 64; ++w) amax = fmaxf(amax, s_max[w]);
+      __syncthreads();
       running = fmaxf(running, amax);
     }
     const float inv = flip_sign(quant_inv(amax, qmax), lane.flip);
     const double scale = (double)flip_sign(quant_scale(amax, qmax), lane.flip);
     if (isinf(inv)) {
-      for (int base = 0; base < nvec; base += 256)
+      for (int base = 0; base < nvec; base += NT)
         sum = add_saturated_sq_err4(sum, transformed(base), inv, scale, (float)qmax);
       continue;
     }
-    for (int base = 0; base < nvec; base += 256) {
+#pragma unroll
+    for (int it = 0; it < HELD; ++it)
+      sum = a.rounding == 0 ? add_sq_err4<0>(sum, held[it], inv, scale, (float)qmax)
+                            : add_sq_err4<1>(sum, held[it], inv, scale, (float)qmax);
+    for (int base = NT * HELD; base < nvec; base += NT) {
       const float4 q = transformed(base);
       sum = a.rounding == 0 ? add_sq_err4<0>(sum, q, inv, scale, (float)qmax)
                             : add_sq_err4<1>(sum, q, inv, scale, (float)qmax);
     }
   }
-  leave_sums<TOKEN>(a, sum, running);
+  leave_sums<TOKEN, NT / 64>(a, sum, running);
 }
 
 // Single workgroup: result[c] = sum of sums[c][0 .. count), fixed order.
@@ -191,6 +226,13 @@ __global__ __launch_bounds__(256) void select_final_kernel(const double* __restr
 
 namespace {
 
+// Float4 per thread from which the per-tensor pass streams its rows (4096 rows of 9216: 97 us held, 90
+// streamed; at 6, 1024 rows of 6144, 46 either way).
+constexpr int kStreamFrom = 8;
+// Longest streamed rows whose first pass runs on 256 threads (4096 rows of 20480: 175 us, 185 on 1024
+// threads; of 32768 276 and 240).
+constexpr int kFewThreads = 20480;
+
 template <int N>
 hipError_t launch_passes(SelectArgs a, double* result, hipStream_t s) {
   double* const sums = a.sums;
@@ -202,14 +244,16 @@ hipError_t launch_passes(SelectArgs a, double* result, hipStream_t s) {
     a.npartials = (int)grid;
     select_rows_kernel<N, ITER, TPR, true><<<dim3(grid), dim3(256), 0, s>>>(a);
     a.sums = sums + grid;
-    select_rows_kernel<N, ITER, TPR, false><<<dim3(grid), dim3(256), 0, s>>>(a);
+    if constexpr (ITER >= kStreamFrom) select_stream_kernel<N, false, 256><<<dim3(grid), dim3(256), 0, s>>>(a);
+    else select_rows_kernel<N, ITER, TPR, false><<<dim3(grid), dim3(256), 0, s>>>(a);
   });
   if (!held) {
     grid = (unsigned)(a.rows < kMaxPartials ? a.rows : kMaxPartials);
     a.npartials = (int)grid;
-    select_stream_kernel<N, true><<<dim3(grid), dim3(256), 0, s>>>(a);
+    if (a.cols <= kFewThreads) select_stream_kernel<N, true, 256><<<dim3(grid), dim3(256), 0, s>>>(a);
+    else select_stream_kernel<N, true, 1024><<<dim3(grid), dim3(1024), 0, s>>>(a);
     a.sums = sums + grid;
-    select_stream_kernel<N, false><<<dim3(grid), dim3(256), 0, s>>>(a);
+    select_stream_kernel<N, false, 256><<<dim3(grid), dim3(256), 0, s>>>(a);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -284,7 +284,8 @@ def test_select_quantizer_matches_oracle(kind, n):
 
 @pytest.mark.parametrize("L,O,n,bits,rounding", [(37, 16, 16, 4, 1), (35, 64, 64, 8, 1), (17, 96, 32, 4, 0),
                                                  (9, 128, 64, 4, 1), (33, 192, 64, 8, 0), (5, 16448, 64, 4, 1),
-                                                 (3, 16384, 32, 4, 1)])
+                                                 (3, 16384, 32, 4, 1), (7, 7232, 64, 8, 1), (5, 11328, 32, 4, 1),
+                                                 (3, 20480, 64, 4, 0), (3, 20512, 32, 8, 1), (5, 50304, 64, 4, 1)])
 def test_row_layouts(L, O, n, bits, rounding):
     """Rows held by 16, 32, 64 and 256 threads and streamed ones, with partly filled workgroups and
     rows that end inside a thread group: the quantised rows and the selection's two sums."""
@@ -308,7 +309,7 @@ def test_select_quantizer_zero_gradient():
     assert (choice, m_tok, m_ten) == (hot.HOT_Q_PER_TENSOR, 0.0, 0.0)
 
 
-@pytest.mark.parametrize("O,bits,rounding", [(48, 4, 1), (48, 8, 0), (1040, 4, 0), (16448, 4, 1)])
+@pytest.mark.parametrize("O,bits,rounding", [(48, 4, 1), (48, 8, 0), (1040, 4, 0), (16448, 4, 1), (32800, 4, 0)])
 def test_select_quantizer_scale_without_a_finite_inverse(O, bits, rounding):
     """A gradient so small that qmax / abs-max overflows: zeros keep code 0 (and no error), every other
     element saturates.  Rows on few threads, on a wave, and streamed; blocks of zeros, and zeros that the
