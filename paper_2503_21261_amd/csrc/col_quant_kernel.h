@@ -45,34 +45,6 @@ __host__ __device__ constexpr int lowpass_row(int n, int j) {
   return r;
 }
 
-// The first half of the LP_L1 list (the order hot_lowpass_l1_rows states) as a compile-time table.
-template <int N>
-struct LpL1Rows {
-  int row[N / 2];
-  static constexpr int changes(int n, int k) {   // sign changes along row k of the n-point matrix
-    int c = 0, prev = 0;
-    for (int j = 0; j < n; ++j) {
-      int neg = 0;
-      for (int b = k & j; b; b &= b - 1) neg ^= 1;
-      c += j > 0 && neg != prev;
-      prev = neg;
-    }
-    return c;
-  }
-  constexpr LpL1Rows() : row() {
-    constexpr int gw = N == 16 ? 4 : 8;
-    int key[N] = {};
-    for (int k = 0; k < N; ++k) {
-      const int sv = changes(N / gw, k / gw), sh = changes(gw, k % gw);
-      key[k] = (((sv + sh) * 64 + (sv > sh ? sv : sh)) * 64 + sv) * 64 + k;
-    }
-    for (int k = 0; k < N; ++k) {
-      int rank = 0;
-      for (int i = 0; i < N; ++i) rank += key[i] < key[k];
-      if (rank < N / 2) row[rank] = k;
-    }
-  }
-};
 template <int N>
 __host__ __device__ constexpr int lp_l1_row(int j) {
   constexpr LpL1Rows<N> t;

@@ -12,6 +12,35 @@ namespace hot {
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The first half of the LP_L1 list (the order hot_lowpass_l1_rows states) as a compile-time table.
+template <int N>
+struct LpL1Rows {
+  int row[N / 2];
+  static constexpr int changes(int n, int k) {   // sign changes along row k of the n-point matrix
+    int c = 0, prev = 0;
+    for (int j = 0; j < n; ++j) {
+      int neg = 0;
+      for (int b = k & j; b; b &= b - 1) neg ^= 1;
+      c += j > 0 && neg != prev;
+      prev = neg;
+    }
+    return c;
+  }
+  constexpr LpL1Rows() : row() {
+    constexpr int gw = N == 16 ? 4 : 8;
+    int key[N] = {};
+    for (int k = 0; k < N; ++k) {
+      const int sv = changes(N / gw, k / gw), sh = changes(gw, k % gw);
+      key[k] = (((sv + sh) * 64 + (sv > sh ? sv : sh)) * 64 + sv) * 64 + k;
+    }
+    for (int k = 0; k < N; ++k) {
+      int rank = 0;
+      for (int i = 0; i < N; ++i) rank += key[i] < key[k];
+      if (rank < N / 2) row[rank] = k;
+    }
+  }
+};
+
 // Position of every natural-order row of an n-block in the kept list (-1 = dropped).
 struct KeepMap {
   int8_t pos[64];
