@@ -420,9 +420,11 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
       // The last tile row and column: buffer stores, whose hardware drops what lies past the
       // descriptor's end: no compare or branch per element, and the row is in the (scalar) base.
       // A descriptor ends with the output; columns past it start at half the range, which no
-      // descriptor reaches and no lane's valid offset either.  Passes of a layer, against a compare and a
-      // branch per element: 3136 tokens 448 x 1792 59.7 -> 56.3 us, 197 tokens 768 x 768
-      // 32.4 -> 31.3, 12608 tokens 3072 x 768 164 -> 161.
+      // descriptor reaches and no lane's valid offset either.  The streaming hint only where rows are whole
+      // 128-byte lines: a line shared by two tiles goes out in parts with it (g_x of 100000 tokens
+      // 256 x 300 84.4 us with it, 75.0 without; 50000 x 512 x 1356 132 and 126).
+      // Passes of a layer, against a compare and a branch per element: 3136 tokens 448 x 1792 59.7 ->
+      // 56.3 us, 197 tokens 768 x 768 32.4 -> 31.3, 12608 tokens 3072 x 768 164 -> 161.
       constexpr unsigned kEnd = 0x80000000u;
       unsigned col_byte[TN];
 #pragma unroll
@@ -447,7 +449,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs& g, const int bid) {
           }
         }
       };
-      if (g.stream_out) store_tile(std::true_type{});
+      if (g.stream_out && g.N % 32 == 0) store_tile(std::true_type{});
       else store_tile(std::false_type{});
     } else {
       const bool raw = !g.out_f32;
