@@ -168,7 +168,7 @@ def test_gx_variants(n, bits, rounding, per_token):
 
 
 def test_gx_config1_full():
-    """configs[0]: L=512, O=768, I=768, n=16, INT4 per token."""
+    """The single 512 x 768 x 768 layer, n=16, INT4 per token."""
     hot = _hot()
     wl = hot_inputs.WORKLOADS["cfg1_single_512x768x768"]
     x, w, gy = hot_inputs.make_layer(wl, wl.layers[0], seed=0)
@@ -361,7 +361,7 @@ def test_calls_are_repeatable_and_stream_ordered():
 # ---- full-size and workload-shaped cases -------------------------------------------------
 
 def test_config2_full_size_in_bench_configuration():
-    """configs[1] (ViT-B fc1, 12608 tokens, n=32, r=16) exactly as bench.py launches it;
+    """ViT-B fc1 (12608 tokens, n=32, r=16) exactly as bench.py launches it;
     the oracle is fast enough to compare every element of every stage."""
     hot = _hot()
     wl = hot_inputs.WORKLOADS["cfg2_vitb_fc1"]
@@ -380,7 +380,7 @@ def test_config2_full_size_in_bench_configuration():
 @pytest.mark.parametrize("name,L", [("cfg3_vitb_block_b256", 1024), ("cfg4_llm7b_mlp", 256),
                                     ("cfg5_vitl_chain", 512)])
 def test_workload_shaped_layers_on_a_token_subrange(name, L):
-    """Layers of configs[2..4] at their real O, I, block and value distributions on a
+    """Layers of the ViT-B block, LLM MLP and ViT-L workloads at their real O, I, block and value distributions on a
     token sub-range the oracle finishes in seconds; config 4 takes its quantizer from
     hot_select_quantizer, which must agree with the oracle's choice."""
     hot = _hot()
@@ -587,7 +587,7 @@ def check_full_size_layer(hot, cfg, xd, wd, gyd, per_token, what, one_call_strat
                                       ("cfg4_llm7b_mlp", 0), ("cfg4_llm7b_mlp", 1),
                                       ("cfg5_vitl_chain", 0), ("cfg5_vitl_chain", 1)])
 def test_full_size_layers_sampled(name, idx):
-    """Every layer of configs[2], [3] and [4] at its full token count (config 4: the 256x256
+    """Every layer of the ViT-B block, LLM MLP and ViT-L workloads at its full token count (config 4: the 256x256
     GEMM tiles, 64-row blocks and the quantiser hot_select_quantizer picks at that size, which
     must be the oracle's; config 5: tensors beyond 2^31 bytes on either side), through the
     separate calls and through hot_linear_backward as the sweeps of the benchmark call it."""
@@ -647,7 +647,7 @@ def test_config5_chain_slice_at_full_size():
 
 
 def test_config2_per_sample_tiling_at_full_size():
-    """configs[1] with its 64 samples of 197 tokens tiled separately (12 blocks of 16 and a
+    """ViT-B fc1 with its 64 samples of 197 tokens tiled separately (12 blocks of 16 and a
     padded one of 5 per sample would be n = 16; here n = 32: 6 blocks and one of 5 tokens), as
     `bench.py --sample-tokens 197` times it: INT8 and bfloat16 g_w operands, every element."""
     hot = _hot()
@@ -888,7 +888,7 @@ def test_single_pass_transposed_stores_with_ragged_edges():
 
 
 def test_config2_two_pass_column_kernels(exchange_wait):
-    """configs[1] with the single-pass kernels switched off (x and w then take the same
+    """ViT-B fc1 with the single-pass kernels switched off (x and w then take the same
     two-pass kernels as tensors too large for the register files)."""
     hot = _hot()
     exchange_wait(-1)
@@ -1038,13 +1038,23 @@ def test_bf16_gemm_on_the_large_tile():
 
 
 @pytest.mark.parametrize("wait_us", [200, 0])
-def test_int8_gemm_large_tile_with_k_split(gemm_mode, wait_us):
-    """A small output with a very long K (40000 reduced tokens): the g_w GEMM takes the 256x256
-    tile with K in two slices; with wait 0 the owner computes the other slice itself."""
+@pytest.mark.parametrize("L,O,I,handed_over", [(66000, 516, 1030, True),    # 45 tiles of 128x128, 15 of 256x256
+                                               (80000, 300, 260, False)])   # 9 tiles: images on the small tile
+def test_int8_gemm_large_tile_with_k_split(gemm_mode, L, O, I, handed_over, wait_us):
+    """A small output with a very long K (33000 and 40000 reduced tokens): the g_w GEMM takes the 256x256
+    tile with K in two slices handed over (with wait 0 the owner computes the other slice itself), or,
+    with few tiles, slices whose images a second kernel adds."""
     hot = _hot()
     hot.hot_debug_set_exchange_wait_us(wait_us)
-    x, w, gy = make(80000, 300, 260, seed=73)
-    check_gw(hot, hot.Config(block=16, keep=8), gy, x, f"large INT8 tile, K split, wait={wait_us}")
+    x, w, gy = make(L, O, I, seed=73)
+    cfg = hot.Config(block=16, keep=8)
+    check_gw(hot, cfg, gy, x, f"large INT8 tile, K split, wait={wait_us}")
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, x.cuda(), act, ws)
+    split_flags(ws).fill_(0x5A)
+    hot.hot_linear_backward_gw(cfg, gy.cuda(), act, I, torch.empty((O, I), device="cuda"), ws)
+    torch.cuda.synchronize()
+    assert bool((split_flags(ws) != 0x5A).any()) == handed_over
 
 
 @pytest.mark.parametrize("L,O,I,bits", [(4096, 128, 128, 8), (4240, 130, 257, 8), (16400, 48, 260, 8),
@@ -1083,7 +1093,7 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     (16384, 640, 33, 64, 0, 8, None),
     (1024, 64, 130, 64, 0, 8, list(range(64))),   # every row kept, in natural order
     (333, 4096, 40, 32, 333, 8, [7, 1, 30]),      # longest row, three rows kept
-    (2048, 128, 130, 32, 0, 8, None),       # g_w images added by a second kernel
+    (4096, 128, 130, 32, 0, 8, None),       # g_w images added by a second kernel
     (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
     (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
     (8208, 2304, 768, 16, 0, 8, None),      # more workgroups than are resident at once
@@ -1210,13 +1220,22 @@ def test_operands_share_a_launch_while_that_pays(n, L, O, I, gx_bits, per_token,
     assert torch.equal(gx, gx3) and torch.equal(gw, gw3)
 
 
-def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode):
+def split_flags(ws):
+    """The workspace's flags of K slices handed over between workgroups (no other kernel writes them)."""
+    return ws[256 + 2 * 8192:256 + 2 * 8192 + 1024 * 8]
+
+
+@pytest.mark.parametrize("O,I,handed_over", [(384, 256, False),    # 6 tiles of 128x128, 32 K stages: images of 8 slices
+                                             (896, 1024, True)])   # 56 tiles: 8 slices handed over
+@pytest.mark.parametrize("call", ["g_w", "both"])
+def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode, O, I, handed_over, call):
     """Two different inputs alternate through the same workspace, twelve back-to-back steps
     without a host synchronisation in between: every g_w must equal the one computed without
     a K split for that input.  A partial sum left in some cache by an earlier launch, or a
-    flag of an earlier launch taken for a fresh one, would show up here."""
+    flag of an earlier launch taken for a fresh one, would show up here.  Both forms of a split,
+    from the g_w call and from g_w's part of the launch that runs both GEMMs."""
     hot = _hot()
-    L, O, I = 8192, 384, 256          # 6 tiles of 128x128, K of 32 stages: split in 8
+    L = 8192
     cfg = hot.Config(block=32, keep=16)
     data = [make(L, O, I, seed=61), make(L, O, I, seed=62)]
     ws = hot.alloc_workspace(cfg, L, O, I)
@@ -1232,11 +1251,21 @@ def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode):
         want.append(gw.clone())
     assert not torch.equal(want[0], want[1])
     gemm_mode(0)
-    gys = [d[2].cuda() for d in data]
+    split_flags(ws).fill_(0x5A)
+    gys, ws_ = [d[2].cuda() for d in data], [d[1].cuda() for d in data]
     outs = [torch.empty((O, I), device="cuda") for _ in range(12)]
+    gx = torch.empty((L, I), device="cuda")
+    if call == "both":
+        roles = backward_stages(hot, cfg, gys[1], ws_[1], acts[1], hot.HOT_Q_PER_TOKEN, ws)[2]
+        assert "gx_and_gw_igemm" in roles, roles
     for step in range(12):
-        hot.hot_linear_backward_gw(cfg, gys[step % 2], acts[step % 2], I, outs[step], ws)
+        k = step % 2
+        if call == "both":
+            hot.hot_linear_backward(cfg, gys[k], ws_[k], acts[k], hot.HOT_Q_PER_TOKEN, gx, outs[step], ws)
+        else:
+            hot.hot_linear_backward_gw(cfg, gys[k], acts[k], I, outs[step], ws)
     torch.cuda.synchronize()
+    assert bool((split_flags(ws) != 0x5A).any()) == handed_over
     for step in range(12):
         assert torch.equal(outs[step], want[step % 2]), f"step {step}"
 
@@ -1438,17 +1467,21 @@ def test_per_sample_tiling_shape_errors_and_gx_is_unaffected():
 
 # ---- calls recorded into a HIP graph ----------------------------------------------------------------
 
-def test_replayable_calls_in_a_hip_graph():
+@pytest.mark.parametrize("L,O,I,per_token,handed_over", [
+    (512, 768, 768, True, False),     # one slice per g_w tile
+    (4096, 896, 1024, False, True),   # 56 g_w tiles in four slices handed over, one g_y scale for the tensor
+    (4096, 128, 256, True, False)])   # two g_w tiles in four slices, images added by a second kernel
+def test_replayable_calls_in_a_hip_graph(L, O, I, per_token, handed_over):
     """With hot_config.replayable the launch tags come from an epoch in the workspace that every
-    call advances, so a recorded step can be replayed.  One step of configs[0] (compression, both
-    gradients: single-pass exchange kernels, the combined weight / g_y launch and the split-K g_w
-    GEMM, all of which use tags) is captured once and replayed six times on inputs that change
+    call advances, so a recorded step can be replayed.  One step (compression, both gradients:
+    single-pass exchange kernels, all operands in one launch, both GEMMs in another, with and
+    without K slices of g_w) is captured once and replayed six times on inputs that change
     between the replays, with eager work and a synchronisation in between; every replay must
     give the bits of the eager, host-tagged call on the same inputs, and the first also the
     oracle's.  Half of the replays run with the exchange wait at zero, so that workgroups also
     take the path that recomputes the other tiles' maxima."""
     hot = _hot()
-    L, O, I = 512, 768, 768
+    quantizer = hot.HOT_Q_PER_TOKEN if per_token else hot.HOT_Q_PER_TENSOR
     cfg_r = hot.Config(block=16, keep=8, replayable=True)
     cfg_e = hot.Config(block=16, keep=8)
     dev = "cuda"
@@ -1462,8 +1495,9 @@ def test_replayable_calls_in_a_hip_graph():
 
     def step(cfg, act, work, gx, gw):
         hot.hot_compress_activation(cfg, x_d, act, work)
-        hot.hot_linear_backward(cfg, gy_d, w_d, act, hot.HOT_Q_PER_TOKEN, gx, gw, work)
+        hot.hot_linear_backward(cfg, gy_d, w_d, act, quantizer, gx, gw, work)
 
+    split_flags(work_r).fill_(0x5A)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):          # launch plans are made on first use: once before recording
@@ -1493,10 +1527,11 @@ def test_replayable_calls_in_a_hip_graph():
             assert torch.equal(gw_r, gw_e), f"replay {k}: g_w differs from the eager call"
             if k == 1:
                 ref_codes, ref_sx = oracle.compress_activation(xs[k].numpy(), 16, 8)
-                ref_x = oracle.backward_gx(gys[k].numpy(), ws_[k].numpy(), 16, bits=4, per_token=True)
+                ref_x = oracle.backward_gx(gys[k].numpy(), ws_[k].numpy(), 16, bits=4, per_token=per_token)
                 ref_w = oracle.backward_gw(gys[k].numpy(), ref_codes, ref_sx, 16, 8)
                 assert_close_maxnorm(gx_r.cpu().numpy(), ref_x["g_x"], "replayed g_x")
                 assert_close_maxnorm(gw_r.cpu().numpy(), ref_w["g_w"], "replayed g_w")
+        assert bool((split_flags(work_r) != 0x5A).any()) == handed_over
     finally:
         hot.hot_debug_set_exchange_wait_us(200)
 
@@ -1507,7 +1542,7 @@ def test_replayable_calls_give_the_bits_of_host_tagged_calls():
     transforms take the single-pass kernels (the g_x call twice in a row, so that the second
     call finds the first one's slots and flags in the workspace)."""
     hot = _hot()
-    L, O, I = 1024, 768, 512
+    L, O, I = 4096, 768, 1024         # 48 g_w tiles of 16 K stages: four slices handed over
     x, w, gy = make(L, O, I, seed=81)
     xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
     outs = {}
@@ -1517,6 +1552,7 @@ def test_replayable_calls_give_the_bits_of_host_tagged_calls():
         act, wq = hot.alloc_act_buffer(cfg, L, I), hot.alloc_weight_buffer(cfg, O, I)
         g = {k: torch.empty((L, I), device="cuda") for k in ("gx", "gx2", "cached", "noalloc", "both_x")}
         gw, gw2 = torch.empty((O, I), device="cuda"), torch.empty((O, I), device="cuda")
+        split_flags(ws).fill_(0x5A)
         hot.hot_compress_activation(cfg, xd, act, ws)
         hot.hot_linear_backward_gx(cfg, gyd, wd, hot.HOT_Q_PER_TOKEN, g["gx"], ws)
         hot.hot_linear_backward_gx(cfg, gyd, wd, hot.HOT_Q_PER_TENSOR, g["gx2"], ws)
@@ -1526,6 +1562,7 @@ def test_replayable_calls_give_the_bits_of_host_tagged_calls():
         hot.hot_linear_backward_gw(cfg, gyd, act, I, gw, ws)
         hot.hot_linear_backward(cfg, gyd, wd, act, hot.HOT_Q_PER_TOKEN, g["both_x"], gw2, ws)
         torch.cuda.synchronize()
+        assert bool((split_flags(ws) != 0x5A).any())
         outs[replayable] = {**{k: v.cpu() for k, v in g.items()}, "gw": gw.cpu(), "gw2": gw2.cpu()}
     for k in outs[False]:
         assert torch.equal(outs[False][k], outs[True][k]), f"{k}: replayable call differs from the host-tagged call"
