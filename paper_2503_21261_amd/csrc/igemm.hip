@@ -109,12 +109,13 @@ double tile_shape_us(const Cand& c, int64_t M, int64_t N, double K, int cus) {
 }
 // Slices of a GEMM on 128x128 tiles whose partial sums a second kernel adds (kImages); 0 = does
 // not apply.  A slice costs about 0.5 us per 128-byte K stage, an image 0.03 us to write and
-// read back, so the sum of both is least at sqrt(16 stages / tiles) slices, at most about two
-// workgroups per compute unit (multiples of 8 let an XCD keep whole slices).  Measured, best of
-// 1-24 slices against this rule's: 4 tiles x 49 stages 13.6 / 13.6 us (8 slices; the hand-over
-// 22.8), 16 x 32 14.6 / 14.6 (21.6), 32 x 49 16.7 / 17.1 (25.8), 36 x 788 104.5 / 106.7 (16
-// slices; the hand-over on 256x256 tiles 197), bfloat16 36 x 99 25.2 / 25.2 (unsplit 55.0),
-// 144 x 99 53.9 / 53.9 (59.8).
+// read back, so the sum of both is least at sqrt(16 stages / tiles) slices, with about two
+// workgroups per compute unit and four stages a slice at most; counts above 8 are rounded to a
+// multiple of 8, which lets an XCD keep whole slices and may pass those two by a little (16 slices
+// of three stages for 4 tiles x 49, 576 workgroups for 36 x 788; 8 slices took 12.0 and 101.2).  Measured,
+// best of 1-24 slices against this rule's: 4 tiles x 49 stages 12.0 / 12.4 us (the hand-over 22.8),
+// 16 x 32 13.5 / 14.3 (21.6), 32 x 49 16.3 / 16.9 (25.8), 36 x 788 97.1 / 99.9 (the hand-over on
+// 256x256 tiles 197), bfloat16 36 x 99 24.4 / 24.5 (unsplit 52.8), 144 x 99 52.8 / 52.8 (56.9).
 // INT8 GEMMs of more than 42 tiles stay with the hand-over, which hides the images under the last
 // slices' work: 56 tiles x 12 stages 16.0 against 15.9 us, 144 x 50 31.1 against 36.4, 108 x 197
 // 71 against 76.  bfloat16 has no hand-over: any output with no more tiles than units, and three
