@@ -30,30 +30,40 @@ OTHERS = ["cfg1_single_512x768x768", "cfg2_vitb_fc1", "cfg3_vitb_block_b256", "c
 STRATEGY = {"auto": 0, "separate": 1, "shared": 2, "unfused": 3}
 
 
-def stage_model(L, O, I, n, r, gx_bits, per_token, gw_bits=8, Lr=None):
+def stage_model(L, O, I, n, r, gx_bits, per_token, gw_bits=8, Lr=None, roles=()):
     """Algorithmic work per launch of every kernel role: HBM bytes for the
-    transform/quantise kernels, operations and compulsory bytes for the GEMMs."""
+    transform/quantise kernels, operations and compulsory bytes for the GEMMs.  `roles`: those the
+    layer launched; a shared operand launch also makes the token-direction view of g_y unless
+    another one does, and leaves the rows' codes to a second pass with one scale per tensor."""
     Lr = L // n * r if Lr is None else Lr
     cb = gx_bits / 8.0
     wb = gw_bits / 8.0
+    gw_peak = BF16_PEAK_TOPS if gw_bits == 16 else INT8_PEAK_TOPS
+    gx_ops, gw_ops = 2 * L * O * I, 2 * O * I * Lr
+    shared = 4 * L * O + 4 * O * I + cb * O * I
+    if per_token:
+        shared += cb * L * O + 4 * L
+    if "w_and_gy_row_quant" in roles and not {"gyT_col_quant", "gy_fused_quant"} & set(roles):
+        shared += wb * Lr * O
     return {
         "act_col_absmax": dict(bytes=4 * L * I),
         "act_col_quant": dict(bytes=4 * L * I + wb * Lr * I),
         "w_col_absmax": dict(bytes=4 * O * I),
         "w_col_quant": dict(bytes=4 * O * I + cb * O * I),
         "gy_row_quant": dict(bytes=4 * L * O + cb * L * O + 4 * L),
-        "w_and_gy_row_quant": dict(bytes=4 * L * O + cb * L * O + 4 * L + 4 * O * I + cb * O * I),
+        "w_and_gy_row_quant": dict(bytes=shared),
         "gy_row_absmax": dict(bytes=4 * L * O),
         "gy_row_quant2": dict(bytes=4 * L * O + cb * L * O),
         "gyT_col_absmax": dict(bytes=4 * L * O),
         "gyT_col_quant": dict(bytes=4 * L * O + wb * Lr * O),
         "gy_fused_absmax": dict(bytes=4 * L * O + (4 * L * ((O + 127) // 128) if per_token else 0)),
         "gy_fused_quant": dict(bytes=4 * L * O + cb * L * O + Lr * O + 4 * L),
-        "gx_igemm": dict(ops=2 * L * O * I, bytes=cb * (L * O + I * O) + 4 * L * I, peak=INT8_PEAK_TOPS),
-        "gx_and_gw_igemm": dict(ops=2 * L * O * I + 2 * O * I * Lr, peak=INT8_PEAK_TOPS,
+        "gx_igemm": dict(ops=gx_ops, bytes=cb * (L * O + I * O) + 4 * L * I, peak=INT8_PEAK_TOPS),
+        # each GEMM's operations at its own operand type's peak
+        "gx_and_gw_igemm": dict(ops=gx_ops + gw_ops,
+                                peak=(gx_ops + gw_ops) / (gx_ops / INT8_PEAK_TOPS + gw_ops / gw_peak),
                                 bytes=cb * (L * O + I * O) + 4 * L * I + wb * Lr * (O + I) + 4 * O * I),
-        "gw_igemm": dict(ops=2 * O * I * Lr, bytes=wb * Lr * (O + I) + 4 * O * I,
-                         peak=BF16_PEAK_TOPS if gw_bits == 16 else INT8_PEAK_TOPS),
+        "gw_igemm": dict(ops=gw_ops, bytes=wb * Lr * (O + I) + 4 * O * I, peak=gw_peak),
     }
 
 
@@ -75,11 +85,26 @@ def kernel_entry(mdl, avg_us, launches_per_step):
         k["bound"] = "mfma" if t_mfma >= t_hbm else "hbm"
         k["frac"] = round(max(t_mfma, t_hbm) / t, 4)
         k["frac_mfma"] = round(t_mfma / t, 4)
-        k["peak_TOPS"] = mdl["peak"]
+        k["peak_TOPS"] = round(mdl["peak"], 1)
     else:
         k["bound"] = "hbm"
         k["frac"] = round(k["GBps"] / HBM_PEAK_GBS, 4)
     return k
+
+
+def brief_line(out):
+    """The line of a run over all workloads, cut to what a reader of one line of a log needs (a tenth
+    of its tables' length): microseconds and share of the bound of every kernel, and of the other
+    workloads their figures."""
+    def kernels(table):
+        return {k: [v["avg_us"], v.get("frac")] for k, v in table.items()}
+    out["kernels"] = kernels(out["kernels"])
+    out["kernels_columns"] = ["avg_us", "frac"]
+    del out["launch_sequence"]
+    for name, res in out["workloads"].items():
+        keep = {k: v for k, v in res.items() if isinstance(v, (int, float, bool))}
+        keep["kernels"] = kernels(res["kernels"])
+        out["workloads"][name] = keep
 
 
 def profiled_traffic(workload, key):
@@ -233,7 +258,7 @@ class Job:
         for (lname, role), (ms, cnt) in acc.items():
             l, quant = shapes[lname]
             mdl = stage_model(l.L, l.O, l.I, cfg.block, cfg.keep, cfg.gx_bits, quant == "token", cfg.gw_bits,
-                              cfg.reduced_tokens(l.L)).get(role)
+                              cfg.reduced_tokens(l.L), {r for (ln, r) in acc if ln == lname}).get(role)
             e = kernel_entry(mdl, ms * 1e3 / cnt, cnt / steps)
             e["step_us"] = round(ms * 1e3 / steps, 1)
             if mdl:
@@ -535,6 +560,8 @@ def main() -> int:
     ap.add_argument("--sweep", action="store_true",
                     help="instead of the timed steps, run the streamed form of one step (inputs generated "
                          "layer by layer) and print per-layer times, buffer bytes and peak memory as JSON")
+    ap.add_argument("--full", action="store_true",
+                    help="with all workloads: every table of each in the line (about 25 KB)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain device copy of 154.9 MB (for scaling rocprofv3 byte counters)")
     args = ap.parse_args()
@@ -609,6 +636,8 @@ def main() -> int:
         out["graph_replay_us_per_step"] = head["graph_replay_us_per_step"]
     if others:
         out["workloads"] = others
+        if not args.full:
+            brief_line(out)
     print(json.dumps(out))
     return 0
 
