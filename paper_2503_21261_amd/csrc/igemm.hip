@@ -401,9 +401,8 @@ hipError_t launch_pair_tile(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, 
 
 namespace {
 
-// Whether g_x (plan of its own: `own`) gains from a place in g_w's launch, where its tiles are 128
-// rows high and do the whole K; `tiles` of them, `together` with all of g_w's workgroups resident at
-// once.  Two things are given up:
+// Whether g_x gains from a place in g_w's launch, where its tiles are 128 rows high and do the whole
+// K; `tiles` of them, `together` with all of g_w's workgroups resident at once.  Two things are given up:
 //  - a split of K.  A tile alone then goes through K stage by stage, 0.2-0.6 us each, while the split
 //    cost one hand-over: shared launches win while K is short, longer where the split already put
 //    two workgroups on a unit (they slow each other down), shorter on 128x256 tiles, and where g_w's
@@ -417,9 +416,12 @@ namespace {
 //    286 us apart, 297 together; 8192 tokens 146 and 134).  Split in two it is the slower one all the
 //    same, in three and more the faster (128 tokens 40960 x 512 288 us apart, 251 together; 65536 x 512
 //    321 and 406).
-bool shares_g_w_launch(const GemmPlan& own, const GemmCall& c, const GemmPlan& w, int64_t tiles, bool wide, bool together) {
+bool shares_g_w_launch(const GemmCall& c, const GemmPlan& w, int64_t tiles, bool wide, bool together) {
+  const int64_t stages = c.k_bytes / (c.bits == 4 ? 64 : 128);
+  if (c.bits == 4 && stages <= 28) return true;   // whatever its own plan is: below every line
+  const GemmPlan own = plan_gemm(c.M, c.N, c.k_bytes, c.bits, true, false);
   const int cus = compute_units();
-  const int64_t stages = c.k_bytes / own.bkb, workgroups = own.tiles * own.split;
+  const int64_t workgroups = own.tiles * own.split;
   if (own.bm == 256 && own.split == 1 && c.bits == 8)
     return (double)tiles / cus * tile_mops(kCands8[0], (double)c.k_bytes) * 0.16 <
            tile_shape_us(kCands8[1], c.M, c.N, (double)c.k_bytes, cus);
@@ -454,8 +456,7 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   const bool int4 = cx.bits == 4, narrow = w + x128 <= (int4 ? cap : most);
   if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
   const int64_t x = narrow ? x128 : x256;
-  if (!shares_g_w_launch(plan_gemm(cx.M, cx.N, cx.k_bytes, cx.bits, true, false), cx, p, x, !narrow, w + x <= cap))
-    return hipSuccess;
+  if (!shares_g_w_launch(cx, p, x, !narrow, w + x <= cap)) return hipSuccess;
   GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
