@@ -192,7 +192,8 @@ hot_status hot_linear_backward_gw(const hot_config* cfg, const float* g_y, const
  * hot_linear_backward_gw.  Where it is faster (16-row blocks and a g_y too large for the
  * single-pass token-direction kernel) the two quantised views of g_y (rotated along O,
  * and HLA-compressed along L) come out of shared reads of g_y: two passes over it instead
- * of three; otherwise the two separate paths run one after the other.
+ * of three; otherwise each path makes its own, in one launch for small layers.  Both GEMMs run
+ * behind the operands, in one launch where that is faster.
  * Arguments as for the two separate calls.  Requires O % n == 0 and L % n == 0
  * (or whole samples with sample_tokens).
  */
@@ -264,11 +265,12 @@ hot_status hot_debug_fused_operands(const hot_config* cfg, void* ws, const void*
                                     float* w_scale, int32_t* acc_gx, int8_t* gyT_codes,
                                     float* gyT_scale, int32_t* acc_gw, void* stream);
 
-/* Strategy of hot_linear_backward: 0 = chosen by the library (default), 1 = always the two
- * separate paths, 2 = the shared passes over g_y whenever they exist (block sizes 16 and
- * 32, INT8 g_w operands, one run of tokens), 3 = the separate paths with every kernel in a
- * launch of its own (by default the g_x path quantises small weights and the per-token g_y
- * operand in one combined launch; the setting also applies to hot_linear_backward_gx).
+/* Strategy of hot_linear_backward: 0 = chosen by the library (default), 1 = never the shared
+ * passes over g_y, 2 = the shared passes whenever they exist (block sizes 16 and
+ * 32, INT8 g_w operands, one run of tokens), 3 = as 1 with every kernel in a launch of its own
+ * (by default small layers have their operands made in one launch, weights and per-token g_y rows
+ * of larger ones in another, and both GEMMs share a launch where that is faster; the setting also
+ * applies to hot_linear_backward_gx).
  * Results do not depend on it.  Process-wide. */
 hot_status hot_debug_set_backward_strategy(int strategy);
 
