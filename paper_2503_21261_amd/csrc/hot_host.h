@@ -217,8 +217,8 @@ hipError_t launch_w_and_rows(const float* w, int64_t O, int64_t I, const Config&
                              int64_t pitch, float* s_w, float* slots, const float* g_y, int64_t L,
                              uint8_t* qg, float* s_g, hipStream_t s, int stage, bool* done);
 
-// All three operands of a small layer in one launch (INT8 g_w, O up to 4096, both column jobs'
-// workgroups resident at once): those of launch_w_and_rows and the token-direction view of g_y
+// All three operands of a small layer in one launch (INT8 g_w, O up to 4096, a g_y that gains by it,
+// both column jobs' workgroups resident at once): those of launch_w_and_rows and the token-direction view of g_y
 // ([O x pitch_h] codes, *s_gh); or, where that view does not fit or is bfloat16, the first two (`*made` = kOperandsOfGx)
 // unless launch_w_and_rows is made for them.  With one g_y scale per tensor the rows' part is the abs-max pass only:
 // row_partials[0 .. *npartials), for mode 2 of launch_row_quant.  slots_*: kMaxPartials floats each;
@@ -251,8 +251,9 @@ struct GemmCall {
   const unsigned long long* epoch;
 };
 hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage = -1);
-// Both GEMMs of a layer in one launch, up to a few thousand workgroups together: `w` with its
-// own plan on 128x128 tiles, `x` on unsplit tiles.  *done says whether the launch was made.
+// Both GEMMs of a layer in one launch, up to a few thousand workgroups together and where `x` gains by
+// it: `w` with its own plan on 128x128 tiles, `x` on unsplit tiles.  *done says whether the launch was
+// made.
 hipError_t launch_gemm_pair(const GemmCall& w, bool images, const GemmCall& x, hipStream_t s, int stage, bool* done);
 
 // Unpack K-contiguous codes [rows x pitch] into one int8 per code.
