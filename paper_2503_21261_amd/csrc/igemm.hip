@@ -408,8 +408,9 @@ namespace {
 //    two workgroups on a unit (they slow each other down), shorter on 128x256 tiles, and where g_w's
 //    own hand-overs, which run beside g_x's stages, take long.  Stages of both sides' equality over
 //    1990 layers of 64 to 32768 tokens, 64 to 8192 inputs and 1024 to 32768 outputs: 40-48 / 60-72 for
-//    INT8 and INT4 on 128x128 tiles, 28-32 / 48 on 128x256, and 32-40 for g_x of 65 to 256 tiles behind
-//    more workgroups than are resident (512 tokens 16384 x 768 93 us apart, 145 together; 1024 tokens
+//    INT8 and INT4 on 128x128 tiles, 28-32 / 48 on 128x256, and behind more workgroups than are resident
+//    32-40 for g_x of 65 to 255 tiles, about 64 for 256 INT8 ones (1024 tokens 5120 x 4096 111 us apart, 97
+//    together; 512 tokens 16384 x 768 93 us apart, 145 together; 1024 tokens
 //    4096 x 512 46 and 34).
 //  - the eight-wave 256x256 INT8 tile.  Against the cost model's time for that one, 128x128 tiles
 //    price at 0.16 us per million operations and unit in this company (16384 tokens 4096 x 1024
@@ -429,8 +430,9 @@ bool shares_g_w_launch(const GemmCall& c, const GemmPlan& w, int64_t tiles, bool
   if (own.bm != 128) return true;   // measured faster in every case
   if (own.split > 1) {
     if (workgroups <= cus) return stages <= (wide ? 28 : 40) + (together && w.split > 1 ? 24 : 0);
-    if (together) return stages <= (wide ? 48 : 64);
-    return stages <= (own.tiles > cus / 4 ? 32 : (wide ? 48 : 56));
+    if (together) return stages <= (wide ? 48 : 72);
+    if (own.tiles <= cus / 4) return stages <= (wide ? 48 : 56);
+    return stages <= (own.tiles == cus && !wide ? 64 : 32);   // 256 tiles in two: every unit has two workgroups
   }
   return together || !wide || own.tiles > cus || stages <= 40;   // one tile per unit against two
 }

@@ -1157,6 +1157,8 @@ def backward_stages(hot, cfg, gy, w, act, q, ws):
     (512, 11008, 1024, 4, False),    # 128x256 tiles behind 688 g_w tiles
     (2048, 4096, 512, 8, True),      # 32 stages on 64 tiles
     (512, 16384, 256, 8, False),
+    (1024, 5120, 4096, 8, True),     # 40 stages on 256 tiles, split in two on its own
+    (1024, 5120, 2048, 8, False),    # on 128 tiles, split in four
     (12800, 4096, 1024, 8, False),   # the 256x256 INT8 tile
     (4096, 1024, 4096, 8, True),     # the same tile, a short K
     (128, 32768, 128, 8, True),      # the same tile, split in two
