@@ -132,19 +132,14 @@ class Config:
         return L // self.block * self.keep
 
     def c(self) -> hot_config:
-        cfg = hot_config()
-        cfg.block, cfg.keep = int(self.block), int(self.keep)
-        cfg.gx_bits, cfg.gw_bits = int(self.gx_bits), int(self.gw_bits)
-        cfg.rounding, cfg.lqs_threshold = int(self.rounding), float(self.lqs_threshold)
-        cfg.sample_tokens = int(self.sample_tokens)
-        cfg.replayable = 1 if self.replayable else 0
-        if self.keep_idx is None:
-            cfg.keep_idx = None
-            self._keep_arr = None
-        else:
+        keep_idx = None
+        self._keep_arr = None
+        if self.keep_idx is not None:
             self._keep_arr = (C.c_int32 * len(self.keep_idx))(*[int(k) for k in self.keep_idx])
-            cfg.keep_idx = C.cast(self._keep_arr, C.POINTER(C.c_int32))
-        return cfg
+            keep_idx = C.cast(self._keep_arr, C.POINTER(C.c_int32))
+        return hot_config(int(self.block), int(self.keep), keep_idx, int(self.gx_bits), int(self.gw_bits),
+                          int(self.rounding), float(self.lqs_threshold), int(self.sample_tokens),
+                          1 if self.replayable else 0)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -152,8 +147,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:   # the handle alone: a Stream object of it costs a call over a microsecond
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     return stream.cuda_stream or None
 
 
@@ -163,7 +158,7 @@ def _check(status: int, where: str) -> None:
 
 
 def _dev_f32(t: torch.Tensor, shape: Tuple[int, ...], name: str) -> None:
-    if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and tuple(t.shape) == shape):
+    if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and t.shape == shape):
         raise ValueError(f"{name}: expected contiguous float32 device tensor of shape {shape}")
 
 

@@ -36,15 +36,6 @@ __device__ __forceinline__ void unpack_vec(const typename VecT<VEC>::type& q, fl
   else { o[0] = q.x; o[1] = q.y; o[2] = q.z; o[3] = q.w; }
 }
 
-// Natural-order index of the row of H_n with j sign changes: bit-reversed Gray code.
-__host__ __device__ constexpr int lowpass_row(int n, int j) {
-  const int g = j ^ (j >> 1);
-  int r = 0;
-  for (int b = 1, t = n >> 1; b < n; b <<= 1, t >>= 1)
-    if (g & b) r |= t;
-  return r;
-}
-
 template <int N>
 __host__ __device__ constexpr int lp_l1_row(int j) {
   constexpr LpL1Rows<N> t;

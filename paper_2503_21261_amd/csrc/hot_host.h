@@ -12,6 +12,15 @@ namespace hot {
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Natural-order index of the row of H_n with j sign changes: bit-reversed Gray code.
+__host__ __device__ constexpr int lowpass_row(int n, int j) {
+  const int g = j ^ (j >> 1);
+  int r = 0;
+  for (int b = 1, t = n >> 1; b < n; b <<= 1, t >>= 1)
+    if (g & b) r |= t;
+  return r;
+}
+
 // The first half of the LP_L1 list (the order hot_lowpass_l1_rows states) as a compile-time table.
 template <int N>
 struct LpL1Rows {
