@@ -276,6 +276,14 @@ int slice_placement(const GemmArgs& g, int64_t tiles) {
   return cols;
 }
 
+// GemmArgs' split of nk_total stages into `split` slices.
+void set_slices(GemmArgs& g, int split) {
+  g.split = split;
+  g.slice_stages = g.nk_total / split;
+  g.slice_rest = g.nk_total % split;
+  g.slice_inverse = (1u << 20) / (unsigned)split + 1;   // exact for split <= 64
+}
+
 // What a hand-over launch needs beyond the tile grid: its tag, placement and bounded wait.
 template <int BM>
 hipError_t prepare_hand_over(GemmArgs& g, int64_t k_bytes, bool int4) {
@@ -298,7 +306,7 @@ hipError_t launch_tile(GemmArgs g, int64_t k_bytes, const GemmPlan& plan, hipStr
   g.nk_total = (int)(k_bytes / BKB);
   g.tiles_m = (int)ceil_div(g.M, BM);
   g.tiles_n = (int)ceil_div(g.N, BN);
-  g.split = split;
+  set_slices(g, split);
   const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
   if (split <= 1) return launch_kernel<BM, BN, BKB, INT4, BF16, kWholeK>(g, (unsigned)tiles, s, gemm_stage);
   if constexpr (BM == 128 && BN == 128 && !INT4) {
@@ -463,7 +471,7 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
   gw.tiles_n = (int)ceil_div(cw.N, 128);
-  gw.split = p.split;
+  set_slices(gw, p.split);
   if (p.images) {
     if (!gw.partial) return hipErrorInvalidValue;
     gw.xcd_cols = p.split % 8 == 0 ? -2 : slice_placement<128>(gw, p.tiles);
@@ -474,7 +482,7 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   gx.nk_total = (int)(cx.k_bytes / (int4 ? 64 : 128));
   gx.tiles_m = (int)rows;
   gx.tiles_n = (int)ceil_div(cx.N, narrow ? 128 : 256);
-  gx.split = 1;
+  set_slices(gx, 1);
   stage_begin(stage, s);
   const hipError_t e = !narrow ? launch_pair_tile<256, true>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s)
                        : int4  ? launch_pair_tile<128, true>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s)
