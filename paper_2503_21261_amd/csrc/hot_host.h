@@ -107,8 +107,9 @@ struct GemmPlan {
   size_t partial_bytes;   // split > 1: tiles * (split - 1, or split with `images`) * bm * bn int32
 };
 // `scratch`: a region of gemm_scratch_bytes() and the workspace's flag slots are available,
-// so K may be split; `images`: a region of image_scratch_bytes() is.
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images);
+// so K may be split; `images`: a region of image_scratch_bytes() is; `beside`: the other gradient's
+// workgroups follow in the same launch.
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images, bool beside = false);
 size_t image_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits);
 // Upper bound of partial_bytes over every plan of this shape (whatever mode is forced).
 size_t gemm_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits);

@@ -76,9 +76,7 @@ int64_t max_split(int64_t tiles, int64_t nk) {
 // K split of the 256x256 INT8 tile (eight waves, one workgroup per compute unit) for an output
 // of at most one such tile per unit: as many slices as there are units per tile, and only when
 // a slice keeps at least 16 KB of K, so that the 256 KB accumulator images the owner collects
-// are a small part of the work.  Measured: ViT-L fc1 g_w (64 tiles, K = 100864, 4 slices) 396 us
-// against 483 us with 128x128 tiles in 2 slices; with 3152-byte slices (ViT-B qkv) 88 against
-// 79 us, so short K stays on the small tile.  0: does not apply.
+// are a small part of the work.  0: does not apply.  Chosen against 128x128 tiles by cost (plan_gemm).
 int64_t large_tile_split(int64_t M, int64_t N, int64_t k_bytes, int bits, int cus) {
   if (bits != 8) return 0;
   const int64_t tiles = ceil_div(M, 256) * ceil_div(N, 256);
@@ -88,6 +86,34 @@ int64_t large_tile_split(int64_t M, int64_t N, int64_t k_bytes, int bits, int cu
   while (s > 1 && (k_bytes / s < 16384 || tiles * (s - 1) > kMaxSplitSlots)) --s;
   return s >= 2 ? s : 0;
 }
+// Time of a hand-over split of 128x128 tiles in us but for what does not depend on the split: the
+// stages of a slice, at another rate while no unit has two workgroups, and the hand-over (the flags, the
+// images an owner adds, and the images' traffic when all units write and read them).  Fitted to g_w and
+// g_x GEMMs of 1200 layers, every split from 1 to 8 timed on each (512 to 200000 tokens, 43 to 512
+// tiles, 8 to 800 stages); the split chosen by it takes 0.7-1.3 % longer than the best one on average.  As many
+// slices as keep all workgroups resident, the rule before, took 17-31 % longer: 9840 tokens 832 x 1184 (70
+// tiles, 39 stages) 34 us in 3 slices, 38 in 7; g_x of 1005 tokens 1024 x 2544 in INT8 12 us whole, 21 in 2;
+// 64 tiles x 96 stages 28 us in 3, 44 in 8.
+struct SplitCost { double stage, stage_two, split, slice, resident; };
+constexpr SplitCost kSplit4{0.48, 0.69, 3.0, 0.84, 6.5};
+constexpr SplitCost kSplit8{0.54, 0.92, 2.3, 1.0, 5.0};
+// g_w behind whose workgroups g_x waits for places, so that their number counts more (640 layers, 2.6 %
+// above the best split; 22 % with the rule before)
+constexpr SplitCost kSplitBeside{0.54, 1.25, 0.0, 0.85, 15.3};
+double split_us(const SplitCost& c, int64_t tiles, int64_t stages, int64_t s, int cus) {
+  const int64_t wgs = tiles * s;
+  const double t = (double)ceil_div(stages, s) * (wgs <= cus ? c.stage : c.stage_two);
+  return s == 1 ? t : t + c.split + c.slice * (double)(s - 1) + c.resident * (double)wgs / (2.0 * cus);
+}
+int64_t best_split(const SplitCost& c, int64_t tiles, int64_t stages, int64_t most, int cus) {
+  int64_t best = 1;
+  for (int64_t s = 2; s <= most && tiles * s <= 2 * (int64_t)cus; ++s)
+    if (split_us(c, tiles, stages, s, cus) < split_us(c, tiles, stages, best, cus)) best = s;
+  return best;
+}
+// The same for 256x256 INT8 tiles in `s` slices (260 layers): 110224 tokens 512 x 4416 (140 tiles of
+// 128x128) 192 us in 3 slices on the large tile, 152 in 4 on the small one; 112928 x 1536 x 1952 209 and 242.
+double large_split_us(int64_t stages, int64_t s) { return 1.25 * (double)ceil_div(stages, s) + 6.75 * (double)(s - 1) - 8.1; }
 // Cost of a tile shape, fitted to measurements on MI355X (ten layer shapes from 512 to 201728
 // tokens, every INT4 tile timed on each; within 4 % of the measured time, and the measured
 // best tile or one within 2 % of it on all ten): a compute unit works through its share of
@@ -137,7 +163,7 @@ int64_t image_slices(int64_t M, int64_t N, int64_t k_bytes, int bits, int cus) {
 void set_gemm_mode(int mode) { g_gemm_mode.store(mode); }
 void set_gemm_wait_us(int us) { g_gemm_wait_us.store(us); }
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images, bool beside) {
   const Cand* cands = bits == 4 ? kCands4 : kCands8;
   const int ncand = bits == 4 ? 4 : 2;
   const double K = (double)k_bytes * (bits == 4 ? 2 : 1);
@@ -162,7 +188,10 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
   // the mode, so that its bits do too; without images one workgroup sums them in their order
   if (bits == 16) images = images && mode == 0;
   if ((images && mode == 0) || bits == 16) {
-    const int64_t s = image_slices(M, N, k_bytes, bits, cus);
+    // beside g_x the second kernel is one launch more, which pays up to 16 tiles (13-16 tiles: 5 % above the
+    // best choice either way, 33-42: 19 % with images and 5 without)
+    const bool pays = bits == 16 || !beside || ceil_div(M, 128) * ceil_div(N, 128) <= cus / 16;
+    const int64_t s = pays ? image_slices(M, N, k_bytes, bits, cus) : 0;
     if (s) {
       p.bm = p.bn = 128;
       p.tiles = ceil_div(M, 128) * ceil_div(N, 128);
@@ -180,26 +209,29 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
     p.tiles = ceil_div(M, p.bm) * ceil_div(N, p.bn);
     return p;
   }
-  if (scratch && mode == 0) {
-    const int64_t s = large_tile_split(M, N, k_bytes, bits, cus);
-    if (s) {
+  if (bits == 16 || !scratch) return p;
+  const SplitCost& cost = bits == 4 ? kSplit4 : (beside ? kSplitBeside : kSplit8);
+  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), nk = k_bytes / p.bkb, most = max_split(tiles, nk);
+  if (mode == 0) {
+    const int64_t l = large_tile_split(M, N, k_bytes, bits, cus);
+    if (l) {
       p.bm = p.bn = 256;
-      p.tiles = ceil_div(M, 256) * ceil_div(N, 256);
-      p.split = (int)s;
-      p.partial_bytes = (size_t)p.tiles * (s - 1) * 256 * 256 * 4;
-      return p;
+      if (tiles <= 2 * (int64_t)cus &&
+          split_us(cost, tiles, nk, best_split(cost, tiles, nk, most, cus), cus) <= large_split_us(nk, l))
+        p.bm = p.bn = 128;
+      p.tiles = ceil_div(M, p.bm) * ceil_div(N, p.bn);
+      if (p.bm == 256) {
+        p.split = (int)l;
+        p.partial_bytes = (size_t)p.tiles * (l - 1) * 256 * 256 * 4;
+        return p;
+      }
     }
   }
-  if (scratch && bits != 16 && p.bm == 128 && p.bn == 128 && mode != 1) {
-    const int64_t nk = k_bytes / p.bkb, most = max_split(p.tiles, nk);
-    // measured on MI355X (128x128 INT8 tiles, K of 50-200 stages): fastest with as many slices
-    // as keep all workgroups resident at once, two per compute unit; a partial second round
-    // costs more than the shorter slices gain
-    int64_t s = mode >= 2 ? mode : (p.tiles <= cus ? 2 * cus / p.tiles : 1);
-    if (s > most) s = most;
+  if (p.bm == 128 && p.bn == 128 && mode != 1) {
+    const int64_t s = mode >= 2 ? (mode < most ? mode : most) : best_split(cost, tiles, nk, most, cus);
     if (s >= 2) {
       p.split = (int)s;
-      p.partial_bytes = (size_t)p.tiles * (s - 1) * 128 * 128 * 4;
+      p.partial_bytes = (size_t)tiles * (s - 1) * 128 * 128 * 4;
     }
   }
   return p;
@@ -413,8 +445,8 @@ namespace {
 // K; `tiles` of them, `together` with all of g_w's workgroups resident at once.  Two things are given up:
 //  - a split of K.  A tile alone then goes through K stage by stage, 0.2-0.6 us each, while the split
 //    cost one hand-over: shared launches win while K is short, longer where the split already put
-//    two workgroups on a unit (they slow each other down), shorter on 128x256 tiles, and where g_w's
-//    own hand-overs, which run beside g_x's stages, take long.  Stages of both sides' equality over
+//    two workgroups on a unit (they slow each other down), shorter on 128x256 tiles, and longer where
+//    g_w's own K, which runs beside g_x's stages, is long.  Stages of both sides' equality over
 //    1990 layers of 64 to 32768 tokens, 64 to 8192 inputs and 1024 to 32768 outputs: 40-48 / 60-72 for
 //    INT8 and INT4 on 128x128 tiles, 28-32 / 48 on 128x256, and behind more workgroups than are resident
 //    32-40 for g_x of 65 to 255 tiles, about 64 for 256 INT8 ones (1024 tokens 5120 x 4096 111 us apart, 97
@@ -425,19 +457,23 @@ namespace {
 //    286 us apart, 297 together; 8192 tokens 146 and 134).  Split in two it is the slower one all the
 //    same, in three and more the faster (128 tokens 40960 x 512 288 us apart, 251 together; 65536 x 512
 //    321 and 406).
-bool shares_g_w_launch(const GemmCall& c, const GemmPlan& w, int64_t tiles, bool wide, bool together) {
+bool shares_g_w_launch(const GemmCall& c, bool w_long, int64_t tiles, bool wide, bool together) {
   const int64_t stages = c.k_bytes / (c.bits == 4 ? 64 : 128);
   if (c.bits == 4 && stages <= 28) return true;   // whatever its own plan is: below every line
-  const GemmPlan own = plan_gemm(c.M, c.N, c.k_bytes, c.bits, true, false);
+  // what g_x would take on its own, its split given as the most slices that are resident at once
+  const GemmPlan own = plan_gemm(c.M, c.N, c.k_bytes, c.bits, false, false);
   const int cus = compute_units();
-  const int64_t workgroups = own.tiles * own.split;
-  if (own.bm == 256 && own.split == 1 && c.bits == 8)
+  const int64_t large = large_tile_split(c.M, c.N, c.k_bytes, c.bits, cus);
+  if (large) return large == 2;
+  if (own.bm == 256 && c.bits == 8)
     return (double)tiles / cus * tile_mops(kCands8[0], (double)c.k_bytes) * 0.16 <
            tile_shape_us(kCands8[1], c.M, c.N, (double)c.k_bytes, cus);
-  if (own.bm == 256 && c.bits == 8) return own.split == 2;
   if (own.bm != 128) return true;   // measured faster in every case
-  if (own.split > 1) {
-    if (workgroups <= cus) return stages <= (wide ? 28 : 40) + (together && w.split > 1 ? 24 : 0);
+  int64_t slices = own.bn == 128 && own.tiles <= cus ? 2 * cus / own.tiles : 1;
+  const int64_t most = max_split(own.tiles, stages);
+  slices = slices < most ? slices : most;
+  if (slices > 1) {
+    if (own.tiles * slices <= cus) return stages <= (wide ? 28 : 40) + (together && w_long ? 24 : 0);
     if (together) return stages <= (wide ? 48 : 72);
     if (own.tiles <= cus / 4) return stages <= (wide ? 48 : 56);
     return stages <= (own.tiles == cus && !wide ? 64 : 32);   // 256 tiles in two: every unit has two workgroups
@@ -450,7 +486,7 @@ bool shares_g_w_launch(const GemmCall& c, const GemmPlan& w, int64_t tiles, bool
 hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, hipStream_t s, int stage, bool* done) {
   *done = false;
   if (g_gemm_mode.load() != 0 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
-  const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images);
+  const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images, true);
   if (p.bm != 128 || p.bn != 128) return hipSuccess;
   if (cw.bits == 16 && p.split > 1 && !p.images) return hipSuccess;
   const int64_t w = p.tiles * p.split, cap = 2 * (int64_t)compute_units();
@@ -466,7 +502,9 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
   const bool int4 = cx.bits == 4, narrow = w + x128 <= (int4 ? cap : most);
   if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
   const int64_t x = narrow ? x128 : x256;
-  if (!shares_g_w_launch(cx, p, x, !narrow, w + x <= cap)) return hipSuccess;
+  // g_w's K long enough to run beside g_x's stages (INT8: two slices of four stages)
+  const bool w_long = cw.bits == 16 ? p.split > 1 : cw.k_bytes >= 1024 && p.tiles <= compute_units();
+  if (!shares_g_w_launch(cx, w_long, x, !narrow, w + x <= cap)) return hipSuccess;
   GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
