@@ -389,8 +389,11 @@ GemmArgs gemm_args(const GemmCall& c) {
   g.xcd_cols = 0;
   // measured on MI355X: streaming stores win for INT8 / bfloat16 operands and for INT4 GEMMs of
   // up to 3072 codes of K (ViT-B fc2 at 50432 tokens 167 -> 134 us, ViT-B fc1 at 12608 tokens
-  // 44.5 -> 39.6 us), and lose 3 % at 4096 codes and a wide output (LLM down-projection)
-  g.stream_out = (c.bits != 4 || c.k_bytes * 2 <= 3072) ? 1 : 0;
+  // 44.5 -> 39.6 us), and lose 3 % at 4096 codes and a wide output (LLM down-projection).  Only where output
+  // rows are whole 64-byte sectors: a sector that two stores share goes out in parts with the hint (11744
+  // tokens 256 x 3079 75.8 us with it, 30.9 without; 4544 x 128 x 8862 70.1 and 33.2; of whole sectors 37627 x
+  // 256 x 1584 103 and 122, 20000 x 512 x 1008 22.6 and 23.8).
+  g.stream_out = (c.bits != 4 || c.k_bytes * 2 <= 3072) && c.N % 16 == 0 ? 1 : 0;
   return g;
 }
 
