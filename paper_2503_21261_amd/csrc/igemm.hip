@@ -114,16 +114,17 @@ int64_t best_split(const SplitCost& c, int64_t tiles, int64_t stages, int64_t mo
 // The same for 256x256 INT8 tiles in `s` slices (260 layers): 110224 tokens 512 x 4416 (140 tiles of
 // 128x128) 192 us in 3 slices on the large tile, 152 in 4 on the small one; 112928 x 1536 x 1952 209 and 242.
 double large_split_us(int64_t stages, int64_t s) { return 1.25 * (double)ceil_div(stages, s) + 6.75 * (double)(s - 1) - 8.1; }
-// Cost of a tile shape, fitted to measurements on MI355X (ten layer shapes from 512 to 201728
-// tokens, every INT4 tile timed on each; within 4 % of the measured time, and the measured
-// best tile or one within 2 % of it on all ten): a compute unit works through its share of
+// Cost of a tile shape, fitted to measurements on MI355X: a compute unit works through its share of
 // the tiles, each costing its operations at the rate the tile sustains plus its output bytes
 // at the rate its stores drain, plus a constant per launch.  The share is a whole number of
 // tiles while the resident workgroups (wgs per unit) take them in a few rounds, the last of
 // which idles units, and averages out over many rounds.
 struct Cand { int bm, bn, wgs; double us_per_mop, us_per_kb, us_launch; };
-constexpr Cand kCands4[] = {{128, 128, 3, 0.0979, 0.0324, 4.3}, {128, 256, 2, 0.0880, 0.0310, 3.6},
-                            {192, 256, 1, 0.0860, 0.0392, 5.6}, {256, 256, 1, 0.0821, 0.0385, 0.0}};
+// The INT4 constants are fitted to 414 layers of 512 to 200000 tokens and 64 to 11008 outputs and inputs, all four
+// tiles timed on each: the choice takes 0.9 % longer than the best tile on average (2.6 % with constants
+// from ten layers, 36 % at worst: 35372 tokens 1152 x 576 35.1 us, 39.0 on 128x256 tiles).
+constexpr Cand kCands4[] = {{128, 128, 3, 0.0978, 0.0289, 4.6}, {128, 256, 2, 0.0882, 0.0291, 3.3},
+                            {192, 256, 1, 0.0910, 0.0405, 3.8}, {256, 256, 1, 0.0827, 0.0431, 2.3}};
 constexpr Cand kCands8[] = {{128, 128, 2, 0.2560, 0.0, 0.0}, {256, 256, 1, 0.1004, 0.0476, 0.0}};
 double tile_mops(const Cand& c, double K) { return 2.0 * c.bm * c.bn * K * 1e-6; }
 double tile_shape_us(const Cand& c, int64_t M, int64_t N, double K, int cus) {
