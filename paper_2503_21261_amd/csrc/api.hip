@@ -413,12 +413,12 @@ hot_status gx_gemm(const Config& c, const uint8_t* qw, const float* s_w, int64_t
 // HLA(g_y) along L as [O x L'] code rows at `qg` with its scale at `s_g` (INT8: one scale;
 // bfloat16: no scale, 1 is stored), then the GEMM with the stored activation and dequantise.
 hot_status gw_operand(const Config& c, const float* g_y, int64_t L, int64_t O, uint8_t* qg, int64_t pitch,
-                      float* s_g, float* slots, hipStream_t s) {
+                      float* s_g, float* slots, hipStream_t s, int have_partials = 0) {
   if (c.gw_bits == 16)
     HOT_TRY(launch_col_bf16(g_y, row_tiling(c, L), O, c, qg, pitch, s_g, s, kStGyTQuant));
   else
     HOT_TRY(launch_col_quant(g_y, row_tiling(c, L), O, c, c.r, c.map, false, c.gw_bits, qg, pitch, s_g, slots, s,
-                             kStGyTAbsmax, kStGyTQuant));
+                             kStGyTAbsmax, kStGyTQuant, have_partials));
   return HOT_OK;
 }
 
@@ -590,8 +590,14 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
     float* const s_g = (float*)(base + f.gx.sg);
     float* const rowpart = (float*)(base + f.rowpart);
     OperandsMade made = kOperandsNone;
-    int npart = 0;
-    if (g_backward_strategy.load() != 3)
+    int npart = 0, have = 0;   // partial maxima of the rows, of the token-direction view
+    const bool joined = g_backward_strategy.load() != 3;
+    if (joined && per_token && rows_and_absmax_applies(c, L, O)) {
+      HOT_TRY(launch_col_quant(w, RowTiling{O / c.n, 0, 1}, I, c, c.n, identity_map(c.n), true, c.gx_bits, base + f.gx.qw,
+                               f.gx.pitch, (float*)(base + f.gx.scalars), slots, s, kStWAbsmax, kStWQuant));
+      HOT_TRY(launch_rows_and_absmax(g_y, L, O, c, base + f.gx.qg, f.gx.pitch, s_g, slots2, &have, s, kStGyRowQuant));
+      made = kOperandsOfGx;
+    } else if (joined)
       HOT_TRY(launch_operands(w, O, I, c, base + f.gx.qw, f.gx.pitch, (float*)(base + f.gx.scalars), slots, g_y, L,
                               per_token, base + f.gx.qg, s_g, rowpart, &npart, base + f.qgh, f.gw.pitch,
                               (float*)(base + f.s_gh), slots2, s, kStWGyRow, &made));
@@ -603,7 +609,7 @@ hot_status hot_linear_backward(const hot_config* cfg, const float* g_y, const fl
                                                  s_g, rowpart, &npart, s));
     }
     if (made != kOperandsAll) {
-      st = gw_operand(c, g_y, L, O, base + f.qgh, f.gw.pitch, (float*)(base + f.s_gh), slots, s);
+      st = gw_operand(c, g_y, L, O, base + f.qgh, f.gw.pitch, (float*)(base + f.s_gh), have ? slots2 : slots, s, have);
       if (st != HOT_OK) return st;
     }
     const GemmCall gx = gemm_call(c, base + f.gx.qg, base + f.gx.qw, L, I, f.gx.pitch, c.gx_bits, base, f.partial, nullptr,

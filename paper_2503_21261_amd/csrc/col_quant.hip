@@ -189,8 +189,16 @@ hipError_t launch_onepass(const ColArgs& a, hipStream_t s, int sq, bool* done) {
   return e;
 }
 
+// `have`: partial maxima that another kernel has left already (the quantise pass alone), or 0.
 template <int N, int KIND>
-hipError_t launch_nk(const ColArgs& a, const ColPlan& p, hipStream_t s, int sa, int sq) {
+hipError_t launch_nk(const ColArgs& a, ColPlan p, hipStream_t s, int sa, int sq, int have) {
+  if (have > 0) {
+    p.absmax_grid = have;
+    stage_begin(sq, s);
+    const hipError_t e = launch_quant<N, 1, KIND>(a, p, s);
+    stage_end(sq, s);
+    return e;
+  }
   if (g_exchange_wait_us.load() >= 0) {
     bool done = false;
     const hipError_t e1 = launch_onepass<N, KIND>(a, s, sq, &done);
@@ -212,13 +220,13 @@ hipError_t launch_nk(const ColArgs& a, const ColPlan& p, hipStream_t s, int sa, 
 }
 
 template <int N>
-hipError_t launch_n(const ColArgs& a, const ColPlan& p, hipStream_t s, int sa, int sq) {
+hipError_t launch_n(const ColArgs& a, const ColPlan& p, hipStream_t s, int sa, int sq, int have) {
   switch (p.kind) {
-    case kKeepLowHalf: return launch_nk<N, kKeepLowHalf>(a, p, s, sa, sq);
-    case kKeepLpL1: return launch_nk<N, kKeepLpL1>(a, p, s, sa, sq);
-    case kKeepAll8: return launch_nk<N, kKeepAll8>(a, p, s, sa, sq);
-    case kKeepAll4: return launch_nk<N, kKeepAll4>(a, p, s, sa, sq);
-    default: return launch_nk<N, kKeepGeneric>(a, p, s, sa, sq);
+    case kKeepLowHalf: return launch_nk<N, kKeepLowHalf>(a, p, s, sa, sq, have);
+    case kKeepLpL1: return launch_nk<N, kKeepLpL1>(a, p, s, sa, sq, have);
+    case kKeepAll8: return launch_nk<N, kKeepAll8>(a, p, s, sa, sq, have);
+    case kKeepAll4: return launch_nk<N, kKeepAll4>(a, p, s, sa, sq, have);
+    default: return launch_nk<N, kKeepGeneric>(a, p, s, sa, sq, have);
   }
 }
 
@@ -227,15 +235,15 @@ hipError_t launch_n(const ColArgs& a, const ColPlan& p, hipStream_t s, int sa, i
 hipError_t launch_col_quant(const float* x, const RowTiling& rows, int64_t C, const Config& cfg, int r,
                             const KeepMap& map, bool identity, int bits, uint8_t* codes,
                             int64_t pitch, float* scale, float* partials, hipStream_t s,
-                            int stage_absmax, int stage_quant) {
+                            int stage_absmax, int stage_quant, int have_partials) {
   if (rows.nblk <= 0 || C <= 0) return hipSuccess;
   if (bits == 4 && !(identity && r == cfg.n)) return hipErrorInvalidValue;
   const ColPlan p = plan_col(cfg, rows.nblk, C, r, bits, identity);
   const ColArgs a{x, rows, C, map, r, cfg.rounding, codes, pitch, scale, partials, cfg.epoch};
   switch (cfg.n) {
-    case 16: return launch_n<16>(a, p, s, stage_absmax, stage_quant);
-    case 32: return launch_n<32>(a, p, s, stage_absmax, stage_quant);
-    case 64: return launch_n<64>(a, p, s, stage_absmax, stage_quant);
+    case 16: return launch_n<16>(a, p, s, stage_absmax, stage_quant, have_partials);
+    case 32: return launch_n<32>(a, p, s, stage_absmax, stage_quant, have_partials);
+    case 64: return launch_n<64>(a, p, s, stage_absmax, stage_quant, have_partials);
   }
   return hipErrorInvalidValue;
 }

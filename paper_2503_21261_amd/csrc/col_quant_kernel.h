@@ -345,44 +345,45 @@ __device__ __forceinline__ float workgroup_max(float m) {
   return m;
 }
 
-// Abs-max pass.  Tiles of (4*kbw blocks) x (64*VEC columns) are dealt to a capped
-// grid; partials[blockIdx.x] = the workgroup's maximum over its tiles.
-// Abs-max pass.  The four waves of a workgroup take adjacent column stripes of the same
-// blocks, so a row of the workgroup's tile is 4 * 64 * VEC consecutive floats requested at
-// about the same time (longer runs per DRAM page than four waves on four different row
-// blocks: 6.0 against 5.3 TB/s on a 721 MB tensor when the kernel runs alone, 152 against
-// 157 us between the GEMMs of a training step); a wave goes through `kbw` consecutive
-// blocks, workgroups loop over the tiles.
+// Largest kept |value| a thread of the workgroup finds in tile (tx, ty) of the abs-max pass.  The four
+// waves take adjacent column stripes of the same blocks, so a row of the workgroup's tile is
+// 4 * 64 * VEC consecutive floats requested at about the same time (longer runs per DRAM page than
+// four waves on four different row blocks: 6.0 against 5.3 TB/s on a 721 MB tensor when the kernel
+// runs alone, 152 against 157 us between the GEMMs of a training step); a wave goes through `kbw`
+// consecutive blocks.
+template <int N, int VEC, int KIND>
+__device__ __forceinline__ float absmax_tile(const float* __restrict__ x, const RowTiling& rt, int64_t C,
+                                             const KeepMap& map, int kbw, int64_t tx, int64_t ty) {
+  constexpr int CT = 64 * VEC;
+  const int64_t c0 = tx * 4 * CT + (threadIdx.x >> 6) * CT + (threadIdx.x & 63) * VEC;
+  float m = 0.0f;
+  if (c0 >= C) return m;
+  for (int kb = 0; kb < kbw; ++kb) {
+    const int64_t gb = ty * kbw + kb;
+    if (gb >= rt.nblk) break;
+    float v[VEC][kept_vals<N, KIND>()];
+    int64_t first;
+    int valid;
+    block_rows<N>(rt, gb, first, valid);
+    load_block_kept<N, VEC, KIND>(x + first * C + c0, C, valid, v);
+    m = fmaxf(m, kept_form_absmax<N, VEC, KIND>(v, map));
+  }
+  return m;
+}
+
+// Abs-max pass: tiles of `kbw` blocks x 256 * VEC columns, dealt to a capped grid;
+// partials[blockIdx.x] = the workgroup's maximum over its tiles.
 template <int N, int VEC, int KIND>
 __global__ __launch_bounds__(256) void col_absmax_kernel(const float* __restrict__ x, RowTiling rt,
                                                          int64_t C, KeepMap map, int kbw,
                                                          float* __restrict__ partials) {
-  constexpr int CT = 64 * VEC;
-  __shared__ float s_max[4];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int64_t nblk = rt.nblk;
-  const int64_t tiles_x = (C + 4 * CT - 1) / (4 * CT);
-  const int64_t tiles_y = (nblk + kbw - 1) / kbw;
+  const int64_t tiles_x = (C + 256 * VEC - 1) / (256 * VEC);
+  const int64_t tiles_y = (rt.nblk + kbw - 1) / kbw;
   float m = 0.0f;
-  for (int64_t t = blockIdx.x; t < tiles_x * tiles_y; t += gridDim.x) {
-    const int64_t tx = t % tiles_x, ty = t / tiles_x;
-    const int64_t c0 = tx * 4 * CT + w * CT + lane * VEC;
-    if (c0 >= C) continue;
-    for (int kb = 0; kb < kbw; ++kb) {
-      const int64_t gb = ty * kbw + kb;
-      if (gb >= nblk) break;
-      float v[VEC][kept_vals<N, KIND>()];
-      int64_t first;
-      int valid;
-      block_rows<N>(rt, gb, first, valid);
-      load_block_kept<N, VEC, KIND>(x + first * C + c0, C, valid, v);
-      m = fmaxf(m, kept_form_absmax<N, VEC, KIND>(v, map));
-    }
-  }
-  m = wave_max(m);
-  if (lane == 0) s_max[w] = m;
-  __syncthreads();
-  if (tid == 0) partials[blockIdx.x] = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+  for (int64_t t = blockIdx.x; t < tiles_x * tiles_y; t += gridDim.x)
+    m = fmaxf(m, absmax_tile<N, VEC, KIND>(x, rt, C, map, kbw, t % tiles_x, t / tiles_x));
+  m = workgroup_max(m);
+  if (threadIdx.x == 0) partials[blockIdx.x] = m;
 }
 
 // Quantise pass: one tile per workgroup.  LDS tile: row (vi*64 + lane) holds the code

@@ -86,6 +86,47 @@ hipError_t front_n(FrontArgs& f, hipStream_t s, int stage, bool* done) {
   return hipSuccess;
 }
 
+// Rows of g_y (per token) and the abs-max pass of its token-direction view, for tensors far beyond the
+// caches.  HBM-bound: both jobs read all of g_y, so the workgroups of an XCD (every eighth) go through
+// slabs of 64 rows together, first a row each, then the slab's column tiles, whose lines the XCD's L2 then
+// holds or has under way: one read of HBM instead of two.  us, rows and abs-max pass apart and together:
+// 16384 tokens 11008 outputs 156 + 127 and 200, 16384 x 4096 57 + 49 and 90 (64-row blocks); 32736 x 5120
+// 151 + 120 and 180, 12800 x 8192 89 + 78 and 114 (32-row blocks).
+constexpr int kSlabRows = 64;
+template <int N, int KIND, int ITER>
+__global__ __launch_bounds__(256) void rows_and_absmax_kernel(const RowQuantArgs ra, const RowTiling rt, const KeepMap map,
+                                                              const int slabs, const int col_wgs, float* partials) {
+  constexpr int VEC = 2, KBW = kSlabRows / N;
+  const int per_slab = kSlabRows + col_wgs, j = (int)blockIdx.x >> 3;
+  const int slab = 8 * (j / per_slab) + ((int)blockIdx.x & 7), k = j % per_slab;
+  if (slab >= slabs) return;
+  if (k < kSlabRows) {
+    const int64_t row = (int64_t)slab * kSlabRows + k;
+    if (row < ra.rows) row_quant_body<N, ITER, 256>(ra, row, ra.rows);
+    return;
+  }
+  const int64_t C = ra.cols, tiles_x = (C + 256 * VEC - 1) / (256 * VEC);
+  float m = 0.0f;
+  for (int64_t tx = k - kSlabRows; tx < tiles_x; tx += col_wgs)
+    m = fmaxf(m, absmax_tile<N, VEC, KIND>(ra.t, rt, C, map, KBW, tx, slab));
+  m = workgroup_max(m);
+  if (threadIdx.x == 0) partials[slab * col_wgs + k - kSlabRows] = m;
+}
+
+template <int N, int KIND>
+hipError_t rows_and_absmax_n(const RowQuantArgs& ra, const RowTiling& rt, const KeepMap& map, int slabs, int col_wgs,
+                             float* partials, hipStream_t s) {
+  const dim3 grid((unsigned)(ceil_div(slabs, 8) * 8 * (kSlabRows + col_wgs)));
+#define HOT_ITER(ITER)                                                                                              \
+  if (ra.cols <= 1024 * ITER) {                                                                                     \
+    rows_and_absmax_kernel<N, KIND, ITER><<<grid, dim3(256), 0, s>>>(ra, rt, map, slabs, col_wgs, partials);        \
+    return hipGetLastError();                                                                                       \
+  }
+  HOT_ITER(3) HOT_ITER(4) HOT_ITER(6) HOT_ITER(8) HOT_ITER(11)
+#undef HOT_ITER
+  return hipErrorInvalidValue;
+}
+
 // All operands of a small layer's two GEMMs in one launch: the weight tiles and the tiles of g_y's
 // token-direction view (each set exchanging its own maxima, all resident at once), then the rows of
 // g_y (per token, or the abs-max pass of one scale per tensor).  Three launches otherwise, each far
@@ -226,6 +267,35 @@ long long wait_ticks(int64_t wait_us, int64_t bytes) {
 }
 
 }  // namespace
+
+// From 48 M elements on no form of the single-pass column kernel holds the kept values (42 M at most: 512
+// workgroups, 160 registers), so that the abs-max pass is there to be saved; 16-row blocks have the shared
+// passes.  Rows of a workgroup each; below 4096 columns the few rows under way at the registers of a
+// 64-row block cost more than the read (32000 x 2112: 287 us a backward call apart, 312 together); above 11264
+// a slab no longer fits an XCD's L2.  At least four column workgroups per slab within kMaxPartials.
+bool rows_and_absmax_applies(const Config& cfg, int64_t L, int64_t O) {
+  return cfg.n >= 32 && cfg.gw_bits == 8 && cfg.sample_tokens == 0 && (cfg.n == 32 ? O > 2048 : O >= 4096) && O <= 11264 &&
+         L * O >= 48ll * 1000 * 1000 && ceil_div(L, kSlabRows) <= kMaxPartials / 4;
+}
+
+hipError_t launch_rows_and_absmax(const float* g_y, int64_t L, int64_t O, const Config& cfg, uint8_t* qg, int64_t pitch,
+                                  float* s_g, float* partials, int* npartials, hipStream_t s, int stage) {
+  const int64_t slabs = ceil_div(L, kSlabRows);
+  const int64_t tiles_x = ceil_div(O, 512);
+  const int64_t col_wgs = tiles_x * slabs <= kMaxPartials ? tiles_x : kMaxPartials / slabs;
+  const RowTiling rt = row_tiling(cfg, L);
+  const RowQuantArgs ra{g_y, L, (int)O, cfg.gx_bits, cfg.rounding, 0, qg, pitch, s_g, nullptr, 0};
+  const bool low = cfg.lowpass_default && cfg.r * 2 == cfg.n;
+  stage_begin(stage, s);
+  hipError_t e;
+  if (cfg.n == 32) e = low ? rows_and_absmax_n<32, kKeepLowHalf>(ra, rt, cfg.map, (int)slabs, (int)col_wgs, partials, s)
+                           : rows_and_absmax_n<32, kKeepGeneric>(ra, rt, cfg.map, (int)slabs, (int)col_wgs, partials, s);
+  else e = low ? rows_and_absmax_n<64, kKeepLowHalf>(ra, rt, cfg.map, (int)slabs, (int)col_wgs, partials, s)
+               : rows_and_absmax_n<64, kKeepGeneric>(ra, rt, cfg.map, (int)slabs, (int)col_wgs, partials, s);
+  stage_end(stage, s);
+  *npartials = (int)(slabs * col_wgs);
+  return e;
+}
 
 hipError_t launch_operands(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw, int64_t pitch, float* s_w,
                            float* slots_w, const float* g_y, int64_t L, bool per_token, uint8_t* qg, float* s_g,

@@ -190,11 +190,12 @@ hipError_t launch_row_quant(const float* t, int64_t rows, int64_t cols, int n, i
 // kernel when the tensor fits it (timed as stage_quant), else the abs-max pass and the
 // quantise pass; `partials` is kMaxPartials floats of scratch either way;
 // *scale is written, pad bytes up to `pitch` are zero-filled.  `identity` says the
-// kept list is 0..n-1 (required for bits == 4).
+// kept list is 0..n-1 (required for bits == 4).  `have_partials` > 0: so many partial maxima are in
+// `partials` already, and only the quantise pass runs.
 hipError_t launch_col_quant(const float* x, const RowTiling& rows, int64_t C, const Config& cfg, int r,
                             const KeepMap& map, bool identity, int bits, uint8_t* codes,
                             int64_t pitch, float* scale, float* partials, hipStream_t s,
-                            int stage_absmax, int stage_quant);
+                            int stage_absmax, int stage_quant, int have_partials = 0);
 
 // Both views of g_y [L x O] from shared reads (block sizes 16 and 32): token rows
 // rotated along O -> qg [L x pitch_g] with scales sg ([L] per token, [1] per tensor),
@@ -226,6 +227,12 @@ uint64_t next_exchange_tag();
 hipError_t launch_w_and_rows(const float* w, int64_t O, int64_t I, const Config& cfg, uint8_t* qw,
                              int64_t pitch, float* s_w, float* slots, const float* g_y, int64_t L,
                              uint8_t* qg, float* s_g, hipStream_t s, int stage, bool* done);
+
+// The rotated, per-token quantised rows of a large g_y (as launch_row_quant in mode 0) and the abs-max
+// pass of its token-direction view from one read of g_y: partials[0 .. *npartials), for launch_col_quant.
+bool rows_and_absmax_applies(const Config& cfg, int64_t L, int64_t O);
+hipError_t launch_rows_and_absmax(const float* g_y, int64_t L, int64_t O, const Config& cfg, uint8_t* qg, int64_t pitch,
+                                  float* s_g, float* partials, int* npartials, hipStream_t s, int stage);
 
 // All three operands of a small layer in one launch (INT8 g_w, O up to 4096, a g_y that gains by it,
 // both column jobs' workgroups resident at once): those of launch_w_and_rows and the token-direction view of g_y

@@ -1612,3 +1612,36 @@ def test_seeded_random_shapes_and_settings(exchange_wait, gemm_mode):
             check_gw(hot, cfg, gy, x, what)
         else:
             check_fused(hot, cfg, gy, x, w, per_token, what)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,O,I,n,keep,keep_idx,gx_bits", [
+    (23456, 2080, 96, 32, 16, None, 4),      # a slab of one block at the end, narrow rows
+    (14720, 3328, 80, 32, 16, "lp_l1", 8),
+    (9600, 5152, 70, 32, 11, None, 4),       # a list of another length, column tiles that end inside
+    (4288, 11264, 64, 64, 32, None, 8),      # the longest rows
+    (12800, 4096, 33, 64, 64, "reversed", 4),
+    (32768, 4096, 32, 64, 32, None, 4)])     # the most slabs
+def test_rows_and_abs_max_from_one_read(L, O, I, n, keep, keep_idx, gx_bits):
+    """Large g_y per token: the rows' launch leaves the token-direction maxima, and the bits are those of
+    separate passes (each kernel a launch of its own)."""
+    hot = _hot()
+    rows = {"lp_l1": lambda: hot.hot_lowpass_l1_rows(n, keep), "reversed": lambda: list(range(n))[::-1]}
+    cfg = hot.Config(block=n, keep=keep, gx_bits=gx_bits, keep_idx=rows[keep_idx]() if keep_idx else None)
+    g = torch.Generator(device="cuda").manual_seed(91)
+    gy = torch.randn((L, O), generator=g, device="cuda")
+    gy[L - 1, O - 1] = 300.0                 # the maxima sit in the last row and column
+    w = torch.randn((O, I), generator=g, device="cuda")
+    x = torch.randn((L, I), generator=g, device="cuda")
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, x, act, ws)
+    out = []
+    for strategy in (3, 0):
+        hot.hot_debug_set_backward_strategy(strategy)
+        try:
+            gx, gw, roles = backward_stages(hot, cfg, gy, w, act, hot.HOT_Q_PER_TOKEN, ws)
+        finally:
+            hot.hot_debug_set_backward_strategy(0)
+        assert ("gyT_col_absmax" in roles) == (strategy == 3), roles
+        out.append((gx, gw))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
