@@ -90,13 +90,16 @@ hipError_t front_n(FrontArgs& f, hipStream_t s, int stage, bool* done) {
 // caches.  HBM-bound: both jobs read all of g_y, so the workgroups of an XCD (every eighth) go through
 // slabs of 64 rows together, first a row each, then the slab's column tiles, whose lines the XCD's L2 then
 // holds or has under way: one read of HBM instead of two.  us, rows and abs-max pass apart and together:
-// 16384 tokens 11008 outputs 156 + 127 and 200, 16384 x 4096 57 + 49 and 90 (64-row blocks); 32736 x 5120
-// 151 + 120 and 180, 12800 x 8192 89 + 78 and 114 (32-row blocks).
+// 16384 tokens 11008 outputs 156 + 127 and 200, 16384 x 4096 57 + 49 and 77 (64-row blocks); 32736 x 5120
+// 151 + 120 and 172, 12800 x 8192 89 + 78 and 105 (32-row blocks).
 constexpr int kSlabRows = 64;
+// Columns per lane of its column tiles: one for 64-row blocks, whose two would set the registers of the
+// rows as well (16384 x 4096 92 us with two, 77 with one; 32768 x 4096 174 and 147).
+__host__ __device__ constexpr int slab_vec(int n) { return n == 64 ? 1 : 2; }
 template <int N, int KIND, int ITER>
 __global__ __launch_bounds__(256) void rows_and_absmax_kernel(const RowQuantArgs ra, const RowTiling rt, const KeepMap map,
                                                               const int slabs, const int col_wgs, float* partials) {
-  constexpr int VEC = 2, KBW = kSlabRows / N;
+  constexpr int VEC = slab_vec(N), KBW = kSlabRows / N;
   const int per_slab = kSlabRows + col_wgs, j = (int)blockIdx.x >> 3;
   const int slab = 8 * (j / per_slab) + ((int)blockIdx.x & 7), k = j % per_slab;
   if (slab >= slabs) return;
@@ -271,8 +274,8 @@ long long wait_ticks(int64_t wait_us, int64_t bytes) {
 // From 48 M elements on no form of the single-pass column kernel holds the kept values (42 M at most: 512
 // workgroups, 160 registers), so that the abs-max pass is there to be saved; 16-row blocks have the shared
 // passes.  Rows of a workgroup each; below 4096 columns the few rows under way at the registers of a
-// 64-row block cost more than the read (32000 x 2112: 287 us a backward call apart, 312 together); above 11264
-// a slab no longer fits an XCD's L2.  At least four column workgroups per slab within kMaxPartials.
+// 64-row block cost more than the read (32000 x 2112, two columns per lane: 287 us a backward call apart, 312
+// together); above 11264 a slab no longer fits an XCD's L2.  At least four column workgroups per slab within kMaxPartials.
 bool rows_and_absmax_applies(const Config& cfg, int64_t L, int64_t O) {
   return cfg.n >= 32 && cfg.gw_bits == 8 && cfg.sample_tokens == 0 && (cfg.n == 32 ? O > 2048 : O >= 4096) && O <= 11264 &&
          L * O >= 48ll * 1000 * 1000 && ceil_div(L, kSlabRows) <= kMaxPartials / 4;
@@ -281,7 +284,7 @@ bool rows_and_absmax_applies(const Config& cfg, int64_t L, int64_t O) {
 hipError_t launch_rows_and_absmax(const float* g_y, int64_t L, int64_t O, const Config& cfg, uint8_t* qg, int64_t pitch,
                                   float* s_g, float* partials, int* npartials, hipStream_t s, int stage) {
   const int64_t slabs = ceil_div(L, kSlabRows);
-  const int64_t tiles_x = ceil_div(O, 512);
+  const int64_t tiles_x = ceil_div(O, 256 * slab_vec(cfg.n));
   const int64_t col_wgs = tiles_x * slabs <= kMaxPartials ? tiles_x : kMaxPartials / slabs;
   const RowTiling rt = row_tiling(cfg, L);
   const RowQuantArgs ra{g_y, L, (int)O, cfg.gx_bits, cfg.rounding, 0, qg, pitch, s_g, nullptr, 0};
