@@ -136,7 +136,7 @@ struct Operands {            // what the matrix instructions of one K slice cons
 // workgroups are not resident together.
 // SPLIT = kImages: the same grid, every workgroup leaves its image (slot = row-major tile index *
 // split + slice) and combine_images_kernel, launched behind, adds them in slice order.  An owner
-// collects images one after the other, 2-3 us each, which many slices cannot afford; and the
+// collects two images at a time, 2-3 us each time, which many slices cannot afford; and the
 // fp32 sums of the bfloat16 operands must not depend on which workgroup added a piece.
 // SPLIT = kSliceSums: the bfloat16 GEMM where kImages has no room for its images, with its bits: a
 // slice's products are summed from zero and the slices' sums added in order, by the tile's own
