@@ -91,7 +91,9 @@ hipError_t front_n(FrontArgs& f, hipStream_t s, int stage, bool* done) {
 // slabs of 64 rows together, first a row each, then the slab's column tiles, whose lines the XCD's L2 then
 // holds or has under way: one read of HBM instead of two.  us, rows and abs-max pass apart and together:
 // 16384 tokens 11008 outputs 156 + 127 and 200, 16384 x 4096 57 + 49 and 77 (64-row blocks); 32736 x 5120
-// 151 + 120 and 172, 12800 x 8192 89 + 78 and 105 (32-row blocks).
+// 151 + 120 and 172, 12800 x 8192 89 + 78 and 105 (32-row blocks).  Fetched: 1.01 times g_y at 4096 columns,
+// 1.78 times at 11008, whose slab is 2.8 of the L2's 4 MB; fewer workgroups under way do not help there
+// (three per unit 198 us, two 244).
 constexpr int kSlabRows = 64;
 // Columns per lane of its column tiles: one for 64-row blocks, whose two would set the registers of the
 // rows as well (16384 x 4096 92 us with two, 77 with one; 32768 x 4096 174 and 147).
