@@ -316,6 +316,16 @@ int64_t hot_debug_profile_sequence(int32_t* stages, int64_t capacity);
 
 const char* hot_debug_stage_name(int stage);
 
+/* How the GEMMs of a layer are distributed in the modes set above, with a full-size workspace (host only, nothing
+ * is launched): whether hot_linear_backward makes one launch of both, and for each its tile rows and columns, its
+ * K slices, and whether a second kernel adds the slices' sums; the last two are those of
+ * hot_linear_backward_gx (also with cached weights) and hot_linear_backward_gw. */
+typedef struct hot_gemm_plan {
+  int32_t one_launch;
+  int32_t gx[4], gw[4], gx_alone[4], gw_alone[4];
+} hot_gemm_plan;
+hot_status hot_debug_gemm_plan(const hot_config* cfg, int64_t L, int64_t O, int64_t I, hot_gemm_plan* plan);
+
 /* Machine-peak probes (context for the roofline figures, not the method): one launch of
  * kind 0 = read `bytes` of buf, 1 = write them (4 = with the streaming, non-temporal, hint the
  * GEMM epilogue uses), 2 / 3 = `iters` x 16 int8 32x32x32 matrix

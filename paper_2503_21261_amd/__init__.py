@@ -32,7 +32,7 @@ EXPORTS = (
     "hot_linear_backward", "hot_linear_backward_gx_noalloc", "hot_lowpass_l1_rows", "hot_select_quantizer", "hot_debug_unpack_activation",
     "hot_debug_gx_operands", "hot_debug_gw_operands", "hot_debug_fused_operands", "hot_debug_set_exchange_wait_us",
     "hot_debug_set_backward_strategy", "hot_debug_set_gemm_mode", "hot_debug_profile_begin", "hot_debug_profile_end", "hot_debug_profile_sequence",
-    "hot_debug_stage_name", "hot_debug_probe",
+    "hot_debug_stage_name", "hot_debug_probe", "hot_debug_gemm_plan",
 )
 HOT_NUM_STAGES = 15
 HOT_WS_PREFIX_BYTES = 24832
@@ -42,6 +42,10 @@ class hot_config(C.Structure):
     _fields_ = [("block", C.c_int32), ("keep", C.c_int32), ("keep_idx", C.POINTER(C.c_int32)),
                 ("gx_bits", C.c_int32), ("gw_bits", C.c_int32), ("rounding", C.c_int32),
                 ("lqs_threshold", C.c_float), ("sample_tokens", C.c_int32), ("replayable", C.c_int32)]
+
+
+class hot_gemm_plan(C.Structure):
+    _fields_ = [("one_launch", C.c_int32)] + [(f, C.c_int32 * 4) for f in ("gx", "gw", "gx_alone", "gw_alone")]
 
 
 class HotError(RuntimeError):
@@ -89,6 +93,7 @@ def lib() -> C.CDLL:
         l.hot_debug_set_gemm_mode.argtypes = [C.c_int]
         l.hot_debug_profile_begin.argtypes = []
         l.hot_debug_profile_end.argtypes = [C.POINTER(C.c_float), C.POINTER(C.c_int64)]
+        l.hot_debug_gemm_plan.argtypes = [cfgp, i64, i64, i64, C.POINTER(hot_gemm_plan)]
         l.hot_debug_probe.argtypes = [C.c_int, vp, sz, C.c_int, vp]
         l.hot_debug_profile_sequence.argtypes = [C.POINTER(C.c_int32), C.c_int64]
         l.hot_weight_buffer_bytes.argtypes = [cfgp, i64, i64]
@@ -408,6 +413,14 @@ def hot_debug_profile_sequence():
     buf = (C.c_int32 * max(n, 1))()
     lib().hot_debug_profile_sequence(buf, n)
     return [lib().hot_debug_stage_name(int(buf[i])).decode() for i in range(n)]
+
+
+def hot_debug_gemm_plan(cfg: Config, L: int, O: int, I: int) -> dict:
+    """{one_launch: bool, gx / gw / gx_alone / gw_alone: (tile rows, tile columns, K slices, added by a second kernel)}."""
+    p = hot_gemm_plan()
+    _check(lib().hot_debug_gemm_plan(C.byref(cfg.c()), L, O, I, C.byref(p)), "hot_debug_gemm_plan")
+    return dict(one_launch=bool(p.one_launch), **{f: (*list(getattr(p, f))[:3], bool(getattr(p, f)[3]))
+                                                  for f in ("gx", "gw", "gx_alone", "gw_alone")})
 
 
 def hot_debug_probe(kind: int, buf: torch.Tensor, iters: int = 1, stream=None) -> None:

@@ -360,11 +360,13 @@ hipError_t gemm(const GemmCall& g, hipStream_t s, int stage = -1, bool images = 
 // Both GEMMs of a layer, in one launch where that pays (they share the scratch: only one of them
 // then splits K).
 hot_status both_gemms(const GemmCall& gx, const GemmCall& gw, bool images, hipStream_t s) {
-  bool both = false;
-  if (g_backward_strategy.load() != 3) HOT_TRY(launch_gemm_pair(gw, images, gx, s, kStGemmPair, &both));
-  if (both) return HOT_OK;
-  HOT_TRY(gemm(gx, s, kStGxGemm));
-  HOT_TRY(gemm(gw, s, kStGwGemm, images));
+  const GemmPairPlan p = plan_gemm_pair(gw, images, gx, g_backward_strategy.load() != 3);
+  if (p.together) {
+    HOT_TRY(launch_gemm_pair(gw, gx, p, s, kStGemmPair));
+    return HOT_OK;
+  }
+  HOT_TRY(launch_igemm(gx, p.x, s, kStGxGemm));
+  HOT_TRY(launch_igemm(gw, p.w, s, kStGwGemm));
   return HOT_OK;
 }
 
@@ -722,6 +724,31 @@ hot_status hot_debug_set_exchange_wait_us(int us) {
 hot_status hot_debug_set_gemm_mode(int mode) {
   if (mode < 0 || (mode > 8 && mode < 10) || mode > 13) return HOT_ERR_ARG;
   set_gemm_mode(mode);
+  return HOT_OK;
+}
+
+hot_status hot_debug_gemm_plan(const hot_config* cfg, int64_t L, int64_t O, int64_t I, hot_gemm_plan* plan) {
+  Config c;
+  hot_status st = resolve_config(cfg, &c);
+  if (st != HOT_OK) return st;
+  if (!plan) return HOT_ERR_ARG;
+  if (!gx_shape_ok(c, L, O, I) || !tok_shape_ok(c, L, O) || !tok_shape_ok(c, L, I)) return HOT_ERR_SHAPE;
+  const GemmCall gx = gemm_call(c, nullptr, nullptr, L, I, gx_layout(c, L, O, I).pitch, c.gx_bits, nullptr, 0, nullptr,
+                                nullptr, nullptr, 0, nullptr);
+  const GemmCall gw = gemm_call(c, nullptr, nullptr, O, I, gw_layout(c, L, O, I).pitch, c.gw_bits, nullptr, 0, nullptr,
+                                nullptr, nullptr, 0, nullptr);
+  const GemmPairPlan p = plan_gemm_pair(gw, true, gx, g_backward_strategy.load() != 3);
+  plan->one_launch = p.together;
+  const auto put = [](const GemmPlan& g, int32_t* out) {
+    out[0] = g.bm;
+    out[1] = g.bn;
+    out[2] = g.split;
+    out[3] = g.images;
+  };
+  put(p.x, plan->gx);
+  put(p.w, plan->gw);
+  put(plan_gemm(gx.M, gx.N, gx.k_bytes, gx.bits, true, false), plan->gx_alone);
+  put(plan_gemm(gw.M, gw.N, gw.k_bytes, gw.bits, true, true), plan->gw_alone);
   return HOT_OK;
 }
 

@@ -107,9 +107,8 @@ struct GemmPlan {
   size_t partial_bytes;   // split > 1: tiles * (split - 1, or split with `images`) * bm * bn int32
 };
 // `scratch`: a region of gemm_scratch_bytes() and the workspace's flag slots are available,
-// so K may be split; `images`: a region of image_scratch_bytes() is; `beside`: the other gradient's
-// workgroups follow in the same launch.
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images, bool beside = false);
+// so K may be split; `images`: a region of image_scratch_bytes() is.
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images);
 size_t image_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits);
 // Upper bound of partial_bytes over every plan of this shape (whatever mode is forced).
 size_t gemm_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits);
@@ -268,10 +267,15 @@ struct GemmCall {
   const unsigned long long* epoch;
 };
 hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage = -1);
-// Both GEMMs of a layer in one launch, up to a few thousand workgroups together and where `x` gains by
-// it: `w` with its own plan on 128x128 tiles, `x` on unsplit tiles.  *done says whether the launch was
-// made.
-hipError_t launch_gemm_pair(const GemmCall& w, bool images, const GemmCall& x, hipStream_t s, int stage, bool* done);
+// Both GEMMs of a layer: one launch (`together`, up to a few thousand workgroups: `w` on 128x128 tiles, `x` on
+// unsplit tiles of 128 rows) or each with its own plan, which is also what `may_share` = false gives.
+// `images`: a region of image_scratch_bytes() for `w` is there.
+struct GemmPairPlan {
+  bool together;
+  GemmPlan w, x;
+};
+GemmPairPlan plan_gemm_pair(const GemmCall& w, bool images, const GemmCall& x, bool may_share);
+hipError_t launch_gemm_pair(const GemmCall& w, const GemmCall& x, const GemmPairPlan& plan, hipStream_t s, int stage);
 
 // Unpack K-contiguous codes [rows x pitch] into one int8 per code.
 //   transpose = 0: out[row * K + k];  transpose = 1: out[k * rows + row].

@@ -97,9 +97,6 @@ int64_t large_tile_split(int64_t M, int64_t N, int64_t k_bytes, int bits, int cu
 struct SplitCost { double stage, stage_two, split, slice, resident; };
 constexpr SplitCost kSplit4{0.48, 0.69, 3.0, 0.84, 6.5};
 constexpr SplitCost kSplit8{0.54, 0.92, 2.3, 1.0, 5.0};
-// g_w behind whose workgroups g_x waits for places, so that their number counts more (640 layers, 2.6 %
-// above the best split; 22 % with the rule before)
-constexpr SplitCost kSplitBeside{0.54, 1.25, 0.0, 0.85, 15.3};
 double split_us(const SplitCost& c, int64_t tiles, int64_t stages, int64_t s, int cus) {
   const int64_t wgs = tiles * s;
   const double t = (double)ceil_div(stages, s) * (wgs <= cus ? c.stage : c.stage_two);
@@ -164,7 +161,7 @@ int64_t image_slices(int64_t M, int64_t N, int64_t k_bytes, int bits, int cus) {
 void set_gemm_mode(int mode) { g_gemm_mode.store(mode); }
 void set_gemm_wait_us(int us) { g_gemm_wait_us.store(us); }
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images, bool beside) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch, bool images) {
   const Cand* cands = bits == 4 ? kCands4 : kCands8;
   const int ncand = bits == 4 ? 4 : 2;
   const double K = (double)k_bytes * (bits == 4 ? 2 : 1);
@@ -189,10 +186,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
   // the mode, so that its bits do too; without images one workgroup sums them in their order
   if (bits == 16) images = images && mode == 0;
   if ((images && mode == 0) || bits == 16) {
-    // beside g_x the second kernel is one launch more, which pays up to 16 tiles (13-16 tiles: 5 % above the
-    // best choice either way, 33-42: 19 % with images and 5 without)
-    const bool pays = bits == 16 || !beside || ceil_div(M, 128) * ceil_div(N, 128) <= cus / 16;
-    const int64_t s = pays ? image_slices(M, N, k_bytes, bits, cus) : 0;
+    const int64_t s = image_slices(M, N, k_bytes, bits, cus);
     if (s) {
       p.bm = p.bn = 128;
       p.tiles = ceil_div(M, 128) * ceil_div(N, 128);
@@ -211,7 +205,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
     return p;
   }
   if (bits == 16 || !scratch) return p;
-  const SplitCost& cost = bits == 4 ? kSplit4 : (beside ? kSplitBeside : kSplit8);
+  const SplitCost& cost = bits == 4 ? kSplit4 : kSplit8;
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), nk = k_bytes / p.bkb, most = max_split(tiles, nk);
   if (mode == 0) {
     const int64_t l = large_tile_split(M, N, k_bytes, bits, cus);
@@ -445,70 +439,144 @@ hipError_t launch_pair_tile(const GemmArgs& gw, const GemmArgs& gx, int gw_wgs, 
 
 namespace {
 
-// Whether g_x gains from a place in g_w's launch, where its tiles are 128 rows high and do the whole
-// K; `tiles` of them, `together` with all of g_w's workgroups resident at once.  Two things are given up:
-//  - a split of K.  A tile alone then goes through K stage by stage, 0.2-0.6 us each, while the split
-//    cost one hand-over: shared launches win while K is short, longer where the split already put
-//    two workgroups on a unit (they slow each other down), shorter on 128x256 tiles, and longer where
-//    g_w's own K, which runs beside g_x's stages, is long.  Stages of both sides' equality over
-//    1990 layers of 64 to 32768 tokens, 64 to 8192 inputs and 1024 to 32768 outputs: 40-48 / 60-72 for
-//    INT8 and INT4 on 128x128 tiles, 28-32 / 48 on 128x256, and behind more workgroups than are resident
-//    32-40 for g_x of 65 to 255 tiles, about 64 for 256 INT8 ones (1024 tokens 5120 x 4096 111 us apart, 97
-//    together; 512 tokens 16384 x 768 93 us apart, 145 together; 1024 tokens
-//    4096 x 512 46 and 34).
-//  - the eight-wave 256x256 INT8 tile.  Against the cost model's time for that one, 128x128 tiles
-//    price at 0.16 us per million operations and unit in this company (16384 tokens 4096 x 1024
-//    286 us apart, 297 together; 8192 tokens 146 and 134).  Split in two it is the slower one all the
-//    same, in three and more the faster (128 tokens 40960 x 512 288 us apart, 251 together; 65536 x 512
-//    321 and 406).
-bool shares_g_w_launch(const GemmCall& c, bool w_long, int64_t tiles, bool wide, bool together) {
-  const int64_t stages = c.k_bytes / (c.bits == 4 ? 64 : 128);
-  if (c.bits == 4 && stages <= 28) return true;   // whatever its own plan is: below every line
-  // what g_x would take on its own, its split given as the most slices that are resident at once
-  const GemmPlan own = plan_gemm(c.M, c.N, c.k_bytes, c.bits, false, false);
-  const int cus = compute_units();
-  const int64_t large = large_tile_split(c.M, c.N, c.k_bytes, c.bits, cus);
-  if (large) return large == 2;
-  if (own.bm == 256 && c.bits == 8)
-    return (double)tiles / cus * tile_mops(kCands8[0], (double)c.k_bytes) * 0.16 <
-           tile_shape_us(kCands8[1], c.M, c.N, (double)c.k_bytes, cus);
-  if (own.bm != 128) return true;   // measured faster in every case
-  int64_t slices = own.bn == 128 && own.tiles <= cus ? 2 * cus / own.tiles : 1;
-  const int64_t most = max_split(own.tiles, stages);
-  slices = slices < most ? slices : most;
-  if (slices > 1) {
-    if (own.tiles * slices <= cus) return stages <= (wide ? 28 : 40) + (together && w_long ? 24 : 0);
-    if (together) return stages <= (wide ? 48 : 72);
-    if (own.tiles <= cus / 4) return stages <= (wide ? 48 : 56);
-    return stages <= (own.tiles == cus && !wide ? 64 : 32);   // 256 tiles in two: every unit has two workgroups
+// us a workgroup of 128-row tiles takes for a K stage while it has its unit to itself, shares it with another
+// workgroup, and in a launch that fills every place several times over; and for what is not a stage
+// (first loads, epilogue).
+struct StageTimes { double one, two, full, each; };
+constexpr StageTimes kTimesW{0.64, 1.43, 0.71, 3.57};         // g_w, 128-byte stages
+constexpr StageTimes kTimesX4{0.464, 0.561, 0.763, 4.08};     // g_x, INT4 on 128x128 tiles, 64-byte stages
+constexpr StageTimes kTimesX4Wide{0.723, 0.932, 1.203, 5.4};  // the same on 128x256
+constexpr StageTimes kTimesX8{0.542, 0.58, 1.018, 3.68};      // g_x, INT8, 128-byte stages
+// A GEMM's part of a launch (wgs = 0: the launch has none).
+struct Part {
+  int64_t wgs, stages;   // workgroups, K stages of each
+  StageTimes t;
+  int64_t slices;        // of K
+  bool images;           // added by a second kernel
+  double store_kb;       // output bytes of a workgroup
+};
+constexpr Part kNoPart{0, 0, kTimesW, 1, false, 0.0};
+// us of a launch of `w`'s workgroups with `x`'s behind them on the chip's places, two to a unit: the longest of
+// g_w with its hand-over, of g_x from when its last workgroups find a place, and of all the work over all
+// places.  `broken`: stores of x that leave parts of 64-byte sectors; once they saturate memory (5 MB per us),
+// g_w's loads wait behind them (62646 tokens 336 x 1477: 1.4 us a stage).
+double launch_us(const Part& w, const Part& x, bool broken) {
+  const double cus = compute_units(), places = 2 * cus, W = (double)w.wgs, X = (double)x.wgs;
+  const double x_each = x.t.each + 0.006 * x.store_kb;
+  const double x1 = X > 0 ? (double)x.stages * x.t.one + x_each : 0.0;
+  const double x2 = X > 0 ? (double)x.stages * x.t.two + x_each : 0.0;
+  const double x3 = X > 0 ? (double)x.stages * x.t.full + x_each : 0.0;
+  double slow = 1.0;
+  if (broken && X > 0) {
+    const double over = (X < places ? X : places) * x.store_kb / 1024.0 / x2 / 5.0 - 1.09;
+    slow += 4.9 * (over < 0.0 ? 0.0 : over < 1.0 ? over : 1.0);
   }
-  return together || !wide || own.tiles > cus || stages <= 40;   // one tile per unit against two
+  const double w1 = W > 0 ? (double)w.stages * w.t.one + w.t.each : 0.0;
+  const double w2 = W > 0 ? (double)w.stages * w.t.two * slow + w.t.each : 0.0;
+  const double w3 = W > 0 ? (double)w.stages * w.t.full + w.t.each : 0.0;
+  const bool resident = W + X <= places, shared = W + X > cus;   // all at once; some unit has two
+  double wt = w1, xt = x1;
+  if (shared) {
+    // what is left of the longer GEMM goes on at its own rate once the other one has ended
+    const double beside = resident ? x2 : X * x2 / (places - W > 64 ? places - W : 64.0);
+    const double alone = W <= cus ? w1 : W > 0 ? (double)w.stages * w.t.two + w.t.each : 0.0;
+    wt = w2 <= beside ? w2 : beside + (1.0 - beside / w2) * alone;
+    xt = x2 <= w2 ? x2 : w2 + (1.0 - w2 / x2) * (resident && X <= cus ? x1 : x2);
+  }
+  const bool hands = w.slices > 1 && !w.images;
+  const double load = W / places;
+  const double hand = hands ? 2.47 + 0.79 * (double)(w.slices - 1) + 9.4 * (load < 2.0 ? load : 2.0) : 0.0;
+  if (W > places) wt = w3 * (load + 0.61);
+  const double waits = (W + (X < places ? X : places) - places) / places * w3;
+  double t = wt + hand;
+  if (xt + (waits > 0.0 ? waits : 0.0) > t) t = xt + (waits > 0.0 ? waits : 0.0);
+  const double all = (W * w3 + X * x3) / places + 0.61 * x3 + 0.56 * hand;
+  if (!resident && all > t) t = all;
+  return t + (w.images ? 2.9 + 0.027 * W : 0.0) + 0.7;
+}
+const StageTimes& x_times(int bits, bool wide) { return bits != 4 ? kTimesX8 : wide ? kTimesX4Wide : kTimesX4; }
+// us of a GEMM in a launch of its own.
+double alone_us(const GemmCall& c, const GemmPlan& p, bool g_w) {
+  const int64_t stages = c.k_bytes / p.bkb;
+  if (p.bm == 128 && p.bn == 128) {
+    const StageTimes& t = g_w ? kTimesW : x_times(c.bits, false);
+    const double store_kb = 4.0 * (double)c.M * (double)c.N / (double)p.tiles / 1024.0;
+    if (!g_w && p.split == 1) return launch_us(kNoPart, Part{p.tiles, stages, t, 1, false, store_kb}, false);
+    return launch_us(Part{p.tiles * p.split, ceil_div(stages, p.split), t, p.split, p.images, 0.0}, kNoPart, false);
+  }
+  if (p.split > 1) return large_split_us(stages, p.split) + 8.0;
+  const double K = (double)c.k_bytes * (c.bits == 4 ? 2 : 1);
+  if (c.bits != 4) return tile_shape_us(kCands8[1], c.M, c.N, K, compute_units());
+  int i = 0;
+  while (kCands4[i].bm != p.bm || kCands4[i].bn != p.bn) ++i;
+  return tile_shape_us(kCands4[i], c.M, c.N, K, compute_units());
 }
 
 }  // namespace
 
-hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, hipStream_t s, int stage, bool* done) {
-  *done = false;
-  if (g_gemm_mode.load() != 0 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return hipSuccess;
-  const GemmPlan p = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images, true);
-  if (p.bm != 128 || p.bn != 128) return hipSuccess;
-  if (cw.bits == 16 && p.split > 1 && !p.images) return hipSuccess;
-  const int64_t w = p.tiles * p.split, cap = 2 * (int64_t)compute_units();
-  const int64_t most = 8 * cap;
-  // Two workgroups per unit are resident (LDS of the g_w tile, registers).  While all are: 128x128
-  // g_x tiles, the most workgroups.  Beyond that 128x256 (INT4): the g_x tiles start where g_w
-  // slices end, no launch and no drained chip between them (12608 tokens 3072 x 768, 432 + 297
-  // workgroups: 155 -> 141 us a layer pass; with 594 tiles of 128x128 151).  Backward calls apart and
-  // together: 8192 tokens 1024 x 4096 114 -> 94 us, 50432 x 768 x 768 145 -> 128, INT8 12608 x 768 x 3072
-  // 117 -> 105, 25216 x 768 x 3072 (2796 workgroups) 173 -> 156.  The gain is one tail and one launch;
-  // sizes above the line, where the g_x GEMM's own choice of tile matters more, were not timed.
-  const int64_t rows = ceil_div(cx.M, 128), x128 = rows * ceil_div(cx.N, 128), x256 = rows * ceil_div(cx.N, 256);
-  const bool int4 = cx.bits == 4, narrow = w + x128 <= (int4 ? cap : most);
-  if (!narrow && !(int4 && w + x256 <= most)) return hipSuccess;
-  const int64_t x = narrow ? x128 : x256;
-  // g_w's K long enough to run beside g_x's stages (INT8: two slices of four stages)
-  const bool w_long = cw.bits == 16 ? p.split > 1 : cw.k_bytes >= 1024 && p.tiles <= compute_units();
-  if (!shares_g_w_launch(cx, w_long, x, !narrow, w + x <= cap)) return hipSuccess;
+// Whether the two GEMMs of a layer share a launch, g_w's plan in it and the tile of g_x, whose workgroups then do
+// the whole of K.  g_w's slices and g_x's tile follow from the time of the whole launch (launch_us), whose constants
+// are fitted to backward calls of 10500 layers (64 to 201728 tokens, 64 to 65536 outputs, 64 to 11008 inputs), every
+// split, both tiles and two launches timed on each, with inputs that change from call to call: what is
+// chosen takes 0.5 % longer than the best of them on average.  Slices chosen without a look at g_x's
+// workgroups, and sizes of g_x for which a launch is shared, took 2.2 %: 20736 tokens 832 x 2816 with g_w unsplit
+// 267 us a layer pass, 251 in two slices; 7880 x 1664 x 2757 in INT8 with bfloat16 g_w apart 214 us a call, 149 together; 128 x 40960
+// x 512 in INT8 together 266 us a pass, 144 apart, where g_x splits K in eight.
+// Two launches are looked at only where g_x has more than 28 stages (up to there they were the faster by 2 % on 19
+// of 7400 layers) or g_w a 256x256 tile of its own, whose time tile_shape_us puts too high: those have
+// to be 15 % slower for a shared launch (25921 tokens 3264 x 3840, bfloat16 g_w, 951 us a call together, 871 apart),
+// others 3 % faster for two.  128x128 g_x tiles in more workgroups than are resident have to be 3 % faster
+// than 128x256.
+GemmPairPlan plan_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, bool may_share) {
+  GemmPairPlan apart, plan;
+  apart.together = plan.together = false;
+  apart.w = plan_gemm(cw.M, cw.N, cw.k_bytes, cw.bits, true, images);
+  apart.x = plan_gemm(cx.M, cx.N, cx.k_bytes, cx.bits, true, false);
+  if (!may_share || g_gemm_mode.load() != 0 || cw.M <= 0 || cw.N <= 0 || cx.M <= 0 || cx.N <= 0) return apart;
+  const int64_t places = 2 * (int64_t)compute_units(), most = 8 * places;
+  const int64_t stages = cw.k_bytes / 128, x_stages = cx.k_bytes / (cx.bits == 4 ? 64 : 128);
+  GemmPlan w = apart.w;
+  w.bm = w.bn = 128;
+  w.tiles = ceil_div(cw.M, 128) * ceil_div(cw.N, 128);
+  int64_t image_split = 0, max_slices = 1;
+  if (cw.bits == 16) {   // the slices, and so the bits, that the shape alone gives
+    if (apart.w.split > 1 && !apart.w.images) return apart;   // one workgroup per tile adds them
+    if (apart.w.images) image_split = apart.w.split, max_slices = 0;
+  } else {
+    if (images) image_split = image_slices(cw.M, cw.N, cw.k_bytes, cw.bits, compute_units());
+    max_slices = max_split(w.tiles, stages);
+  }
+  double best_us = 1e30;
+  for (int wide = 0; wide <= (cx.bits == 4 ? 1 : 0); ++wide) {
+    const int64_t tiles = ceil_div(cx.M, 128) * ceil_div(cx.N, wide ? 256 : 128);
+    if (w.tiles + tiles > most) continue;
+    const Part px{tiles, x_stages, x_times(cx.bits, wide != 0), 1, false,
+                  4.0 * (double)cx.M * (double)cx.N / (double)tiles / 1024.0};
+    for (int64_t s = image_split ? 0 : 1; s <= max_slices; ++s) {   // 0: images
+      const int64_t slices = s ? s : image_split, wgs = w.tiles * slices;
+      if (s > 1 && wgs > places) break;
+      double us = launch_us(Part{wgs, ceil_div(stages, slices), kTimesW, slices, s == 0, 0.0}, px, cx.N % 16 != 0);
+      if (cx.bits == 4 && !wide && wgs + tiles > places) us *= 1.03;
+      if (us >= best_us) continue;
+      best_us = us;
+      plan.together = true;
+      plan.w = w;
+      plan.w.split = (int)slices;
+      plan.w.images = s == 0;
+      plan.w.partial_bytes = s == 0 ? image_scratch_bytes(cw.M, cw.N, cw.k_bytes, cw.bits)
+                                    : (size_t)w.tiles * (slices - 1) * 128 * 128 * 4;
+      plan.x = GemmPlan{128, wide ? 256 : 128, cx.bits == 4 ? 64 : 128, 1, tiles, false, 0};
+    }
+  }
+  if (!plan.together || (x_stages <= 28 && apart.w.bm == 128)) return plan.together ? plan : apart;
+  const double us = alone_us(cx, apart.x, false) + alone_us(cw, apart.w, true) - 0.5;
+  return us * (apart.w.bm == 128 ? 1.03 : 0.85) < best_us ? apart : plan;
+}
+
+hipError_t launch_gemm_pair(const GemmCall& cw, const GemmCall& cx, const GemmPairPlan& plan, hipStream_t s, int stage) {
+  const GemmPlan& p = plan.w;
+  const bool int4 = cx.bits == 4, narrow = plan.x.bn == 128;
+  const int64_t rows = ceil_div(cx.M, 128), w = p.tiles * p.split, x = plan.x.tiles;
   GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
@@ -530,7 +598,6 @@ hipError_t launch_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
                        : int4  ? launch_pair_tile<128, true>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s)
                                : launch_pair_tile<128, false>(gw, gx, (int)w, (int)x, cw.bits, p.split, p.images, s);
   stage_end(stage, s);
-  *done = true;
   return e;
 }
 

@@ -1086,7 +1086,7 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
 
 @pytest.mark.parametrize("L,O,I,n,S,gw_bits,keep_idx", [
     (512, 768, 768, 16, 0, 8, None),        # one slice per g_w tile
-    (3136, 448, 1792, 16, 49, 8, [0, 1, 2, 4, 8, 5, 3, 12]),   # slices handed over, 128x256 g_x tiles, padded blocks
+    (3136, 448, 1792, 16, 49, 8, [0, 1, 2, 4, 8, 5, 3, 12]),   # padded blocks; 128x256 g_x tiles, or (INT8) slices handed over
     (3330, 1008, 771, 16, 333, 8, None),    # ragged in every direction, one column per lane
     (8192, 640, 65, 16, 0, 8, None),        # two blocks per wave
     (8192, 640, 64, 32, 0, 8, None),
@@ -1097,7 +1097,7 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
     (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
     (8208, 2304, 768, 16, 0, 8, None),      # more workgroups than are resident at once
-    (33024, 768, 768, 16, 0, 8, None),      # behind the shared g_y passes
+    (33024, 768, 768, 16, 0, 8, None),      # slices handed over, behind the shared g_y passes
     (16400, 4096, 100, 16, 0, 8, None),     # the token-direction view in a launch of its own
     (2048, 256, 130, 32, 0, 8, "lp_l1"),    # the compile-time LP_L1 list
     (1040, 128, 96, 16, 0, 8, "lp_l1"),
@@ -1148,21 +1148,20 @@ def backward_stages(hot, cfg, gy, w, act, q, ws):
 
 
 @pytest.mark.parametrize("L,O,I,gx_bits,shared", [
-    (512, 768, 768, 4, True),        # 12 K stages of g_x, unsplit next to g_w
-    (512, 2560, 640, 4, True),       # 20, at 20 tiles
-    (128, 5120, 256, 4, True),       # 40 stages, split eight ways on its own
-    (128, 5376, 256, 4, False),      # 42
-    (2048, 8192, 256, 4, True),      # 64, beside hand-overs of g_w
-    (128, 16384, 256, 4, False),     # 128 stages on two tiles
-    (512, 11008, 1024, 4, False),    # 128x256 tiles behind 688 g_w tiles
-    (2048, 4096, 512, 8, True),      # 32 stages on 64 tiles
+    (512, 768, 768, 4, True),        # 12 K stages of g_x
+    (512, 2560, 640, 4, True),       # 20, at 20 tiles that would split K in three
+    (128, 3584, 256, 4, True),       # 28, in four
+    (128, 3840, 256, 4, False),      # 30, in five
+    (2048, 4096, 256, 4, True),      # 32 beside four times as many g_w workgroups
+    (2048, 8192, 256, 4, False),     # 64
+    (512, 11008, 1024, 4, False),    # behind 688 g_w tiles
+    (2048, 3072, 512, 8, True),      # 24 stages
     (512, 16384, 256, 8, False),
-    (1024, 5120, 4096, 8, True),     # 40 stages on 256 tiles, split in two on its own
-    (1024, 5120, 2048, 8, False),    # on 128 tiles, split in four
-    (12800, 4096, 1024, 8, False),   # the 256x256 INT8 tile
+    (1024, 5120, 2048, 8, False),    # 40 stages, split in two
+    (12800, 4096, 1024, 8, True),    # the 256x256 INT8 tile
     (4096, 1024, 4096, 8, True),     # the same tile, a short K
-    (128, 32768, 128, 8, True),      # the same tile, split in two
-    (128, 65536, 128, 8, False)])    # in four
+    (8192, 3072, 4096, 8, False),    # the same tile, for g_w too
+    (128, 32768, 128, 8, False)])    # 256 stages, split in eight
 def test_gemms_share_a_launch_while_that_pays(L, O, I, gx_bits, shared):
     """g_x's GEMM joins g_w's launch, where its tiles do the whole K, only while giving up its own split
     of K or its own tile costs less than a launch: the roles launched, and the bits of both forms."""
@@ -1228,7 +1227,7 @@ def split_flags(ws):
 
 
 @pytest.mark.parametrize("O,I,handed_over", [(384, 256, False),    # 6 tiles of 128x128, 32 K stages: images of 8 slices
-                                             (896, 1024, True)])   # 56 tiles: 8 slices handed over
+                                             (896, 1024, True)])   # 56 tiles: 4 slices handed over
 @pytest.mark.parametrize("call", ["g_w", "both"])
 def test_split_k_hand_over_sees_fresh_partial_sums(gemm_mode, O, I, handed_over, call):
     """Two different inputs alternate through the same workspace, twelve back-to-back steps
@@ -1471,7 +1470,7 @@ def test_per_sample_tiling_shape_errors_and_gx_is_unaffected():
 
 @pytest.mark.parametrize("L,O,I,per_token,handed_over", [
     (512, 768, 768, True, False),     # one slice per g_w tile
-    (4096, 896, 1024, False, True),   # 56 g_w tiles in four slices handed over, one g_y scale for the tensor
+    (8192, 896, 1024, False, True),   # 56 g_w tiles in four slices handed over, one g_y scale for the tensor
     (4096, 128, 256, True, False)])   # two g_w tiles in four slices, images added by a second kernel
 def test_replayable_calls_in_a_hip_graph(L, O, I, per_token, handed_over):
     """With hot_config.replayable the launch tags come from an epoch in the workspace that every
@@ -1544,7 +1543,7 @@ def test_replayable_calls_give_the_bits_of_host_tagged_calls():
     transforms take the single-pass kernels (the g_x call twice in a row, so that the second
     call finds the first one's slots and flags in the workspace)."""
     hot = _hot()
-    L, O, I = 4096, 768, 1024         # 48 g_w tiles of 16 K stages: four slices handed over
+    L, O, I = 4096, 768, 1024         # 48 g_w tiles of 16 K stages: two slices handed over
     x, w, gy = make(L, O, I, seed=81)
     xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
     outs = {}
