@@ -518,15 +518,15 @@ double alone_us(const GemmCall& c, const GemmPlan& p, bool g_w) {
 // the whole of K.  g_w's slices and g_x's tile follow from the time of the whole launch (launch_us), whose constants
 // are fitted to backward calls of 10500 layers (64 to 201728 tokens, 64 to 65536 outputs, 64 to 11008 inputs), every
 // split, both tiles and two launches timed on each, with inputs that change from call to call: what is
-// chosen takes 0.5 % longer than the best of them on average.  Slices chosen without a look at g_x's
+// chosen takes 0.8 % longer than the best of them on average.  Slices chosen without a look at g_x's
 // workgroups, and sizes of g_x for which a launch is shared, took 2.2 %: 20736 tokens 832 x 2816 with g_w unsplit
 // 267 us a layer pass, 251 in two slices; 7880 x 1664 x 2757 in INT8 with bfloat16 g_w apart 214 us a call, 149 together; 128 x 40960
 // x 512 in INT8 together 266 us a pass, 144 apart, where g_x splits K in eight.
 // Two launches are looked at only where g_x has more than 28 stages (up to there they were the faster by 2 % on 19
-// of 7400 layers) or g_w a 256x256 tile of its own, whose time tile_shape_us puts too high: those have
-// to be 15 % slower for a shared launch (25921 tokens 3264 x 3840, bfloat16 g_w, 951 us a call together, 871 apart),
-// others 3 % faster for two.  128x128 g_x tiles in more workgroups than are resident have to be 3 % faster
-// than 128x256.
+// of 7400 layers) or g_w a 256x256 tile of its own, whose time tile_shape_us puts too high: there a shared launch
+// has to be 15 % faster by these figures and g_x short (25921 tokens 3264 x 3840, bfloat16 g_w, 951 us a call
+// together, 871 apart; 16384 x 7904 x 3584 a pass 1262 and 1193); others have to be 3 % faster apart.
+// 128x128 g_x tiles in more workgroups than are resident have to be 3 % faster than 128x256.
 GemmPairPlan plan_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, bool may_share) {
   GemmPairPlan apart, plan;
   apart.together = plan.together = false;
@@ -568,7 +568,8 @@ GemmPairPlan plan_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
       plan.x = GemmPlan{128, wide ? 256 : 128, cx.bits == 4 ? 64 : 128, 1, tiles, false, 0};
     }
   }
-  if (!plan.together || (x_stages <= 28 && apart.w.bm == 128)) return plan.together ? plan : apart;
+  if (!plan.together || (x_stages > 28 && apart.w.bm != 128)) return apart;
+  if (x_stages <= 28 && apart.w.bm == 128) return plan;
   const double us = alone_us(cx, apart.x, false) + alone_us(cw, apart.w, true) - 0.5;
   return us * (apart.w.bm == 128 ? 1.03 : 0.85) < best_us ? apart : plan;
 }

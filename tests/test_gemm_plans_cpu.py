@@ -29,6 +29,14 @@ def test_short_g_x_reductions_share_g_w_s_launch(L, O, I, gx_bits):
     assert p["one_launch"] and p["gx"][0] == 128 and p["gx"][2:] == (1, False)
 
 
+@pytest.mark.parametrize("L,O,I,gw_bits", [(16384, 7904, 3584, 16),    # a layer pass 1193, in one launch 1262
+                                           (15360, 7712, 3840, 8),     # 928, 953
+                                           (25136, 5952, 1600, 16)])   # 932, 969
+def test_large_tiles_of_both_gemms_keep_their_launches(L, O, I, gw_bits):
+    p = plan(L, O, I, gw_bits=gw_bits)
+    assert not p["one_launch"] and p["gw"][:2] == (256, 256)
+
+
 @pytest.mark.parametrize("L,O,I,gx_bits,least", [
     (20736, 832, 2816, 4, 2),      # a layer pass 251 with g_w in two slices, unsplit 267
     (56128, 576, 912, 4, 4),       # outputs of half sectors ...
