@@ -1038,23 +1038,57 @@ def test_bf16_gemm_on_the_large_tile():
 
 
 @pytest.mark.parametrize("wait_us", [200, 0])
-@pytest.mark.parametrize("L,O,I,handed_over", [(66000, 516, 1030, True),    # 45 tiles of 128x128, 15 of 256x256
-                                               (80000, 300, 260, False)])   # 9 tiles: images on the small tile
-def test_int8_gemm_large_tile_with_k_split(gemm_mode, L, O, I, handed_over, wait_us):
-    """A small output with a very long K (33000 and 40000 reduced tokens): the g_w GEMM takes the 256x256
-    tile with K in two slices handed over (with wait 0 the owner computes the other slice itself), or,
-    with few tiles, slices whose images a second kernel adds."""
+@pytest.mark.parametrize("L,O,I,handed_over", [(66000, 516, 1030, True),    # 45 tiles in five slices
+                                               (80000, 300, 260, False)])   # 9 tiles: images of the slices
+def test_int8_gemm_with_a_very_long_k(gemm_mode, L, O, I, handed_over, wait_us):
+    """A small output with a very long K (33000 and 40000 reduced tokens): the g_w GEMM takes 128x128 tiles
+    with slices handed over (with wait 0 the owner computes the other slices itself), or, with few tiles,
+    slices whose images a second kernel adds."""
     hot = _hot()
     hot.hot_debug_set_exchange_wait_us(wait_us)
     x, w, gy = make(L, O, I, seed=73)
     cfg = hot.Config(block=16, keep=8)
-    check_gw(hot, cfg, gy, x, f"large INT8 tile, K split, wait={wait_us}")
+    check_gw(hot, cfg, gy, x, f"very long K, wait={wait_us}")
     act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
     hot.hot_compress_activation(cfg, x.cuda(), act, ws)
     split_flags(ws).fill_(0x5A)
     hot.hot_linear_backward_gw(cfg, gy.cuda(), act, I, torch.empty((O, I), device="cuda"), ws)
     torch.cuda.synchronize()
     assert bool((split_flags(ws) != 0x5A).any()) == handed_over
+
+
+@pytest.mark.parametrize("L,O,I,call,slices", [(66192, 2064, 1932, "gw", 2),    # 72 tiles of 256x256, ragged both ways
+                                               (98352, 1872, 1418, "gw", 3),    # 48, K slices of unequal length
+                                               (2064, 33024, 1932, "gx", 2),
+                                               (1872, 49168, 1418, "gx", 3)])
+def test_int8_gemm_large_tile_with_k_split(gemm_mode, L, O, I, call, slices):
+    """The 256x256 INT8 tile with K in slices handed over: the plan, the flags its workgroups leave, and the
+    bits of 128x128 tiles without a split.  With wait 0 the owner computes the other slices itself."""
+    hot = _hot()
+    _say(f"[large split] {call} L={L} O={O} I={I}")
+    cfg = hot.Config(block=16, keep=8, gx_bits=8)
+    assert hot.hot_debug_gemm_plan(cfg, L, O, I)[call + "_alone"] == (256, 256, slices, False)
+    g = torch.Generator(device="cuda").manual_seed(76)
+    gy = torch.randn((L, O), generator=g, device="cuda")
+    ws = hot.alloc_workspace(cfg, L, O, I)
+    if call == "gw":
+        act = hot.alloc_act_buffer(cfg, L, I)
+        hot.hot_compress_activation(cfg, torch.randn((L, I), generator=g, device="cuda"), act, ws)
+        rows, run = O, lambda out: hot.hot_linear_backward_gw(cfg, gy, act, I, out, ws)
+    else:
+        w = torch.randn((O, I), generator=g, device="cuda")
+        rows, run = L, lambda out: hot.hot_linear_backward_gx(cfg, gy, w, hot.HOT_Q_PER_TOKEN, out, ws)
+    outs = []
+    for mode, wait_us in ((10, 200), (0, 200), (0, 0)):
+        gemm_mode(mode)
+        hot.hot_debug_set_exchange_wait_us(wait_us)
+        flags = split_flags(ws).fill_(0x5A)
+        outs.append(torch.full((rows, I), -7.0, device="cuda"))
+        run(outs[-1])
+        torch.cuda.synchronize()
+        written = int((flags.view(-1, 8) != 0x5A).any(1).sum())
+        assert written == (0 if mode else -(-rows // 256) * -(-I // 256) * (slices - 1))
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
 @pytest.mark.parametrize("L,O,I,bits", [(4096, 128, 128, 8), (4240, 130, 257, 8), (16400, 48, 260, 8),
@@ -1095,6 +1129,7 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
     (333, 4096, 40, 32, 333, 8, [7, 1, 30]),      # longest row, three rows kept
     (4096, 128, 130, 32, 0, 8, None),       # g_w images added by a second kernel
     (2048, 256, 320, 16, 0, 16, None),      # bfloat16 images
+    (8192, 2208, 2112, 16, 0, 16, None),    # bfloat16, on the 256x256 tile where it has a launch of its own
     (64, 96, 40, 32, 0, 16, None),          # bfloat16, one slice
     (8208, 2304, 768, 16, 0, 8, None),      # more workgroups than are resident at once
     (33024, 768, 768, 16, 0, 8, None),      # slices handed over, behind the shared g_y passes
