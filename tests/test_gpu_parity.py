@@ -1653,6 +1653,10 @@ def test_seeded_random_shapes_and_settings(exchange_wait, gemm_mode):
     (23456, 2080, 96, 32, 16, None, 4),      # a slab of one block at the end, narrow rows
     (14720, 3328, 80, 32, 16, "lp_l1", 8),
     (9600, 5152, 70, 32, 11, None, 4),       # a list of another length, column tiles that end inside
+    (7712, 6240, 64, 32, 16, None, 4),       # rows that end inside each step of registers ...
+    (5376, 9120, 36, 32, 16, "lp_l1", 4),
+    (10048, 5056, 33, 64, 32, None, 4),
+    (6976, 7104, 40, 64, 40, None, 8),       # ... for both block sizes
     (4288, 11264, 64, 64, 32, None, 8),      # the longest rows
     (12800, 4096, 33, 64, 64, "reversed", 4),
     (32768, 4096, 32, 64, 32, None, 4)])     # the most slabs
@@ -1678,4 +1682,33 @@ def test_rows_and_abs_max_from_one_read(L, O, I, n, keep, keep_idx, gx_bits):
             hot.hot_debug_set_backward_strategy(0)
         assert ("gyT_col_absmax" in roles) == (strategy == 3), roles
         out.append((gx, gw))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,L,O", [(32, 14720, 3328), (64, 10048, 5056)])
+@pytest.mark.parametrize("values", ["zero", "inf", "nan", "zero_but_one"])
+def test_rows_and_abs_max_of_special_values(n, L, O, values):
+    """All zeros, an infinity, a NaN, one value among zeros: as separate passes have them (a NaN is a NaN)."""
+    hot = _hot()
+    I = 64
+    cfg = hot.Config(block=n, keep=n // 2)
+    g = torch.Generator(device="cuda").manual_seed(92)
+    gy = torch.zeros((L, O), device="cuda")
+    if values in ("inf", "nan"):
+        gy.normal_(generator=g)[L // 2 + 5, O - 7] = float(values)
+    elif values == "zero_but_one":
+        gy[L - 1, 0] = -2.0
+    w, x = (torch.randn(shape, generator=g, device="cuda") for shape in ((O, I), (L, I)))
+    act, ws = hot.alloc_act_buffer(cfg, L, I), hot.alloc_workspace(cfg, L, O, I)
+    hot.hot_compress_activation(cfg, x, act, ws)
+    out = []
+    for strategy in (3, 0):
+        hot.hot_debug_set_backward_strategy(strategy)
+        try:
+            gx, gw, roles = backward_stages(hot, cfg, gy, w, act, hot.HOT_Q_PER_TOKEN, ws)
+        finally:
+            hot.hot_debug_set_backward_strategy(0)
+        assert ("gyT_col_absmax" in roles) == (strategy == 3), roles
+        out.append([torch.where(t.isnan(), 1 << 30, t.view(torch.int32)) for t in (gx, gw)])
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
