@@ -318,11 +318,11 @@ const char* hot_debug_stage_name(int stage);
 
 /* How the GEMMs of a layer are distributed in the modes set above, with a full-size workspace (host only, nothing
  * is launched): whether hot_linear_backward makes one launch of both, and for each its tile rows and columns, its
- * K slices, and whether a second kernel adds the slices' sums; the last two are those of
- * hot_linear_backward_gx (also with cached weights) and hot_linear_backward_gw. */
+ * K slices, whether a second kernel adds the slices' sums, and whether the output is stored with the streaming hint;
+ * the last two are those of hot_linear_backward_gx (also with cached weights) and hot_linear_backward_gw. */
 typedef struct hot_gemm_plan {
   int32_t one_launch;
-  int32_t gx[4], gw[4], gx_alone[4], gw_alone[4];
+  int32_t gx[5], gw[5], gx_alone[5], gw_alone[5];
 } hot_gemm_plan;
 hot_status hot_debug_gemm_plan(const hot_config* cfg, int64_t L, int64_t O, int64_t I, hot_gemm_plan* plan);
 

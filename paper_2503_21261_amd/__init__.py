@@ -45,7 +45,7 @@ class hot_config(C.Structure):
 
 
 class hot_gemm_plan(C.Structure):
-    _fields_ = [("one_launch", C.c_int32)] + [(f, C.c_int32 * 4) for f in ("gx", "gw", "gx_alone", "gw_alone")]
+    _fields_ = [("one_launch", C.c_int32)] + [(f, C.c_int32 * 5) for f in ("gx", "gw", "gx_alone", "gw_alone")]
 
 
 class HotError(RuntimeError):
@@ -416,11 +416,13 @@ def hot_debug_profile_sequence():
 
 
 def hot_debug_gemm_plan(cfg: Config, L: int, O: int, I: int) -> dict:
-    """{one_launch: bool, gx / gw / gx_alone / gw_alone: (tile rows, tile columns, K slices, added by a second kernel)}."""
+    """{one_launch: bool, gx / gw / gx_alone / gw_alone: (tile rows, tile columns, K slices, added by a second kernel),
+    streams: which of the four store their output with the streaming hint}."""
     p = hot_gemm_plan()
     _check(lib().hot_debug_gemm_plan(C.byref(cfg.c()), L, O, I, C.byref(p)), "hot_debug_gemm_plan")
-    return dict(one_launch=bool(p.one_launch), **{f: (*list(getattr(p, f))[:3], bool(getattr(p, f)[3]))
-                                                  for f in ("gx", "gw", "gx_alone", "gw_alone")})
+    names = ("gx", "gw", "gx_alone", "gw_alone")
+    return dict(one_launch=bool(p.one_launch), streams={f for f in names if getattr(p, f)[4]},
+                **{f: (*list(getattr(p, f))[:3], bool(getattr(p, f)[3])) for f in names})
 
 
 def hot_debug_probe(kind: int, buf: torch.Tensor, iters: int = 1, stream=None) -> None:

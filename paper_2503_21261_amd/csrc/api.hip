@@ -739,16 +739,17 @@ hot_status hot_debug_gemm_plan(const hot_config* cfg, int64_t L, int64_t O, int6
                                 nullptr, nullptr, 0, nullptr);
   const GemmPairPlan p = plan_gemm_pair(gw, true, gx, g_backward_strategy.load() != 3);
   plan->one_launch = p.together;
-  const auto put = [](const GemmPlan& g, int32_t* out) {
+  const auto put = [](const GemmCall& c, const GemmPlan& g, bool in_pair, int32_t* out) {
     out[0] = g.bm;
     out[1] = g.bn;
     out[2] = g.split;
     out[3] = g.images;
+    out[4] = streams_out(c, g.tiles, in_pair);
   };
-  put(p.x, plan->gx);
-  put(p.w, plan->gw);
-  put(plan_gemm(gx.M, gx.N, gx.k_bytes, gx.bits, true, false), plan->gx_alone);
-  put(plan_gemm(gw.M, gw.N, gw.k_bytes, gw.bits, true, true), plan->gw_alone);
+  put(gx, p.x, p.together, plan->gx);
+  put(gw, p.w, p.together, plan->gw);
+  put(gx, plan_gemm(gx.M, gx.N, gx.k_bytes, gx.bits, true, false), false, plan->gx_alone);
+  put(gw, plan_gemm(gw.M, gw.N, gw.k_bytes, gw.bits, true, true), false, plan->gw_alone);
   return HOT_OK;
 }
 

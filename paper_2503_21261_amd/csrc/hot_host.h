@@ -266,6 +266,9 @@ struct GemmCall {
   int n;
   const unsigned long long* epoch;
 };
+// Whether a GEMM's output is stored with the streaming hint; `tiles`: of the output, in a launch of its own or in
+// one with the other gradient (`in_pair`).
+bool streams_out(const GemmCall& c, int64_t tiles, bool in_pair);
 hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage = -1);
 // Both GEMMs of a layer: one launch (`together`, up to a few thousand workgroups: `w` on 128x128 tiles, `x` on
 // unsplit tiles of 128 rows) or each with its own plan, which is also what `may_share` = false gives.

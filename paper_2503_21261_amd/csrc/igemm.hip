@@ -248,8 +248,31 @@ size_t gemm_scratch_bytes(int64_t M, int64_t N, int64_t k_bytes, int bits) {
   return small > large ? small : large;
 }
 
-namespace {
+// Whether output stores carry the streaming hint.  Measured on MI355X: it wins for INT8 / bfloat16 operands and for
+// INT4 GEMMs of up to 3072 codes of K (ViT-B fc2 at 50432 tokens 167 -> 134 us, ViT-B fc1 at 12608 tokens
+// 44.5 -> 39.6 us), and loses 3 % at 4096 codes and a wide output (LLM down-projection).
+// Where output rows are not whole 64-byte sectors, a sector that two stores share goes out in parts with the hint, and
+// those saturate memory when many outputs follow on few K stages (11744 tokens 256 x 3079 75.8 us with it,
+// 30.9 without; 4544 x 128 x 8862 70.1 and 33.2).  It pays there too
+//  - for an output of the L2s' size, at any K (608 x 992 x 6570 15.5 us with it, 16.2 without); below 6 MB both
+//    are the same within 1 %;
+//  - where the other gradient's workgroups keep the units busy between the stores, by K and a width whose tiles
+//    are under way together (16848 x 1152 x 2344 240 us a layer pass with it, 251 without; 12096 x 1088 x 4492 272 and
+//    290; 5536 x 576 x 5434 too short and wide, 134 and 125);
+//  - alone, where K is long and the tiles of a unit are many, so that their stores spread out (178000 x 896 x 5828 1728
+//    us with it, 1493 without: too short; 26595 x 1376 x 1332 124 and 134; 9062 x 1280 x 6163 too few, 112 and 96).
+// Mean loss against the better of both over such layers: 405 calls of g_x alone 0.57 % by this rule, 1.1 never,
+// 8.2 always; 242 in a launch of both 0.30, 1.3, 0.63.
+bool streams_out(const GemmCall& c, int64_t tiles, bool in_pair) {
+  const int64_t k = c.k_bytes * (c.bits == 4 ? 2 : 1);
+  if (c.bits == 4 && k > 3072) return false;
+  if (c.N % 16 == 0) return true;
+  const double mb = 4e-6 * (double)c.M * (double)c.N;
+  if (mb <= 22.0) return mb > 6.0;
+  return in_pair ? k >= 800 || (k >= 448 && c.N <= 2048) : k >= 1300 && tiles >= 6 * (int64_t)compute_units();
+}
 
+namespace {
 
 // Waves per workgroup: 2x2, except 4x2 for the 256x256 INT8 and bfloat16 tiles.  Four waves,
 // alone on their SIMDs, cannot hide the LDS traffic of those operands (two and four times the
@@ -363,7 +386,7 @@ hipError_t launch_tile(GemmArgs g, int64_t k_bytes, const GemmPlan& plan, hipStr
   }
 }
 
-GemmArgs gemm_args(const GemmCall& c) {
+GemmArgs gemm_args(const GemmCall& c, int64_t tiles, bool in_pair) {
   GemmArgs g;
   g.A = c.A;
   g.B = c.B;
@@ -382,13 +405,7 @@ GemmArgs gemm_args(const GemmCall& c) {
   g.col_scale = c.col_scale;
   g.inv_n = 1.0f / (float)c.n;
   g.xcd_cols = 0;
-  // measured on MI355X: streaming stores win for INT8 / bfloat16 operands and for INT4 GEMMs of
-  // up to 3072 codes of K (ViT-B fc2 at 50432 tokens 167 -> 134 us, ViT-B fc1 at 12608 tokens
-  // 44.5 -> 39.6 us), and lose 3 % at 4096 codes and a wide output (LLM down-projection).  Only where output
-  // rows are whole 64-byte sectors: a sector that two stores share goes out in parts with the hint (11744
-  // tokens 256 x 3079 75.8 us with it, 30.9 without; 4544 x 128 x 8862 70.1 and 33.2; of whole sectors 37627 x
-  // 256 x 1584 103 and 122, 20000 x 512 x 1008 22.6 and 23.8).
-  g.stream_out = (c.bits != 4 || c.k_bytes * 2 <= 3072) && c.N % 16 == 0 ? 1 : 0;
+  g.stream_out = streams_out(c, tiles, in_pair) ? 1 : 0;
   return g;
 }
 
@@ -578,7 +595,7 @@ hipError_t launch_gemm_pair(const GemmCall& cw, const GemmCall& cx, const GemmPa
   const GemmPlan& p = plan.w;
   const bool int4 = cx.bits == 4, narrow = plan.x.bn == 128;
   const int64_t rows = ceil_div(cx.M, 128), w = p.tiles * p.split, x = plan.x.tiles;
-  GemmArgs gw = gemm_args(cw), gx = gemm_args(cx);
+  GemmArgs gw = gemm_args(cw, p.tiles, true), gx = gemm_args(cx, x, true);
   gw.nk_total = (int)(cw.k_bytes / 128);
   gw.tiles_m = (int)ceil_div(cw.M, 128);
   gw.tiles_n = (int)ceil_div(cw.N, 128);
@@ -604,7 +621,7 @@ hipError_t launch_gemm_pair(const GemmCall& cw, const GemmCall& cx, const GemmPa
 
 hipError_t launch_igemm(const GemmCall& c, const GemmPlan& plan, hipStream_t s, int gemm_stage) {
   if (c.M <= 0 || c.N <= 0) return hipSuccess;
-  const GemmArgs g = gemm_args(c);
+  const GemmArgs g = gemm_args(c, plan.tiles, false);
   const int64_t k_bytes = c.k_bytes;
   const int bits = c.bits;
   const int gs = gemm_stage;

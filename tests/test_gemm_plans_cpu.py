@@ -48,6 +48,22 @@ def test_g_w_is_split_finer_in_front_of_many_g_x_workgroups(L, O, I, gx_bits, le
     assert p["one_launch"] and p["gw"][:2] == (128, 128) and p["gw"][2] >= least
 
 
+@pytest.mark.parametrize("L,O,I,block,gx_bits,where,streams", [
+    (12608, 3072, 768, 16, 4, "gx", True),       # whole sectors
+    (2048, 4096, 11008, 64, 4, "gx_alone", False),   # a long INT4 reduction
+    (11744, 256, 3079, 16, 4, "gx_alone", False),    # broken sectors: 31 us, 76 with the hint
+    (608, 992, 6570, 16, 4, "gx_alone", True),       # 15.5, 16.2 without: 16 MB
+    (1024, 384, 771, 16, 4, "gx_alone", False),      # 3 MB
+    (16848, 1152, 2344, 16, 4, "gx", True),          # a layer pass 240, 251 without
+    (5536, 576, 5434, 16, 4, "gx", False),           # 125, with it 134
+    (8432, 512, 1862, 16, 4, "gx", True),
+    (26592, 1376, 1332, 32, 4, "gx_alone", True),    # 124, 134 without
+    (9088, 1280, 6163, 64, 4, "gx_alone", False),    # 96, with it 112
+    (178432, 896, 5828, 64, 4, "gx_alone", False)])  # 1493, 1728
+def test_streaming_stores_of_broken_sectors(L, O, I, block, gx_bits, where, streams):
+    assert (where in plan(L, O, I, block=block, gx_bits=gx_bits)["streams"]) == streams
+
+
 def test_plans_stay_within_their_limits():
     rng = random.Random(5)
 
