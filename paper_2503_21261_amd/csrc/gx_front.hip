@@ -275,11 +275,13 @@ long long wait_ticks(int64_t wait_us, int64_t bytes) {
 
 // From 48 M elements on no form of the single-pass column kernel holds the kept values (42 M at most: 512
 // workgroups, 160 registers), so that the abs-max pass is there to be saved; 16-row blocks have the shared
-// passes.  Rows of a workgroup each; below 4096 columns the few rows under way at the registers of a
-// 64-row block cost more than the read (32000 x 2112, two columns per lane: 287 us a backward call apart, 312
-// together); above 11264 a slab no longer fits an XCD's L2.  At least four column workgroups per slab within kMaxPartials.
+// passes.  From 2048 columns on (layer passes with 512 inputs, apart and together: 64-row blocks 23872 x 2048 218 and
+// 196 us, 32000 x 2112 309 and 278, 23424 x 3072 285 and 248, 28544 x 4032 430 and 367; 32-row blocks 30464 x 2048 242 and
+// 220): below, the LP_L1 list, whose column tiles are the slower ones, loses what the default list gains (32-row
+// blocks 31200 x 1568 213 and 221, 64-row blocks 32704 x 1536 258 and 261 with it, 31872 x 1536 246 and 225 with the default).
+// Above 11264 a slab no longer fits an XCD's L2.  At least four column workgroups per slab within kMaxPartials.
 bool rows_and_absmax_applies(const Config& cfg, int64_t L, int64_t O) {
-  return cfg.n >= 32 && cfg.gw_bits == 8 && cfg.sample_tokens == 0 && (cfg.n == 32 ? O > 2048 : O >= 4096) && O <= 11264 &&
+  return cfg.n >= 32 && cfg.gw_bits == 8 && cfg.sample_tokens == 0 && O >= 2048 && O <= 11264 &&
          L * O >= 48ll * 1000 * 1000 && ceil_div(L, kSlabRows) <= kMaxPartials / 4;
 }
 

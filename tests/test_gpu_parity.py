@@ -1657,6 +1657,9 @@ def test_seeded_random_shapes_and_settings(exchange_wait, gemm_mode):
     (5376, 9120, 36, 32, 16, "lp_l1", 4),
     (10048, 5056, 33, 64, 32, None, 4),
     (6976, 7104, 40, 64, 40, None, 8),       # ... for both block sizes
+    (23488, 2048, 33, 64, 32, None, 4),      # the fewest columns
+    (23456, 2048, 34, 32, 16, None, 8),
+    (20032, 2432, 48, 64, 32, "lp_l1", 8),
     (4288, 11264, 64, 64, 32, None, 8),      # the longest rows
     (12800, 4096, 33, 64, 64, "reversed", 4),
     (32768, 4096, 32, 64, 32, None, 4)])     # the most slabs
