@@ -151,9 +151,16 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle alone, a Stream object of which costs a call over a microsecond; private to torch, so
+# that a torch without it takes the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
-    if stream is None:   # the handle alone: a Stream object of it costs a call over a microsecond
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+    if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device()) or None
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
 

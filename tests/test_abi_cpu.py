@@ -192,3 +192,16 @@ def test_binding_refuses_host_tensors():
     x = torch.zeros(64, 64)
     with pytest.raises(ValueError):
         hot.hot_compress_activation(cfg, x, torch.zeros(10, dtype=torch.uint8), torch.zeros(10, dtype=torch.uint8))
+
+
+def test_current_stream_without_torch_s_private_handle(monkeypatch):
+    """Either way to the current stream gives its handle, and None for the default stream."""
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    for handle, want in ((0x50, 0x50), (0, None)):
+        monkeypatch.setattr(hot, "_raw_stream", lambda device: handle if device == 3 else -1)
+        assert hot._stream(None) == want
+        monkeypatch.setattr(hot, "_raw_stream", None)
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=handle))
+        assert hot._stream(None) == want
