@@ -109,7 +109,8 @@ int64_t best_split(const SplitCost& c, int64_t tiles, int64_t stages, int64_t mo
   return best;
 }
 // The same for 256x256 INT8 tiles in `s` slices (260 layers): 110224 tokens 512 x 4416 (140 tiles of
-// 128x128) 192 us in 3 slices on the large tile, 152 in 4 on the small one; 112928 x 1536 x 1952 209 and 242.
+// 128x128) 198 us in 3 slices on the large tile, 164 in 3 on the small one (205 in 4, beyond the resident
+// count); 112928 x 1536 x 1952 204 in 3 slices and 237.
 double large_split_us(int64_t stages, int64_t s) { return 1.25 * (double)ceil_div(stages, s) + 6.75 * (double)(s - 1) - 8.1; }
 // Cost of a tile shape, fitted to measurements on MI355X: a compute unit works through its share of
 // the tiles, each costing its operations at the rate the tile sustains plus its output bytes
@@ -211,9 +212,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t k_bytes, int bits, bool scratch
     const int64_t l = large_tile_split(M, N, k_bytes, bits, cus);
     if (l) {
       p.bm = p.bn = 256;
-      if (tiles <= 2 * (int64_t)cus &&
-          split_us(cost, tiles, nk, best_split(cost, tiles, nk, most, cus), cus) <= large_split_us(nk, l))
-        p.bm = p.bn = 128;
+      if (split_us(cost, tiles, nk, best_split(cost, tiles, nk, most, cus), cus) <= large_split_us(nk, l))
+        p.bm = p.bn = 128;   // at most 512 tiles, of which every large one is four
       p.tiles = ceil_div(M, p.bm) * ceil_div(N, p.bn);
       if (p.bm == 256) {
         p.split = (int)l;
@@ -460,10 +460,12 @@ namespace {
 // workgroup, and in a launch that fills every place several times over; and for what is not a stage
 // (first loads, epilogue).
 struct StageTimes { double one, two, full, each; };
-constexpr StageTimes kTimesW{0.64, 1.43, 0.71, 3.57};         // g_w, 128-byte stages
-constexpr StageTimes kTimesX4{0.464, 0.561, 0.763, 4.08};     // g_x, INT4 on 128x128 tiles, 64-byte stages
-constexpr StageTimes kTimesX4Wide{0.723, 0.932, 1.203, 5.4};  // the same on 128x256
-constexpr StageTimes kTimesX8{0.542, 0.58, 1.018, 3.68};      // g_x, INT8, 128-byte stages
+constexpr StageTimes kTimesW{0.67, 1.86, 1.29, 2.6};      // g_w, 128-byte stages
+constexpr StageTimes kTimesX4{0.48, 0.65, 0.80, 3.8};     // g_x, INT4 on 128x128 tiles, 64-byte stages
+constexpr StageTimes kTimesX4Wide{0.56, 1.16, 1.20, 6.5};  // the same on 128x256
+constexpr StageTimes kTimesX8{0.60, 1.16, 1.44, 3.4};     // g_x, INT8, 128-byte stages
+// An unsplit GEMM on 256x256 INT8 or bfloat16 tiles as a launch between a step's other kernels.
+constexpr Cand kLargeAlone{256, 256, 1, 0.097, 0.125, 4.4};
 // A GEMM's part of a launch (wgs = 0: the launch has none).
 struct Part {
   int64_t wgs, stages;   // workgroups, K stages of each
@@ -475,41 +477,35 @@ struct Part {
 constexpr Part kNoPart{0, 0, kTimesW, 1, false, 0.0};
 // us of a launch of `w`'s workgroups with `x`'s behind them on the chip's places, two to a unit: the longest of
 // g_w with its hand-over, of g_x from when its last workgroups find a place, and of all the work over all
-// places.  `broken`: stores of x that leave parts of 64-byte sectors; once they saturate memory (5 MB per us),
-// g_w's loads wait behind them (62646 tokens 336 x 1477: 1.4 us a stage).
-double launch_us(const Part& w, const Part& x, bool broken) {
+// places.
+double launch_us(const Part& w, const Part& x) {
   const double cus = compute_units(), places = 2 * cus, W = (double)w.wgs, X = (double)x.wgs;
-  const double x_each = x.t.each + 0.006 * x.store_kb;
+  const double x_each = x.t.each + 0.0095 * x.store_kb;
   const double x1 = X > 0 ? (double)x.stages * x.t.one + x_each : 0.0;
   const double x2 = X > 0 ? (double)x.stages * x.t.two + x_each : 0.0;
   const double x3 = X > 0 ? (double)x.stages * x.t.full + x_each : 0.0;
-  double slow = 1.0;
-  if (broken && X > 0) {
-    const double over = (X < places ? X : places) * x.store_kb / 1024.0 / x2 / 5.0 - 1.09;
-    slow += 4.9 * (over < 0.0 ? 0.0 : over < 1.0 ? over : 1.0);
-  }
   const double w1 = W > 0 ? (double)w.stages * w.t.one + w.t.each : 0.0;
-  const double w2 = W > 0 ? (double)w.stages * w.t.two * slow + w.t.each : 0.0;
+  const double w2 = W > 0 ? (double)w.stages * w.t.two + w.t.each : 0.0;
   const double w3 = W > 0 ? (double)w.stages * w.t.full + w.t.each : 0.0;
   const bool resident = W + X <= places, shared = W + X > cus;   // all at once; some unit has two
   double wt = w1, xt = x1;
   if (shared) {
     // what is left of the longer GEMM goes on at its own rate once the other one has ended
     const double beside = resident ? x2 : X * x2 / (places - W > 64 ? places - W : 64.0);
-    const double alone = W <= cus ? w1 : W > 0 ? (double)w.stages * w.t.two + w.t.each : 0.0;
+    const double alone = W <= cus ? w1 : w2;
     wt = w2 <= beside ? w2 : beside + (1.0 - beside / w2) * alone;
     xt = x2 <= w2 ? x2 : w2 + (1.0 - w2 / x2) * (resident && X <= cus ? x1 : x2);
   }
   const bool hands = w.slices > 1 && !w.images;
   const double load = W / places;
-  const double hand = hands ? 2.47 + 0.79 * (double)(w.slices - 1) + 9.4 * (load < 2.0 ? load : 2.0) : 0.0;
-  if (W > places) wt = w3 * (load + 0.61);
+  const double hand = hands ? 3.6 + 1.07 * (double)(w.slices - 1) + 7.3 * (load < 2.0 ? load : 2.0) : 0.0;
+  if (W > places) wt = w3 * (load + 0.66);
   const double waits = (W + (X < places ? X : places) - places) / places * w3;
   double t = wt + hand;
   if (xt + (waits > 0.0 ? waits : 0.0) > t) t = xt + (waits > 0.0 ? waits : 0.0);
-  const double all = (W * w3 + X * x3) / places + 0.61 * x3 + 0.56 * hand;
+  const double all = (W * w3 + X * x3) / places + 0.66 * x3 + 0.54 * hand;
   if (!resident && all > t) t = all;
-  return t + (w.images ? 2.9 + 0.027 * W : 0.0) + 0.7;
+  return t + (w.images ? 2.9 + 0.019 * W : 0.0) + 0.7;
 }
 const StageTimes& x_times(int bits, bool wide) { return bits != 4 ? kTimesX8 : wide ? kTimesX4Wide : kTimesX4; }
 // us of a GEMM in a launch of its own.
@@ -518,12 +514,12 @@ double alone_us(const GemmCall& c, const GemmPlan& p, bool g_w) {
   if (p.bm == 128 && p.bn == 128) {
     const StageTimes& t = g_w ? kTimesW : x_times(c.bits, false);
     const double store_kb = 4.0 * (double)c.M * (double)c.N / (double)p.tiles / 1024.0;
-    if (!g_w && p.split == 1) return launch_us(kNoPart, Part{p.tiles, stages, t, 1, false, store_kb}, false);
-    return launch_us(Part{p.tiles * p.split, ceil_div(stages, p.split), t, p.split, p.images, 0.0}, kNoPart, false);
+    if (!g_w && p.split == 1) return launch_us(kNoPart, Part{p.tiles, stages, t, 1, false, store_kb});
+    return launch_us(Part{p.tiles * p.split, ceil_div(stages, p.split), t, p.split, p.images, 0.0}, kNoPart);
   }
   if (p.split > 1) return large_split_us(stages, p.split) + 8.0;
   const double K = (double)c.k_bytes * (c.bits == 4 ? 2 : 1);
-  if (c.bits != 4) return tile_shape_us(kCands8[1], c.M, c.N, K, compute_units());
+  if (c.bits != 4) return tile_shape_us(kLargeAlone, c.M, c.N, K, compute_units());
   int i = 0;
   while (kCands4[i].bm != p.bm || kCands4[i].bn != p.bn) ++i;
   return tile_shape_us(kCands4[i], c.M, c.N, K, compute_units());
@@ -533,16 +529,17 @@ double alone_us(const GemmCall& c, const GemmPlan& p, bool g_w) {
 
 // Whether the two GEMMs of a layer share a launch, g_w's plan in it and the tile of g_x, whose workgroups then do
 // the whole of K.  g_w's slices and g_x's tile follow from the time of the whole launch (launch_us), whose constants
-// are fitted to backward calls of 10500 layers (64 to 201728 tokens, 64 to 65536 outputs, 64 to 11008 inputs), every
-// split, both tiles and two launches timed on each, with inputs that change from call to call: what is
-// chosen takes 0.8 % longer than the best of them on average.  Slices chosen without a look at g_x's
+// are fitted to layer passes of 3600 layers (128 to 201728 tokens, 64 to 11008 outputs and inputs), every
+// split, both tiles and two launches timed on each in the same buffers: what is chosen takes 0.4 % longer than the best
+// of them on average, more than 5 % on 44.  Slices chosen without a look at g_x's
 // workgroups, and sizes of g_x for which a launch is shared, took 2.2 %: 20736 tokens 832 x 2816 with g_w unsplit
-// 267 us a layer pass, 251 in two slices; 7880 x 1664 x 2757 in INT8 with bfloat16 g_w apart 214 us a call, 149 together; 128 x 40960
-// x 512 in INT8 together 266 us a pass, 144 apart, where g_x splits K in eight.
+// 257 us a layer pass, 239 in two slices; 7880 x 1664 x 2757 in INT8 with bfloat16 g_w apart 214 us a call, 149 together; 128 x 40960
+// x 512 in INT8 together 266 us a pass, 138 apart, where g_x splits K in eight.
 // Two launches are looked at only where g_x has more than 28 stages (up to there they were the faster by 2 % on 19
-// of 7400 layers) or g_w a 256x256 tile of its own, whose time tile_shape_us puts too high: there a shared launch
-// has to be 15 % faster by these figures and g_x short (25921 tokens 3264 x 3840, bfloat16 g_w, 951 us a call
-// together, 871 apart; 16384 x 7904 x 3584 a pass 1262 and 1193); others have to be 3 % faster apart.
+// of 7400 layers) or g_w a 256x256 tile of its own.  There a shared launch has to be 10 % faster by these figures, whose
+// error grows with the layer: of 996 such layers it is taken on 732 and 6.5 % faster on average over all (13653
+// x 3600 x 1060 in INT8 368 us and 306, 6784 x 5824 x 768 207 and 181), more than 2 % slower on six; without that
+// margin on twenty (15360 x 7712 x 3840 981 us apart, 1027 together).
 // 128x128 g_x tiles in more workgroups than are resident have to be 3 % faster than 128x256.
 GemmPairPlan plan_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx, bool may_share) {
   GemmPairPlan apart, plan;
@@ -572,7 +569,7 @@ GemmPairPlan plan_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
     for (int64_t s = image_split ? 0 : 1; s <= max_slices; ++s) {   // 0: images
       const int64_t slices = s ? s : image_split, wgs = w.tiles * slices;
       if (s > 1 && wgs > places) break;
-      double us = launch_us(Part{wgs, ceil_div(stages, slices), kTimesW, slices, s == 0, 0.0}, px, cx.N % 16 != 0);
+      double us = launch_us(Part{wgs, ceil_div(stages, slices), kTimesW, slices, s == 0, 0.0}, px);
       if (cx.bits == 4 && !wide && wgs + tiles > places) us *= 1.03;
       if (us >= best_us) continue;
       best_us = us;
@@ -585,10 +582,10 @@ GemmPairPlan plan_gemm_pair(const GemmCall& cw, bool images, const GemmCall& cx,
       plan.x = GemmPlan{128, wide ? 256 : 128, cx.bits == 4 ? 64 : 128, 1, tiles, false, 0};
     }
   }
-  if (!plan.together || (x_stages > 28 && apart.w.bm != 128)) return apart;
+  if (!plan.together) return apart;
   if (x_stages <= 28 && apart.w.bm == 128) return plan;
   const double us = alone_us(cx, apart.x, false) + alone_us(cw, apart.w, true) - 0.5;
-  return us * (apart.w.bm == 128 ? 1.03 : 0.85) < best_us ? apart : plan;
+  return us * (apart.w.bm == 128 ? 1.0 : 0.9) < best_us ? apart : plan;
 }
 
 hipError_t launch_gemm_pair(const GemmCall& cw, const GemmCall& cx, const GemmPairPlan& plan, hipStream_t s, int stage) {

@@ -30,11 +30,20 @@ def test_short_g_x_reductions_share_g_w_s_launch(L, O, I, gx_bits):
 
 
 @pytest.mark.parametrize("L,O,I,gw_bits", [(16384, 7904, 3584, 16),    # a layer pass 1193, in one launch 1262
-                                           (15360, 7712, 3840, 8),     # 928, 953
-                                           (25136, 5952, 1600, 16)])   # 932, 969
+                                           (15360, 7712, 3840, 8),     # 982, 1027
+                                           (25920, 3264, 3840, 16)])   # 863, 904
 def test_large_tiles_of_both_gemms_keep_their_launches(L, O, I, gw_bits):
     p = plan(L, O, I, gw_bits=gw_bits)
     assert not p["one_launch"] and p["gw"][:2] == (256, 256)
+
+
+@pytest.mark.parametrize("L,O,I,gx_bits,gw_bits", [(13648, 3600, 1060, 8, 8),    # a layer pass 306, apart 368
+                                                   (20816, 3840, 1113, 4, 16),   # 437, 548
+                                                   (6784, 5824, 768, 4, 8),      # 181, 207
+                                                   (7072, 5360, 1214, 8, 8)])    # 226, 250
+def test_large_g_w_tiles_are_given_up_where_a_launch_gains_by_it(L, O, I, gx_bits, gw_bits):
+    p = plan(L, O, I, gx_bits=gx_bits, gw_bits=gw_bits)
+    assert p["one_launch"] and p["gw_alone"][0] == 256 and p["gw"][:2] == (128, 128)
 
 
 @pytest.mark.parametrize("L,O,I,gx_bits,least", [

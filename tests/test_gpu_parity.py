@@ -1120,8 +1120,9 @@ def test_gw_gemm_with_combined_images(gemm_mode, L, O, I, bits):
 
 @pytest.mark.parametrize("L,O,I,n,S,gw_bits,keep_idx", [
     (512, 768, 768, 16, 0, 8, None),        # one slice per g_w tile
-    (3136, 448, 1792, 16, 49, 8, [0, 1, 2, 4, 8, 5, 3, 12]),   # padded blocks; 128x256 g_x tiles, or (INT8) slices handed over
+    (3136, 448, 1792, 16, 49, 8, [0, 1, 2, 4, 8, 5, 3, 12]),   # padded blocks, 128x256 g_x tiles
     (3330, 1008, 771, 16, 333, 8, None),    # ragged in every direction, one column per lane
+    (9990, 1008, 771, 16, 333, 8, None),    # the same with slices handed over
     (8192, 640, 65, 16, 0, 8, None),        # two blocks per wave
     (8192, 640, 64, 32, 0, 8, None),
     (16384, 640, 33, 64, 0, 8, None),
@@ -1193,7 +1194,7 @@ def backward_stages(hot, cfg, gy, w, act, q, ws):
     (2048, 3072, 512, 8, True),      # 24 stages
     (512, 16384, 256, 8, False),
     (1024, 5120, 2048, 8, False),    # 40 stages, split in two
-    (12800, 4096, 1024, 8, True),    # the 256x256 INT8 tile
+    (12800, 4096, 1024, 8, False),   # the 256x256 INT8 tile
     (4096, 1024, 4096, 8, True),     # the same tile, a short K
     (8192, 3072, 4096, 8, False),    # the same tile, for g_w too
     (128, 32768, 128, 8, False)])    # 256 stages, split in eight
@@ -1578,7 +1579,7 @@ def test_replayable_calls_give_the_bits_of_host_tagged_calls():
     transforms take the single-pass kernels (the g_x call twice in a row, so that the second
     call finds the first one's slots and flags in the workspace)."""
     hot = _hot()
-    L, O, I = 4096, 768, 1024         # 48 g_w tiles of 16 K stages: two slices handed over
+    L, O, I = 8192, 768, 1024         # 48 g_w tiles of 32 K stages: slices handed over, in both launches
     x, w, gy = make(L, O, I, seed=81)
     xd, wd, gyd = x.cuda(), w.cuda(), gy.cuda()
     outs = {}
